@@ -526,15 +526,14 @@ hdc_status hdc_eval_configs(void *stream,
  *             (hdc_eval_configs; compute is ignored, x_type is the
  *             feature type of the job)
  *   variants  encoder / classifier: HDC_TILE_DMA_2X2 and HDC_TILE_DMA_1X1
- *             (projection staged straight into LDS; two query tiles x two
- *             dimension tiles per wave, or one of each; int8 features on the
- *             int8 path), HDC_TILE_DMA_2X3 (classifier only, one class tile,
- *             F <= 640: two query tiles x three dimension tiles, 96-
- *             dimension chunks in two LDS stages; it cannot split its
- *             dimensions, so a batch too small to fill the device runs on
- *             the 2x2 shape with dimension splits instead),
- *             HDC_TILE_REG_QT2 and HDC_TILE_REG_QT1 (register
- *             staging, two or one query tiles of 32 per wave);
+ *             (projection staged straight into LDS; two query tiles per wave,
+ *             or one with two waves per SIMD), HDC_TILE_DMA_2X3,
+ *             HDC_TILE_REG_QT2 and HDC_TILE_REG_QT1 (register staging, two or
+ *             one query tiles of 32 per wave).  Byte features (int8, uint8)
+ *             run on the direct-staged shape of their bucket under every id
+ *             it lists, except that HDC_TILE_DMA_1X1 is a shape of its own on
+ *             int8 features up to 640 wide and 64 classes; the register-
+ *             staged shapes are those of fp32 features;
  *             sweep: HDC_TILE_SWEEP_256 (work items of 256 queries: int8
  *             configurations take two query tiles per wave where the
  *             registers allow), HDC_TILE_SWEEP_128 (items of 128) and

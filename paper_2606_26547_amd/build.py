@@ -29,15 +29,10 @@ FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE,
          "-Wno-unused-result"]
 
 
-# Per-source additions.  The int8 encoder keeps its MFMA accumulators in
-# ordinary VGPRs, so the epilogue that reads them between the next chunk's
-# MFMAs needs no accumulator-register moves; it takes the default machine
-# scheduler, the bf16 and E4M3 encoders the max-ILP one (each measured the
-# faster for its source).
-FILE_FLAGS = {"hdc_encode_i8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-              "hdc_encode_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-              "hdc_encode_fp8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-              "hdc_encode_fp8s.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
+# Per-source additions.  The int8-feature encoder keeps its MFMA accumulators
+# in ordinary VGPRs, so the epilogue that reads them between the next tile's
+# MFMAs needs no accumulator-register moves.
+FILE_FLAGS = {"hdc_encode_i8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str) -> str:

@@ -7,6 +7,7 @@
 
 namespace hdc {
 hipError_t launch_encode_i8(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
+hipError_t launch_encode_u8(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
 hipError_t launch_encode_fp8(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
 hipError_t launch_encode_bf16(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
 hipError_t launch_encode_f32(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
@@ -14,8 +15,17 @@ hipError_t launch_encode_fp8s(const EncodeArgs &a, int mode, Tile tile, hipStrea
 
 hipError_t launch_encode(const EncodeArgs &a, int compute, int mode, Tile tile, hipStream_t st)
 {
+    // bf16 on byte features is the int8 path: integers up to 255 and +-1 are
+    // exact in bf16 and their sums (|y| < 2^24) in its fp32 accumulator, so
+    // the signs and distances are those of the exact integer sums, which the
+    // int8 matrix instructions give at twice the rate and half the operand
+    // registers (65536 x 617, 4096 dimensions: 476 us against 143).
+    if (compute == C_BF16 && a.x_type != X_FP32) {
+        compute = C_I8;
+        tile = Tile{TV_AUTO};
+    }
     switch (compute) {
-    case C_I8: return launch_encode_i8(a, mode, tile, st);
+    case C_I8: return a.x_type == X_UINT8 ? launch_encode_u8(a, mode, tile, st) : launch_encode_i8(a, mode, tile, st);
     case C_FP8: return launch_encode_fp8(a, mode, tile, st);
     case C_BF16: return launch_encode_bf16(a, mode, tile, st);
     case C_F32: return launch_encode_f32(a, mode, tile, st);

@@ -50,6 +50,14 @@ __device__ __forceinline__ void lds_dma16(const void *base, uint32_t voff, const
                  : "memory", "m0");
 }
 
+// The same from a 64-bit address per lane.
+__device__ __forceinline__ void lds_dma16(const void *addr, const lds_u8 *dst)
+{
+    const uint32_t m = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m), "v"(addr)
+                 : "memory", "m0");
+}
+
 // ---------------------------------------------------------------------------
 // Operand traits.  Every compute type uses a 32x32 MFMA (rows = dimensions,
 // columns = queries).  KSTEP features are consumed per instruction; each
@@ -129,17 +137,23 @@ __device__ __forceinline__ uint32_t sign_word(float y) { return __float_as_uint(
 // ---------------------------------------------------------------------------
 // Conversions to the compute type.
 // ---------------------------------------------------------------------------
-// Four floats -> four OCP E4M3 bytes (round to nearest even), saturating at
-// +-448 like the format's "satfinite" conversion.
+// Four floats within +-448 -> four OCP E4M3 bytes (round to nearest even).
+__device__ __forceinline__ uint32_t fp8x4_raw(float a, float b, float c, float d)
+{
+    int w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
+    w = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
+    return (uint32_t)w;
+}
+
+// Four floats -> four OCP E4M3 bytes, saturating at +-448 like the format's
+// "satfinite" conversion.
 __device__ __forceinline__ uint32_t fp8x4(float a, float b, float c, float d)
 {
     a = fminf(fmaxf(a, -448.f), 448.f);
     b = fminf(fmaxf(b, -448.f), 448.f);
     c = fminf(fmaxf(c, -448.f), 448.f);
     d = fminf(fmaxf(d, -448.f), 448.f);
-    int w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
-    w = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
-    return (uint32_t)w;
+    return fp8x4_raw(a, b, c, d);
 }
 
 // Two floats -> two bfloat16 (round to nearest even) packed low/high.
@@ -150,11 +164,12 @@ __device__ __forceinline__ uint32_t bf16x2(float a, float b)
     return __builtin_bit_cast(uint32_t, r);
 }
 
-// Byte e of a dword as a float, for signed or unsigned 8-bit features.
+// Byte e of a dword as a float, for signed or unsigned 8-bit features:
+// (b ^ 0x80) - 128 for signed ones, without a branch on the type (exact).
 __device__ __forceinline__ float byte_value(uint32_t w, int e, bool is_signed)
 {
-    uint32_t b = (w >> (8 * e)) & 0xffu;
-    return is_signed ? (float)(int)(int8_t)b : (float)b;
+    const uint32_t u = w ^ (is_signed ? 0x80808080u : 0u);
+    return (float)((u >> (8 * e)) & 0xffu) + (is_signed ? -128.0f : 0.0f);
 }
 
 // Four integer features (bytes of w, signed or unsigned) split into E4M3
@@ -165,9 +180,9 @@ __device__ __forceinline__ float byte_value(uint32_t w, int e, bool is_signed)
 __device__ __forceinline__ void fp8_split4(uint32_t w, bool is_signed, uint32_t *hi, uint32_t *lo)
 {
     const uint32_t h = w & 0xF0F0F0F0u, l = w & 0x0F0F0F0Fu;
-    *hi = fp8x4(byte_value(h, 0, is_signed), byte_value(h, 1, is_signed), byte_value(h, 2, is_signed),
+    *hi = fp8x4_raw(byte_value(h, 0, is_signed), byte_value(h, 1, is_signed), byte_value(h, 2, is_signed),
                 byte_value(h, 3, is_signed));
-    *lo = fp8x4((float)(l & 0xffu), (float)((l >> 8) & 0xffu), (float)((l >> 16) & 0xffu), (float)(l >> 24));
+    *lo = fp8x4_raw((float)(l & 0xffu), (float)((l >> 8) & 0xffu), (float)((l >> 16) & 0xffu), (float)(l >> 24));
 }
 
 // Keep the bytes of w whose feature index (k0 + byte) is below F.

@@ -15,13 +15,14 @@ namespace hdc {
 // with the split index fastest each XCD's L2 holds the projection rows of
 // its splits only, not all of them.  In classify mode every split adds its
 // own part of the class sums, so a split launch writes them to
-// part[z][n][K] and k_split_argmin finishes.
-template <int CT, int XF, int QT, int KS, int KT, int MODE, bool DMA, int RT>
+// part[z][K][n] (a wave's stores cover whole lines) and k_split_argmin
+// finishes.
+template <int CT, int XF, int QT, int KS, int KT, int MODE, bool DMA, int RT, int SRC>
 __global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(Encoder<CT, XF, QT, KS, KT, MODE, 0, DMA, RT>::WAVES)))
+__attribute__((amdgpu_waves_per_eu(Encoder<CT, XF, QT, KS, KT, MODE, 0, DMA, RT, SRC>::WAVES)))
 void k_encode(EncodeArgs a)
 {
-    typedef Encoder<CT, XF, QT, KS, KT, MODE, 0, DMA, RT> E;
+    typedef Encoder<CT, XF, QT, KS, KT, MODE, 0, DMA, RT, SRC> E;
     __shared__ __align__(16) uint8_t smem[E::LDS];
     const int Z = a.nsplit;
     const int z = Z > 1 ? (int)blockIdx.x : 0;
@@ -54,7 +55,7 @@ void k_encode(EncodeArgs a)
                     for (int v = 0; v < 16; ++v) {
                         const int k = kt * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
                         if (k < a.K)
-                            a.part[((int64_t)z * a.n + q) * a.K + k] = dacc[kt][qt][v];
+                            a.part[((int64_t)z * a.K + k) * a.n + q] = dacc[kt][qt][v];
                     }
             }
             return;
@@ -70,194 +71,173 @@ void k_encode(EncodeArgs a)
     }
 }
 
-// Distances and argmin of a split classify launch: one wave per query,
-// lane k (and k + 64) sums class k's partials over the splits, dist_k =
-// popc_k - sum; the first smallest distance wins, as in Encoder::finish.
-static __global__ __launch_bounds__(256) void k_split_argmin(EncodeArgs a, int Z)
+// Distances and argmin of a split classify launch: a workgroup takes 32
+// queries, thread (slot, query) sums the splits' partials of classes slot,
+// slot + 32, ... (coalesced over the queries, all of a class's loads in
+// flight), dist_k = popc_k - sum.  The first smallest distance wins, as in
+// Encoder::finish: the minimum of (distance, class) packed in one integer
+// (distances are at most 65536, classes below 128).
+static __global__ __launch_bounds__(1024) void k_split_argmin(EncodeArgs a, int Z)
 {
-    const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (q >= a.n)
-        return;
-    int bd = 0x7fffffff, bk = 0;
-    for (int k0 = 0; k0 < a.K; k0 += 64) {
-        const int k = k0 + lane;
-        const bool kv = k < a.K;
+    __shared__ int best[16][32];
+    const int ql = threadIdx.x & 31, slot = threadIdx.x >> 5, wave = threadIdx.x >> 6;
+    const int64_t q = (int64_t)blockIdx.x * 32 + ql, qc = q < a.n ? q : a.n - 1;
+    const int64_t zs = a.n * a.K;
+    int m = 0x7fffffff;
+    for (int k = slot; k < a.K; k += 32) {
+        const int32_t *p = a.part + k * a.n + qc;
         int s = 0;
-        if (kv) {
-            const int32_t *p = a.part + q * a.K + k;
-            const int64_t zs = a.n * a.K;
-#pragma unroll 8
-            for (int z = 0; z < Z; ++z)
-                s += p[z * zs];
-        }
-        const int d = kv ? a.cpop[k] - s : 0x7fffffff;
-        if (kv && a.dists)
+#pragma unroll 16
+        for (int z = 0; z < Z; ++z)
+            s += p[z * zs];
+        const int d = a.cpop[k] - s;
+        if (a.dists && q < a.n)
             a.dists[q * a.K + k] = d;
-        if (d < bd) {
-            bd = d;
-            bk = k;
-        }
+        const int key = d * 128 + k;
+        m = key < m ? key : m;
     }
-    // first minimum across the lanes (lower class index on ties)
+    const int o = __shfl_xor(m, 32);
+    m = o < m ? o : m;
+    if (threadIdx.x % 64 < 32)
+        best[wave][ql] = m;
+    __syncthreads();
+    if (threadIdx.x < 32) {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const int od = __shfl_xor(bd, o), ok = __shfl_xor(bk, o);
-        if (od < bd || (od == bd && ok < bk)) {
-            bd = od;
-            bk = ok;
-        }
+        for (int w = 0; w < 16; ++w)
+            m = best[w][ql] < m ? best[w][ql] : m;
+        if (q < a.n)
+            a.labels[q] = m % 128;
     }
-    if (lane == 0)
-        a.labels[q] = bk;
 }
 
-template <int CT, int XF, int QT, int KS, int KT, int MODE, bool DMA = false, int RT = 1>
+template <int CT, int XF, int QT, int KS, int KT, int MODE, bool DMA = false, int RT = 1, int SRC = W_ROWS>
 static hipError_t launch_one(const EncodeArgs &a, hipStream_t st)
 {
-    typedef Encoder<CT, XF, QT, KS, KT, MODE, 0, DMA, RT> E;
+    typedef Encoder<CT, XF, QT, KS, KT, MODE, 0, DMA, RT, SRC> E;
     const int64_t blocks = (a.n + E::QPB - 1) / E::QPB;
     // resident workgroups: one per CU per wave per SIMD the kernel is built for
     const int Z = split_count(blocks, a.nd, a.max_split, 256 * E::WAVES);
     EncodeArgs b = a;
     b.nsplit = Z;
     const dim3 grid = Z > 1 ? dim3((unsigned)Z, (unsigned)blocks) : dim3((unsigned)blocks);
-    hipLaunchKernelGGL((k_encode<CT, XF, QT, KS, KT, MODE, DMA, RT>), grid, dim3(256), 0, st, b);
+    hipLaunchKernelGGL((k_encode<CT, XF, QT, KS, KT, MODE, DMA, RT, SRC>), grid, dim3(256), 0, st, b);
     if (MODE == M_CLASSIFY && Z > 1)
-        hipLaunchKernelGGL(k_split_argmin, dim3((unsigned)((a.n + 3) / 4)), dim3(256), 0, st, a, Z);
+        hipLaunchKernelGGL(k_split_argmin, dim3((unsigned)((a.n + 31) / 32)), dim3(1024), 0, st, a, Z);
     return hipGetLastError();
 }
 
-// int8 features on the int8 path stage the projection straight into LDS.
-// Where the registers allow (big_tile), each wave (one per SIMD) multiplies
-// two query tiles by two row tiles per chunk: four independent accumulator
-// chains, each projection fragment read from LDS feeds two MFMAs, and a
-// barrier every 80 MFMAs; the classifier can also take three row tiles per
-// chunk (TV_DMA_2X3: a barrier every 120 MFMAs, two stages).  Otherwise (or
-// when the tile table asks for it) one tile of each, two waves per SIMD.
-template <int KS, int KT, int MODE>
-static hipError_t launch_dma(const EncodeArgs &a, int variant, hipStream_t st)
+// The direct-staged shape of a bucket: two query tiles per wave (one wave per
+// SIMD), so that each projection fragment read from LDS feeds two MFMAs: with
+// one, four waves ask LDS for 128 bytes a cycle, all it has (784 uint8
+// features, n = 60000, 8192 dimensions: 820 us of encoding against 439).  Two row tiles per
+// chunk (80 MFMAs between barriers at 640 features) while three stages of
+// them fit the LDS, else one.  One query tile where the registers hold no
+// second beside the accumulators: four class tiles from 833 features, and the
+// split E4M3 type, whose query operand is twice as wide (there each fragment
+// feeds two MFMAs already).
+template <int CT, int KS, int KT, int MODE, int SRC>
+static hipError_t launch_direct(const EncodeArgs &a, hipStream_t st)
 {
-    if constexpr (MODE == M_CLASSIFY && big3_tile(KS, KT)) {
-        // 96-dimension chunks: a dimension split would end inside a chunk
-        // and read the next split's class tiles, so this shape never splits;
-        // a batch the 2x2 shape would split (too few query blocks to fill
-        // the device) runs on that shape instead
-        if (variant == TV_DMA_2X3) {
-            typedef Encoder<C_I8, 0, 2, KS, KT, MODE, 0, true, 2> E2;
-            const int64_t blocks = (a.n + E2::QPB - 1) / E2::QPB;
-            if (split_count(blocks, a.nd, a.max_split, 256 * E2::WAVES) == 1) {
-                EncodeArgs b = a;
-                b.max_split = 1;
-                return launch_one<C_I8, 0, 2, KS, KT, MODE, true, 3>(b, st);
-            }
-        }
-    }
-    if (a.poff && (!shift_tile(KS, KT) || variant == TV_DMA_1X1))
-        return hipErrorInvalidValue;   // the shifted projection: shift_tile shapes only
-    if constexpr (big_tile(KS, KT)) {
-        if (variant != TV_DMA_1X1)
-            return launch_one<C_I8, 0, 2, KS, KT, MODE, true, 2>(a, st);
-    }
-    return launch_one<C_I8, 0, 1, KS, KT, MODE, true, 1>(a, st);
+    constexpr int W = KS * Tr<CT>::KSTEP;
+    constexpr int QT = CT == C_FP8S || (W > 832 && KT == 4) ? 1 : 2;
+    return launch_one<CT, 0, QT, KS, KT, MODE, true, (W <= 640 ? 2 : 1), SRC>(a, st);
 }
 
-// One feature-width bucket: the tile variant picks direct or register
-// staging and the query tiles per wave; 0 is the built-in rule (direct
-// staging for int8 features on the int8 path, else as many query tiles as
-// fit).
-template <int CT, int XF, int KS>
-static hipError_t launch_bucket(const EncodeArgs &a, int mode, Tile tile, hipStream_t st)
+// One feature-width bucket of byte features: everything is staged directly,
+// whichever variant a tile table names, except that int8 features on the
+// int8 path also have one tile of each with two waves per SIMD (TV_DMA_1X1,
+// up to 640 features and two class tiles).  The register-staged kernels that
+// the other ids once named were slower for every bucket (one query tile: LDS
+// bound, as above).
+template <int CT, int KS, int KT, int MODE, int SRC>
+static hipError_t launch_bytes_kt(const EncodeArgs &a, int variant, hipStream_t st)
 {
-    const int v = tile.variant;
-    if constexpr (CT == C_I8 && XF == 0) {
-        const bool dma = a.x_type == X_INT8 && (v == TV_AUTO || v == TV_DMA_2X2 || v == TV_DMA_1X1 || v == TV_DMA_2X3);
-        if (a.poff && !dma)   // the shifted projection runs on direct staging only
-            return hipErrorInvalidValue;
-        if (dma) {
-            if (mode == M_ENCODE)
-                return launch_dma<KS, 1, M_ENCODE>(a, v, st);
-            const int kt = class_tiles(a.K);
-            if (kt == 1)
-                return launch_dma<KS, 1, M_CLASSIFY>(a, v, st);
-            if (kt == 2)
-                return launch_dma<KS, 2, M_CLASSIFY>(a, v, st);
-            return launch_dma<KS, 4, M_CLASSIFY>(a, v, st);
+    if (a.poff) {   // the shifted projections
+        if constexpr (SRC == W_ROWS && (CT == C_I8 ? shift_tile(KS, KT) : shift8_tile(KS, KT))) {
+            if (variant != TV_DMA_1X1)
+                return launch_direct<CT, KS, KT, MODE, SRC>(a, st);
         }
-    }
-    if constexpr (CT == C_FP8 && XF == 0) {
-        // E4M3 on the shifted projection (rows of E4M3 bytes 0 / 2.0, poff
-        // set): the direct-staged 2x2 shape, shift8_tile widths only
-        if (a.poff) {
-            if (v != TV_AUTO && v != TV_DMA_2X2)
-                return hipErrorInvalidValue;
-            if constexpr (shift8_tile(KS, 2)) {
-                if (mode == M_ENCODE)
-                    return launch_one<C_FP8, 0, 1, KS, 1, M_ENCODE, true, 1>(a, st);
-                const int kt = class_tiles(a.K);
-                if (kt == 1)
-                    return launch_one<C_FP8, 0, 1, KS, 1, M_CLASSIFY, true, 1>(a, st);
-                if (kt == 2)
-                    return launch_one<C_FP8, 0, 1, KS, 2, M_CLASSIFY, true, 1>(a, st);
-            }
-            return hipErrorInvalidValue;
-        }
-    }
-    if (a.poff)
         return hipErrorInvalidValue;
+    }
+    if constexpr (CT == C_I8 && SRC == W_ROWS && big_tile(KS, KT)) {
+        if (variant == TV_DMA_1X1)
+            return launch_one<CT, 0, 1, KS, KT, MODE, true, 1>(a, st);
+    }
+    if constexpr (CT == C_FP8 && SRC == W_ROWS)   // E4M3 rows: the shifted ones only
+        return hipErrorInvalidValue;
+    else
+        return launch_direct<CT, KS, KT, MODE, SRC>(a, st);
+}
+
+template <int CT, int W, int SRC>
+static hipError_t launch_bytes_bucket(const EncodeArgs &a, int mode, int variant, hipStream_t st)
+{
+    constexpr int KS = W / Tr<CT>::KSTEP;
+    if (mode == M_ENCODE)
+        return launch_bytes_kt<CT, KS, 1, M_ENCODE, SRC>(a, variant, st);
+    const int kt = class_tiles(a.K);
+    if (kt == 1)
+        return launch_bytes_kt<CT, KS, 1, M_CLASSIFY, SRC>(a, variant, st);
+    if (kt == 2)
+        return launch_bytes_kt<CT, KS, 2, M_CLASSIFY, SRC>(a, variant, st);
+    return launch_bytes_kt<CT, KS, 4, M_CLASSIFY, SRC>(a, variant, st);
+}
+
+// Byte features: the smallest compiled width (kIntWidths) >= F is used.
+template <int CT, int SRC>
+static hipError_t launch_bytes(const EncodeArgs &a, int mode, Tile tile, hipStream_t st)
+{
+    const int F = a.F, v = tile.variant;
+    if (F <= 64) return launch_bytes_bucket<CT, 64, SRC>(a, mode, v, st);
+    if (F <= 128) return launch_bytes_bucket<CT, 128, SRC>(a, mode, v, st);
+    if (F <= 192) return launch_bytes_bucket<CT, 192, SRC>(a, mode, v, st);
+    if (F <= 256) return launch_bytes_bucket<CT, 256, SRC>(a, mode, v, st);
+    if (F <= 320) return launch_bytes_bucket<CT, 320, SRC>(a, mode, v, st);
+    if (F <= 384) return launch_bytes_bucket<CT, 384, SRC>(a, mode, v, st);
+    if (F <= 512) return launch_bytes_bucket<CT, 512, SRC>(a, mode, v, st);
+    if (F <= 640) return launch_bytes_bucket<CT, 640, SRC>(a, mode, v, st);
+    if (F <= 832) return launch_bytes_bucket<CT, 832, SRC>(a, mode, v, st);
+    if (F <= 1024) return launch_bytes_bucket<CT, 1024, SRC>(a, mode, v, st);
+    return hipErrorInvalidValue;
+}
+
+// One width of fp32 features, register staged: as many query tiles per wave
+// as fit (the built-in rule), or the variant's.
+template <int CT, int W>
+static hipError_t launch_fp32_bucket(const EncodeArgs &a, int mode, Tile tile, hipStream_t st)
+{
+    constexpr int KS = W / Tr<CT>::KSTEP;
     constexpr int QM = qt2_fits(CT, KS) ? 2 : 1;
-    const int qt = (v == TV_REG_QT1 || QM == 1) ? 1 : 2;
+    const int qt = (tile.variant == TV_REG_QT1 || QM == 1) ? 1 : 2;
     if (mode == M_ENCODE) {
         if (qt == 2)
-            return launch_one<CT, XF, QM, KS, 1, M_ENCODE>(a, st);
-        return launch_one<CT, XF, 1, KS, 1, M_ENCODE>(a, st);
+            return launch_one<CT, 1, QM, KS, 1, M_ENCODE>(a, st);
+        return launch_one<CT, 1, 1, KS, 1, M_ENCODE>(a, st);
     }
     const int kt = class_tiles(a.K);
     if (kt == 1) {
         if (qt == 2)
-            return launch_one<CT, XF, QM, KS, 1, M_CLASSIFY>(a, st);
-        return launch_one<CT, XF, 1, KS, 1, M_CLASSIFY>(a, st);
+            return launch_one<CT, 1, QM, KS, 1, M_CLASSIFY>(a, st);
+        return launch_one<CT, 1, 1, KS, 1, M_CLASSIFY>(a, st);
     }
     if (kt == 2) {
         if (qt == 2)
-            return launch_one<CT, XF, QM, KS, 2, M_CLASSIFY>(a, st);
-        return launch_one<CT, XF, 1, KS, 2, M_CLASSIFY>(a, st);
+            return launch_one<CT, 1, QM, KS, 2, M_CLASSIFY>(a, st);
+        return launch_one<CT, 1, 1, KS, 2, M_CLASSIFY>(a, st);
     }
-    return launch_one<CT, XF, 1, KS, 4, M_CLASSIFY>(a, st);
+    return launch_one<CT, 1, 1, KS, 4, M_CLASSIFY>(a, st);
 }
 
-// Feature-count buckets: the smallest compiled width >= F is used.
+// fp32 features: the smallest compiled width (kF32Widths) >= F is used.
 template <int CT>
-static hipError_t launch_encode_ct(const EncodeArgs &a, int mode, Tile tile, hipStream_t st)
+static hipError_t launch_fp32(const EncodeArgs &a, int mode, Tile tile, hipStream_t st)
 {
-    constexpr int KSTEP = Tr<CT>::KSTEP;
-    const int F = a.F;
-    if (a.x_type == X_FP32) {
-        if constexpr (CT == C_I8 || CT == C_FP8S) {
-            return hipErrorInvalidValue;
-        } else {
-            if (F <= 64) return launch_bucket<CT, 1, 64 / KSTEP>(a, mode, tile, st);
-            if (F <= 128) return launch_bucket<CT, 1, 128 / KSTEP>(a, mode, tile, st);
-            if (F <= 256) return launch_bucket<CT, 1, 256 / KSTEP>(a, mode, tile, st);
-            return hipErrorInvalidValue;
-        }
-    }
-    if constexpr (CT == C_F32) {
+    if (a.poff)
         return hipErrorInvalidValue;
-    } else {
-        constexpr int K1 = 64 / KSTEP > 0 ? 64 / KSTEP : 1;
-        if (F <= 64) return launch_bucket<CT, 0, K1>(a, mode, tile, st);
-        if (F <= 128) return launch_bucket<CT, 0, 128 / KSTEP>(a, mode, tile, st);
-        if (F <= 192) return launch_bucket<CT, 0, 192 / KSTEP>(a, mode, tile, st);
-        if (F <= 256) return launch_bucket<CT, 0, 256 / KSTEP>(a, mode, tile, st);
-        if (F <= 320) return launch_bucket<CT, 0, 320 / KSTEP>(a, mode, tile, st);
-        if (F <= 384) return launch_bucket<CT, 0, 384 / KSTEP>(a, mode, tile, st);
-        if (F <= 512) return launch_bucket<CT, 0, 512 / KSTEP>(a, mode, tile, st);
-        if (F <= 640) return launch_bucket<CT, 0, 640 / KSTEP>(a, mode, tile, st);
-        if (F <= 832) return launch_bucket<CT, 0, 832 / KSTEP>(a, mode, tile, st);
-        if (F <= 1024) return launch_bucket<CT, 0, 1024 / KSTEP>(a, mode, tile, st);
-        return hipErrorInvalidValue;
-    }
+    if (a.F <= 64) return launch_fp32_bucket<CT, 64>(a, mode, tile, st);
+    if (a.F <= 128) return launch_fp32_bucket<CT, 128>(a, mode, tile, st);
+    if (a.F <= 256) return launch_fp32_bucket<CT, 256>(a, mode, tile, st);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace hdc

@@ -1,10 +1,11 @@
 // The gfx950 random-projection encoder: one 256-thread workgroup = 4
 // waves, each wave owning QT tiles of 32 queries whose features stay in
 // VGPRs (converted once to the compute type) for the whole launch.  The
-// workgroup walks the selected dimensions 32 at a time: the 32 gathered
-// projection rows of the next chunk are prefetched into registers, converted
-// and written to one half of a double-buffered LDS area while the current
-// chunk is multiplied on the matrix cores (rows = dimensions, columns =
+// workgroup walks the selected dimensions in chunks of one or two row tiles
+// of 32: the gathered projection rows go through LDS, copied straight into a
+// ring of stages (byte features) or through registers, converted, into a
+// double buffer (fp32 features and the sweep's other bodies), while an
+// earlier chunk is multiplied on the matrix cores (rows = dimensions, columns =
 // queries).  The 32x32 accumulator of each query tile then goes through one
 // of two epilogues, which run between the MFMAs of the following chunk:
 //   M_ENCODE   sign -> packed bits, one uint32 half-word per query per chunk
@@ -17,11 +18,21 @@
 // sweep can run it per work item.
 #pragma once
 
+#include <type_traits>
+
 #include "hdc_device.h"
 
 namespace hdc {
 
-template <int CT, int XF, int QT, int KS, int KT, int MODE, int WV = 0, bool DMA = false, int RT = 1>
+// Projection rows as the direct-staged kernels read them (their SRC
+// parameter): W_ROWS multiplies the bytes as they are (int8 features on the
+// int8 path, the shifted projections, E4M3 rows); W_ALT is int8 +-1 rows with
+// uint8 features on the int8 path (column sums), or converted to E4M3 as
+// each fragment is read on the E4M3 paths.
+enum Weights : int { W_ROWS = 0, W_ALT = 1 };
+
+template <int CT, int XF, int QT, int KS, int KT, int MODE, int WV = 0, bool DMA = false, int RT = 1,
+          int SRC = W_ROWS>
 struct Encoder {
     typedef Tr<CT> T;
     typedef typename T::frag frag;
@@ -33,31 +44,32 @@ struct Encoder {
     static constexpr int PIECES = (KS * KSTEP + 15) / 16;  // 16-byte int8 pieces per row (max)
     static constexpr int MP = (PIECES + 7) / 8;            // pieces per thread (8 threads / row)
     // DMA: projection rows and class fragments go from global memory
-    // straight into LDS (global_load_lds, 16 bytes per lane), three stages
-    // deep.  Each load fills 1 KiB of LDS contiguously, so a stage is NIW
-    // loads per wave and the units past the 32 rows land in the stage's
-    // slack.  The rows are copied as they are: int8 +-1 for the int8 path,
-    // or the shifted weights 0 / 2 with poff set (int8 features: uint8 ones
-    // would need column sums), or rows already in the compute type (bf16 /
-    // E4M3 +-1.0, built once by the caller) for those paths, which take
-    // either feature type.
-    // A chunk is RT row tiles of 32 dimensions (RT > 1 with DMA staging
-    // only; three row tiles classify only, in two stages); its class operand
-    // is RT * KT KiB.
-    static_assert(!DMA || (XF == 0 && (CT == C_I8 || CT == C_BF16 || CT == C_FP8)),
-                  "direct LDS staging is for integer features on the int8, bf16 and E4M3 paths");
-    static_assert(RT == 1 || DMA, "several row tiles per chunk need direct LDS staging");
-    static_assert(RT != 3 || MODE == M_CLASSIFY, "three row tiles per chunk: classify only");
+    // straight into LDS (global_load_lds, 16 bytes per lane), a ring of three
+    // or four stages.  Each load fills 1 KiB of LDS contiguously, so a stage is NIW
+    // loads per wave and the units past the chunk's rows land in the stage's
+    // slack.  The rows are copied as they are (bytes on every path).
+    // A chunk is RT row tiles of 32 dimensions (one or two, direct staging
+    // only); its class operand is RT * KT KiB.
+    static_assert(!DMA || (XF == 0 && (CT == C_I8 || CT == C_FP8 || CT == C_FP8S)),
+                  "direct LDS staging is for integer features on the int8 and E4M3 paths");
+    static_assert(RT == 1 || (RT == 2 && DMA), "two row tiles per chunk need direct LDS staging");
+    static_assert(SRC == W_ROWS || DMA, "weight forms are for direct staging");
+    static constexpr bool U8 = DMA && CT == C_I8 && SRC == W_ALT;    // uint8 features: column sums
+    static constexpr bool CVT = DMA && CT != C_I8 && SRC == W_ALT;   // int8 rows, E4M3 on read
     static constexpr int CH = kDimChunk * RT;              // dimensions per chunk
     static constexpr int UPR = RSB / 16;                   // 16-byte units per LDS row
     static constexpr int NIW = (CH * UPR + 64 * kWaves - 1) / (64 * kWaves);
     static constexpr int NCT = RT * KT;                    // class tiles per chunk
     static constexpr int NCW = (NCT + kWaves - 1) / kWaves;   // class-tile loads per wave
-    static constexpr int NBUF = DMA ? (RT == 3 ? 2 : 3) : 2;   // LDS stages
     static constexpr int SSZ = DMA ? NIW * kWaves * 1024 : CH * RSB;   // bytes per stage
+    // LDS stages: chunks of one row tile are short, so where one workgroup has
+    // the LDS to itself they are loaded three ahead (else two)
+    static constexpr int CSZ = MODE == M_CLASSIFY ? NCT * 1024 : 0;
+    static constexpr int NBUF = !DMA ? 2 : RT == 1 && QT * KS > 20 && 4 * (SSZ + CSZ) + 512 <= 160 * 1024 ? 4 : 3;
     static constexpr int OFF_C = NBUF * SSZ;
     static constexpr int OFF_CS = OFF_C + (MODE == M_CLASSIFY ? NBUF * NCT * 1024 : 0);
-    static constexpr int LDS = OFF_CS + (DMA ? 0 : NBUF * kDimChunk * 4);
+    static constexpr int LDS = OFF_CS + (!DMA ? NBUF * kDimChunk * 4 : U8 ? kWaves * kDimChunk * 4 : 0);
+    static_assert(LDS <= 160 * 1024, "LDS of one workgroup");
     static constexpr int QPW = QT * 32;                    // queries per wave
     // Waves per SIMD the kernel is compiled for (WV, or by default two where
     // the resident query operand leaves room, so that one wave's stalls are
@@ -69,58 +81,82 @@ struct Encoder {
     static constexpr int QPB = QPW * kWaves;               // queries per workgroup
 
     // ---------------------------------------------------------------- X
+    // One K step of byte features (16 bytes at k0 on the int8 path, 32 on
+    // the E4M3 ones, 8 for bf16) converted to the B operand, features past F
+    // cleared.
+    static constexpr int XW = XF == 0 ? KSTEP / 8 : 0;   // feature dwords per lane and K step
+    static __device__ __forceinline__ xfrag conv_bytes(const uint32_t (&d)[XW ? XW : 1], int k0, int F, bool sgn)
+    {
+        xfrag r;
+        if constexpr (CT == C_I8) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                uint32_t x = keep_bytes(d[e], k0 + 4 * e, F);
+                if constexpr (U8)
+                    x ^= 0x80808080u;            // x - 128; -128 past F (see column_sum)
+                else if (!sgn)
+                    x = keep_bytes(d[e] ^ 0x80808080u, k0 + 4 * e, F);
+                r[e] = (int)x;
+            }
+        } else if constexpr (CT == C_FP8) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                uint32_t x = keep_bytes(d[e], k0 + 4 * e, F);
+                r[e] = (int)fp8x4_raw(byte_value(x, 0, sgn), byte_value(x, 1, sgn), byte_value(x, 2, sgn),
+                                      byte_value(x, 3, sgn));
+            }
+        } else if constexpr (CT == C_FP8S) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                uint32_t hi, lo;
+                fp8_split4(keep_bytes(d[e], k0 + 4 * e, F), sgn, &hi, &lo);
+                r[e] = (int)hi;
+                r[8 + e] = (int)lo;
+            }
+        } else {   // C_BF16
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const uint32_t x = keep_bytes(d[e], k0 + 4 * e, F);
+                r[2 * e] = (int)bf16x2(byte_value(x, 0, sgn), byte_value(x, 1, sgn));
+                r[2 * e + 1] = (int)bf16x2(byte_value(x, 2, sgn), byte_value(x, 3, sgn));
+            }
+        }
+        return r;
+    }
+
+    // A K step past the features.
+    static __device__ __forceinline__ xfrag no_features()
+    {
+        xfrag f{};
+        if constexpr (U8) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                f[e] = (int)0x80808080u;
+        }
+        return f;
+    }
+
     static __device__ __forceinline__ xfrag load_frag(const EncodeArgs &a, int64_t q, int s, int g)
     {
         const int k0 = s * KSTEP + g * (KSTEP / 2);
         if constexpr (XF == 0) {
             const uint8_t *row = (const uint8_t *)a.X + q * a.ldx;
-            const bool sgn = a.x_type == X_INT8;
-            if constexpr (CT == C_I8) {
-                uint4 w = *(const uint4 *)(row + k0);
-                uint32_t d[4] = {w.x, w.y, w.z, w.w};
-                v4i r;
+            uint32_t d[XW];
+            if constexpr (XW == 2) {
+                const uint2 w = *(const uint2 *)(row + k0);
+                d[0] = w.x;
+                d[1] = w.y;
+            } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    uint32_t x = sgn ? d[e] : (d[e] ^ 0x80808080u);   // uint8: x - 128
-                    r[e] = (int)keep_bytes(x, k0 + 4 * e, a.F);
+                for (int i = 0; i < XW / 4; ++i) {
+                    const uint4 w = *(const uint4 *)(row + k0 + 16 * i);
+                    d[4 * i] = w.x;
+                    d[4 * i + 1] = w.y;
+                    d[4 * i + 2] = w.z;
+                    d[4 * i + 3] = w.w;
                 }
-                return r;
-            } else if constexpr (CT == C_FP8) {
-                uint4 w0 = *(const uint4 *)(row + k0);
-                uint4 w1 = *(const uint4 *)(row + k0 + 16);
-                uint32_t d[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-                v8i r;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    uint32_t x = keep_bytes(d[e], k0 + 4 * e, a.F);
-                    r[e] = (int)fp8x4(byte_value(x, 0, sgn), byte_value(x, 1, sgn),
-                                      byte_value(x, 2, sgn), byte_value(x, 3, sgn));
-                }
-                return r;
-            } else if constexpr (CT == C_FP8S) {
-                uint4 w0 = *(const uint4 *)(row + k0);
-                uint4 w1 = *(const uint4 *)(row + k0 + 16);
-                uint32_t d[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-                v16i r;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    uint32_t hi, lo;
-                    fp8_split4(keep_bytes(d[e], k0 + 4 * e, a.F), sgn, &hi, &lo);
-                    r[e] = (int)hi;
-                    r[8 + e] = (int)lo;
-                }
-                return r;
-            } else {   // C_BF16
-                uint2 w = *(const uint2 *)(row + k0);
-                uint32_t d[2] = {keep_bytes(w.x, k0, a.F), keep_bytes(w.y, k0 + 4, a.F)};
-                v4i r;
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    r[2 * e] = (int)bf16x2(byte_value(d[e], 0, sgn), byte_value(d[e], 1, sgn));
-                    r[2 * e + 1] = (int)bf16x2(byte_value(d[e], 2, sgn), byte_value(d[e], 3, sgn));
-                }
-                return r;
             }
+            return conv_bytes(d, k0, a.F, a.x_type == X_INT8);
         } else {
             static_assert(CT != C_FP8S, "the split E4M3 type is for integer features");
             const float *row = (const float *)a.X + q * a.ldx;
@@ -156,21 +192,142 @@ struct Encoder {
                                                   int64_t qbase, int lane, int ks_used)
     {
         // Branch-free: out-of-range rows / steps load an in-bounds address
-        // (row n-1, step 0) and are zeroed, so all loads are in flight at once.
+        // (row n-1, step 0), so all loads are in flight at once; the steps
+        // hold no features.
         const int g = lane >> 5;
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) {
             const int64_t q = qbase + qt * 32 + (lane & 31);
-            const bool qv = q < a.n;
-            const int64_t qc = qv ? q : a.n - 1;
+            const int64_t qc = q < a.n ? q : a.n - 1;
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                const bool v = qv && s < ks_used;
+                const bool v = s < ks_used;
                 xfrag f = load_frag(a, qc, v ? s : 0, g);
                 if (!v)
-                    f = xfrag{};
+                    f = no_features();
                 xr[qt][s] = f;
             }
+        }
+    }
+
+    // Direct-staged features.  Reading fragments straight from global memory
+    // touches 32 rows per load (16 bytes of each) and takes every 128-byte
+    // line four times through an L1 it does not fit: 13.6 thousand cycles for
+    // a workgroup's 256 x 640 bytes.  Instead each wave copies its own rows
+    // into its part of the ring past stage 0 (which is receiving the first
+    // chunk meanwhile) with full-line loads, in pieces of one 128-byte line of
+    // each row of a query tile, XNB pieces in flight, and takes the fragments
+    // from LDS.
+    // Rows past n re-read row n - 1 (their results are not stored, or stored
+    // over row n - 1 with the same value).
+    static constexpr int XAREA = (NBUF - 1) * NIW * 1024;  // bytes per wave
+    static constexpr int KSX = KS * KSTEP < 128 ? KS : 128 / KSTEP;   // K steps per piece
+    static constexpr int UPX = KSX * KSTEP / 16 + 1;       // 16-byte units per row (one of skew)
+    static constexpr int NXL = (32 * UPX + 63) / 64;       // loads per piece
+    static constexpr int NPQ = (KS + KSX - 1) / KSX;       // pieces per query tile
+    static constexpr int XNB0 = XAREA / (NXL * 1024);
+    static constexpr int XNB = XNB0 < QT * NPQ ? XNB0 : QT * NPQ;
+    static constexpr bool XLDS = DMA && XNB > 0;           // else (64 features, one tile) directly
+    // waits until at most `pieces` pieces are in flight
+    static __device__ __forceinline__ void wait_loads(int pieces)
+    {
+        switch (pieces) {
+        case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+        case 1: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NXL) : "memory"); break;
+        case 2: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NXL) : "memory"); break;
+        case 3: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NXL) : "memory"); break;
+        case 4: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * NXL) : "memory"); break;
+        default: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(5 * NXL) : "memory"); break;
+        }
+    }
+    static __device__ __forceinline__ void load_x_lds(xfrag (&xr)[QT][KS], const EncodeArgs &a, lds_u8 *area,
+                                                      int64_t qbase, int lane, int ks_used)
+    {
+        const int g = lane >> 5;
+        const bool sgn = a.x_type == X_INT8;
+        const int npx = ks_used * KSTEP / 16;              // 16-byte pieces of a row holding features
+        const int64_t q0 = qbase < a.n ? qbase : a.n - 1;
+        const int last = a.n - q0 < QPW ? (int)(a.n - q0) - 1 : QPW - 1;
+        const uint8_t *xb = (const uint8_t *)a.X + q0 * a.ldx;
+        // A wave with all its rows and 32-bit offsets within them: offsets of a
+        // piece's units computed once, the piece in the scalar base; units past
+        // the row's features read on (cut at the last row's end), and are
+        // cleared below with the rest of the bytes past F.  Otherwise unit by
+        // unit, to the byte.
+        const bool full = qbase + QPW <= a.n && a.ldx < (1 << 24);
+        uint32_t off[NXL];
+#pragma unroll
+        for (int i = 0; i < NXL; ++i) {
+            const int u = i * 64 + lane;
+            off[i] = (uint32_t)__umul24(u / UPX < 32 ? u / UPX : 31, (int)a.ldx) + 16u * (uint32_t)(u % UPX);
+        }
+        auto issue = [&](int j) {
+            const int qt = j / NPQ, kp = j % NPQ;
+            lds_u8 *dst = area + (j % XNB) * (NXL * 1024);
+            if (full) {
+                const uint32_t po = (uint32_t)__umul24(qt * 32, (int)a.ldx) + kp * (KSX * KSTEP);
+                const uint32_t lim = (uint32_t)__umul24(QPW - 1, (int)a.ldx) + 16u * (uint32_t)(npx - 1) - po;
+#pragma unroll
+                for (int i = 0; i < NXL; ++i)
+                    lds_dma16(xb + po, off[i] < lim ? off[i] : lim, dst + i * 1024);
+            } else {
+                int r = qt * 32 + lane / UPX, p = lane % UPX;  // unit i * 64 + lane of the piece
+#pragma unroll 1
+                for (int i = 0; i < NXL; ++i) {
+                    const int row = r < last ? r : last;
+                    const int pc = p + kp * (UPX - 1);
+                    lds_dma16(xb + row * a.ldx + (pc < npx ? 16 * pc : 0), dst + i * 1024);
+                    r += 64 / UPX;
+                    p += 64 % UPX;
+                    if (p >= UPX) {
+                        p -= UPX;
+                        ++r;
+                    }
+                }
+            }
+        };
+#pragma unroll
+        for (int j = 0; j < XNB; ++j)
+            issue(j);
+#pragma unroll
+        for (int j = 0; j < QT * NPQ; ++j) {
+            const int qt = j / NPQ, kp = j % NPQ;
+            wait_loads(QT * NPQ - 1 - j < XNB - 1 ? QT * NPQ - 1 - j : XNB - 1);
+            lds_u8 *xrow = area + (j % XNB) * (NXL * 1024) + (lane & 31) * (UPX * 16);
+            // clear the bytes past F
+            constexpr int PB = KSX * KSTEP;
+            const int f0 = a.F - kp * PB;                  // first such byte of the piece
+            const int fe = (KS - kp * KSX < KSX ? KS - kp * KSX : KSX) * KSTEP;
+            if (f0 < fe) {
+                const int o = f0 > 0 ? f0 : 0;
+                if ((o & 3) && g == 0) {
+                    lds_i32 *w = (lds_i32 *)(xrow + (o & ~3));
+                    *w = *w & (int)((1u << (8 * (o & 3))) - 1u);
+                }
+#pragma unroll 1
+                for (int w = (o + 3) / 4 + g; w < fe / 4; w += 2)
+                    ((lds_i32 *)xrow)[w] = 0;
+                __builtin_amdgcn_wave_barrier();           // (LDS operations of a wave are in order)
+            }
+            const lds_u8 *src = xrow + g * (KSTEP / 2);
+#pragma unroll
+            for (int s = 0; s < KSX; ++s) {
+                if (kp * KSX + s >= KS)
+                    break;
+                uint32_t d[XW];
+#pragma unroll
+                for (int i = 0; i < XW / 4; ++i) {
+                    const v4i w = *(const lds_v4i *)(src + s * KSTEP + 16 * i);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        d[4 * i + e] = (uint32_t)w[e];
+                }
+                xr[qt][kp * KSX + s] = conv_bytes(d, 0, KSTEP, sgn);   // already cleared past F
+            }
+            // the reads are done before the next piece lands on them
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (j + XNB < QT * NPQ)
+                issue(j + XNB);
         }
     }
 
@@ -186,21 +343,22 @@ struct Encoder {
     // the sum of its rounded features from the matrix cores (an all -1.0
     // operand against the query fragments; integers below 2^24, exact in
     // fp32).  Only the shapes the shifted types launch take the shifted
-    // projection (int8: two query tiles, shift_tile; E4M3: one query tile,
-    // shift8_tile); the others start from 0.
-    static constexpr bool kShift = DMA && ((CT == C_I8 && QT == 2 && shift_tile(KS, KT)) ||
-                                           (CT == C_FP8 && QT == 1 && shift8_tile(KS, KT)));
+    // projection (two query tiles, shift_tile / shift8_tile); the others
+    // start from 0.
+    static constexpr bool kShift = DMA && SRC == W_ROWS && QT == 2 && ((CT == C_I8 && shift_tile(KS, KT)) ||
+                                                                       (CT == C_FP8 && shift8_tile(KS, KT)));
     static __device__ __forceinline__ void shift_start(acc_t (&x0)[QT], const xfrag (&xr)[QT][KS], int poff)
     {
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) {
+            x0[qt] = acc_t{};
+            if (!kShift || !poff)
+                continue;
             if constexpr (kShift && CT == C_FP8) {
-                const int m1 = poff ? (int)0xB8B8B8B8u : 0;   // E4M3 -1.0 bytes, or zeros
                 frag neg;
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
-                    neg[i] = m1;
-                x0[qt] = acc_t{};
+                    neg[i] = (int)0xB8B8B8B8u;   // E4M3 -1.0 bytes
 #pragma unroll
                 for (int k = 0; k < KS; ++k)
                     mma(x0[qt], neg, xr[qt][k]);
@@ -212,12 +370,9 @@ struct Encoder {
                     for (int e = 0; e < 4; ++e)
                         s = __builtin_amdgcn_sdot4(xr[qt][k][e], 0x01010101, s, false);
                 s += __shfl_xor(s, 32);
-                const int v = poff ? -s : 0;
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
-                    x0[qt][i] = v;
-            } else {
-                x0[qt] = acc_t{};
+                    x0[qt][i] = -s;
             }
         }
     }
@@ -341,7 +496,7 @@ struct Encoder {
     // wave instead; two query tiles are two chains already.
     // The split E4M3 type always has two: its high parts accumulate in the
     // first, its low parts in the second (|sums| < 2^24, exact).
-    static constexpr int KC = CT == C_FP8S ? 2 : (QT == 1 && (WAVES == 1 || DMA) && KS >= 2) ? 2 : 1;
+    static constexpr int KC = CT == C_FP8S ? 2 : (QT == 1 && (WAVES == 1 || DMA) && KS >= 2) ? 2 : 1;   // chains
     typedef acc_t Parts[QT][KC];             // accumulators of one row tile
     static constexpr int kPhases = 4 * QT;   // epilogue phases (see Epilogue)
 
@@ -513,6 +668,12 @@ struct Encoder {
                 epi(p);
         }
     };
+    template <class H1, class H2> struct Both;
+    template <class H1, class H2>
+    static __device__ __forceinline__ Both<H1, H2> both(const H1 &h1, const H2 &h2)
+    {
+        return Both<H1, H2>{h1, h2};
+    }
     template <class H1, class H2>
     struct Both {
         H1 h1;
@@ -632,114 +793,338 @@ struct Encoder {
 
     // ------------------------------------------------------------ DMA
     // Source of each of this lane's NIW loads: LDS unit u = (i * 4 + wave) *
-    // 64 + lane of a stage is row u / UPR, piece u % UPR; the skew unit,
-    // pieces past the features and rows past the chunk re-read piece 0 of an
-    // in-bounds row (finite int8 against zero features, or slack).  Row r of
-    // chunk c is dimension S_{c*CH + r}.  Byte offsets fit 32 bits: the
-    // projection holds at most 65536 rows of at most 1024 + padding bytes.
+    // 64 + lane of a stage is row u / UPR, piece u % UPR; the skew unit and
+    // pieces past the features re-read piece 0 (finite weights against zero
+    // features), units past the chunk's rows land in slack.  Row r of chunk c
+    // is dimension S_{c*CH + r}; offsets past the last dimension's last piece
+    // are cut to it (those rows' results are masked, or meet zero class
+    // bytes).  Byte offsets fit 32 bits: the projection holds at most 65536
+    // rows of at most 1024 + padding bytes.
     struct Loader {
         const EncodeArgs &a;
         uint32_t off0[NIW];   // offset of load i in chunk 0
-        int rp[NIW];          // row | piece byte offset << 8
-        uint32_t rstep, base, cbytes, lastrow;
+        uint32_t cbytes, limit;
         int NC, lane, wave;
 
         __device__ __forceinline__ Loader(const EncodeArgs &a_, int NC_, int npc, int wave_, int lane_)
             : a(a_), NC(NC_), lane(lane_), wave(wave_)
         {
-            rstep = (uint32_t)a.stride * (uint32_t)a.ldp;
-            base = (uint32_t)a.s0 * (uint32_t)a.ldp;
+            const uint32_t rstep = (uint32_t)a.stride * (uint32_t)a.ldp;
+            const uint32_t base = (uint32_t)a.s0 * (uint32_t)a.ldp;
             cbytes = (uint32_t)CH * rstep;
-            lastrow = base + (uint32_t)(a.nd - 1) * rstep;   // row of the last dimension
+            limit = base + (uint32_t)(a.nd - 1) * rstep + 16u * (uint32_t)(npc - 1);
 #pragma unroll
             for (int i = 0; i < NIW; ++i) {
                 const int u = (i * kWaves + wave) * 64 + lane;
-                int r = u / UPR, p = u % UPR;
-                if (r >= CH) {
-                    r = CH - 1;
-                    p = 0;
-                }
-                const int pb = 16 * (p < npc ? p : 0);
-                off0[i] = base + (uint32_t)r * rstep + (uint32_t)pb;
-                rp[i] = r | (pb << 8);
+                const int r = u / UPR < CH ? u / UPR : CH - 1, p = u % UPR;
+                off0[i] = base + (uint32_t)r * rstep + 16u * (uint32_t)(p < npc ? p : 0);
             }
         }
-        // Load i (< NIW + NCW) of chunk c, clamped to the last chunk: the
-        // projection rows, then the class fragments (wave w loads class tiles
-        // (w + 4j) % NCT; duplicate tiles write the same bytes).  In the
-        // chunk holding the last dimension, rows past it re-read that row
-        // (a select, not a branch: branches here would split the MFMA
-        // sequence the loads are interleaved with into separate scheduling
-        // regions).  The class table holds a whole number of chunks (zero
-        // rows past nd).
-        __device__ __forceinline__ void issue(int i, int c, lds_u8 *stage, lds_u8 *lcls) const
+        // Chunk c's offset, or the last chunk's from there on (the class table
+        // holds a whole number of chunks, zero rows past nd), as scalars.
+        struct Chunk {
+            uint32_t cc, off;
+        };
+        __device__ __forceinline__ Chunk chunk(int c) const
         {
-            const int cc = c < NC ? c : NC - 1;
+            const uint32_t cc = (uint32_t)(c < NC ? c : NC - 1);
+            return Chunk{cc, cc * cbytes};
+        }
+        // Load i (< NIW + NCW) of a chunk: the projection rows, then the class
+        // fragments (wave w loads class tiles (w + 4j) % NCT; duplicate tiles
+        // write the same bytes).
+        __device__ __forceinline__ void issue(int i, const Chunk &c, lds_u8 *stage, lds_u8 *lcls) const
+        {
             if (i < NIW) {
-                const int last = a.nd - 1 - cc * CH;      // >= CH - 1 except in the last chunk
-                const uint32_t off = (rp[i] & 255) <= last ? off0[i] + (uint32_t)cc * cbytes
-                                                            : lastrow + (uint32_t)(rp[i] >> 8);
-                lds_dma16(a.P, off, stage + (i * kWaves + wave) * 1024);
+                const uint32_t off = off0[i] + c.off;
+                lds_dma16(a.P, off < limit ? off : limit, stage + (i * kWaves + wave) * 1024);
             } else if constexpr (MODE == M_CLASSIFY) {
                 const int tile = (wave + kWaves * (i - NIW)) % NCT;   // rt * KT + kt
-                lds_dma16(a.ctab, (uint32_t)((cc * NCT + tile) * 1024 + lane * 16), lcls + tile * 1024);
+                lds_dma16(a.ctab + (c.cc * NCT + tile) * 1024, (uint32_t)(lane * 16), lcls + tile * 1024);
             }
+        }
+        __device__ __forceinline__ void all(int c, lds_u8 *stage, lds_u8 *lcls) const
+        {
+            const Chunk ch = chunk(c);
+#pragma unroll
+            for (int i = 0; i < NIW + (MODE == M_CLASSIFY ? NCW : 0); ++i)
+                issue(i, ch, stage, lcls);
         }
     };
     static constexpr int NLOADS = NIW + (MODE == M_CLASSIFY ? NCW : 0);   // loads per wave per chunk
 
-    // The loads of one chunk as a pass hook: load s after K step s.
-    struct LoadHook {
+    // MFMAs are issued in order and each holds the matrix core for 32 (int8)
+    // or 64 cycles, so between two of them a wave can issue about 7 (15) other
+    // instructions for free and more than that stalls it.  The work beside
+    // the MFMAs is therefore cut into pieces of a few instructions, handed
+    // out by slot: slot s * MPS + m follows MFMA m of K step s.
+    static constexpr int MPS = CT == C_FP8S ? 2 : QT;      // MFMAs per K step
+    static_assert(!DMA || CT != C_FP8S || QT == 1, "the split E4M3 type takes one query tile");
+    static constexpr int SLOTS = KS * MPS;
+
+    // The loads of one chunk as a pass hook: one per slot from slot SL on, so
+    // that they have the longest time to land.
+    template <int S0> struct LoadHook {
         const Loader &ld;
-        int c;
+        typename Loader::Chunk c;
         lds_u8 *stage, *lcls;
+        static constexpr int SL = S0 + (S0 + 1 < SLOTS ? 1 : 0);
         __device__ __forceinline__ void at(int s) const
         {
-            if (s < NLOADS)
-                ld.issue(s, c, stage, lcls);
+            if (s >= SL && s - SL < NLOADS)
+                ld.issue(s - SL, c, stage, lcls);
         }
         __device__ __forceinline__ void tail() const
         {
 #pragma unroll
-            for (int s = KS; s < NLOADS; ++s)
-                ld.issue(s, c, stage, lcls);
+            for (int i = SLOTS - SL; i < NLOADS; ++i)
+                ld.issue(i, c, stage, lcls);
         }
     };
 
     // Wait until at most G of this wave's vector memory operations are in
-    // flight (they complete in issue order, so everything older is done),
-    // drain LDS operations, and meet the other waves.
-    template <int G>
+    // flight (they complete in issue order, so everything older is done) and
+    // meet the other waves; with DRAIN also for this wave's LDS reads.
+    template <int G, bool DRAIN>
     static __device__ __forceinline__ void dma_barrier()
     {
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(G) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (DRAIN)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(G) : "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(G) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
     }
 
-    // Staged loop: step c multiplies the RT row tiles of chunk c one after
-    // the other, each with the previous row tile's epilogue between its
-    // MFMAs (the first pass also issues the loads of the chunk NBUF - 1
-    // ahead there), reads each tile's class fragments into registers right
-    // after its pass, waits for chunk c+1's loads and synchronises once.
-    // Three stages for one or two row tiles; two for three (96-dimension
-    // chunks: 120 MFMAs per wave between barriers), whose next chunk's
-    // loads then have one step to land.  Row tile passes rotate through RT
-    // accumulator sets (two with RT = 1, the loop unrolled by two).
+    // ------------------------------------------------ direct-staged passes
+    // Projection fragments in flight (the ring f): KS * RT (RT * KS over the
+    // two unrolled steps with RT = 1) is a multiple of PDD, so every pass
+    // starts at a fixed slot.
+    static constexpr int PDD = KS < 4 ? KS : (CT == C_I8 ? 4 : 2);
+    // A pass takes its first PDD fragments from the previous pass, which
+    // reads them between its last MFMAs, so the matrix cores do not wait for
+    // LDS at a row tile's start.  With one row tile per chunk the barrier
+    // that makes the next chunk visible then has to come inside the pass,
+    // after K step BAR (> PDD: by then every LDS read of the previous chunk
+    // has been waited for) and before the first of those reads; shorter
+    // passes synchronise between the chunks instead.
+    static constexpr int BAR = PDD + 1;
+    static constexpr bool XPF = RT == 2 || BAR < KS - PDD;
+
+    static __device__ __forceinline__ frag read_frag(const lds_u8 *p) { return *(const HDC_LDS frag *)p; }
+
+    // The A operand of a fragment: int8 +-1 bytes become E4M3 +-1.0 (0x38 /
+    // 0xB8) on the converting kernels: one operation per dword, in the shadow
+    // of the MFMAs it feeds.
+    static __device__ __forceinline__ frag weights(frag f)
+    {
+        if constexpr (CVT) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                f[i] = (int)(((uint32_t)f[i] & 0x80808080u) | 0x38383838u);
+        }
+        return f;
+    }
+
+    // uint8 features are multiplied as x - 128, so a row tile's sums need
+    // 128 * sum_i p_i added per dimension.  Each wave sums the bytes of the
+    // fragments it reads anyway (4 dot products per K step beside 64 cycles
+    // of MFMAs).  The sum covers every byte multiplied, pad columns included:
+    // there the query operand is -128 and the two terms cancel.
+    static __device__ __forceinline__ int column_sum(const frag &f, int s, int m)
+    {
+        if constexpr (U8) {
+#pragma unroll
+            for (int e = 4 * m / MPS; e < 4 * (m + 1) / MPS; ++e)
+                s = __builtin_amdgcn_sdot4(f[e], 0x01010101, s, false);
+        }
+        return s;
+    }
+
+    // One pass over a row tile in LDS (base) that ends with the first PDD
+    // fragments of the next one (nbase) in the ring; OFF is the ring slot of
+    // the pass's first fragment.
+    template <int OFF, class Hook>
+    static __device__ __forceinline__ void tile_pass(Parts &part, const xfrag (&xr)[QT][KS], frag (&f)[PDD],
+                                                     const lds_u8 *base, const lds_u8 *nbase, int &cs,
+                                                     const Hook &hook, const acc_t (&x0)[QT])
+    {
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+            for (int k = 0; k < KC; ++k)
+                part[qt][k] = k == 0 ? x0[qt] : acc_t{};
+        cs = 0;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const frag cur = weights(f[(OFF + s) % PDD]);
+            if (s + PDD < KS)
+                f[(OFF + s) % PDD] = read_frag(base + (s + PDD) * KB);
+            else if constexpr (XPF)
+                f[(OFF + s) % PDD] = read_frag(nbase + (s + PDD - KS) * KB);
+#pragma unroll
+            for (int m = 0; m < MPS; ++m) {
+                if constexpr (CT == C_FP8S) {
+                    if (m == 0)
+                        mma(part[0][0], cur, split_hi(xr[0][s]));
+                    else
+                        mma(part[0][1], cur, split_lo(xr[0][s]));
+                } else {
+                    mma(part[m][s % KC], cur, xr[m][s]);
+                }
+                cs = column_sum(cur, cs, m);
+                hook.at(s * MPS + m);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        hook.tail();
+    }
+
+    // Epilogue of row tile w in phases of a few instructions, five per query
+    // tile: four take four dimensions each (adding the partial accumulators
+    // and the uint8 correction, then the signs: bytes {0, -1} of the Hamming
+    // MFMA's B operand, or bits), the fifth runs the Hamming MFMAs or finishes
+    // the word.  Encoding: a lane holds half the signs of a dimension tile for
+    // one query of each query tile; one lane-half swap gives the lower lanes
+    // the first tile's words and the upper lanes the second's, the 32-bit word
+    // of an even tile (LO) waits in hw, and the odd tile's last phase stores
+    // both as one 64-bit word per query (always issued, so that the barriers
+    // can count it).
+    static constexpr int EPH = 5 * QT;
+    template <bool LO> struct EpiD {
+        const EncodeArgs &a;
+        Parts &part;
+        v16i (&dacc)[KT][QT];
+        const v4i (&cf)[KT];
+        const v4i (&cs4)[4];         // uint8: column sums of this lane's 16 dimensions
+        uint32_t &hw;
+        uint32_t *hrow;              // packed row of this lane's query
+        int w, lane;
+        mutable v4i mb[QT];
+        mutable uint32_t bits[QT];
+
+        __device__ __forceinline__ void phase(int p) const
+        {
+            const int qt = p / 5, ph = p % 5;
+            acc_t &y = part[qt][0];
+            if (CT != C_I8 && ph == 0) {
+                // The 16-pass E4M3 MFMA's accumulator was observed to be read
+                // one wait state early by the compiler-inserted hazard
+                // padding; extra wait states keep the read clear.
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (ph < 4) {
+                const int j = 3 - ph;                      // registers 4j .. 4j + 3
+#pragma unroll
+                for (int v = 4 * j; v < 4 * j + 4; ++v) {
+                    if constexpr (KC == 2)
+                        y[v] += part[qt][1][v];
+                    if constexpr (U8)
+                        y[v] += cs4[j][v & 3] << 7;
+                }
+                if constexpr (MODE == M_CLASSIFY) {
+                    // bytes: 0xFF where the projection is negative, else 0
+                    const uint32_t t0 = __builtin_amdgcn_perm(sign_word(y[4 * j + 1]), sign_word(y[4 * j]),
+                                                              0x0C0C0B09u);
+                    const uint32_t t1 = __builtin_amdgcn_perm(sign_word(y[4 * j + 3]), sign_word(y[4 * j + 2]),
+                                                              0x0B090C0Cu);
+                    mb[qt][j] = (int)(t0 | t1);
+                } else {
+                    // signs shifted in from the top: register v lands on bit
+                    // 8 * (v / 4) + v % 4
+                    uint32_t b = ph == 0 ? 0u : bits[qt] << 4;
+#pragma unroll
+                    for (int v = 4 * j + 3; v >= 4 * j; --v)
+                        b = __builtin_amdgcn_alignbit(b, sign_word(y[v]), 31);
+                    bits[qt] = b;
+                }
+            } else if constexpr (MODE == M_CLASSIFY) {
+#pragma unroll
+                for (int kt = 0; kt < KT; ++kt)
+                    mma(dacc[kt][qt], cf[kt], mb[qt]);
+            } else if (qt == QT - 1) {
+                // lane half g holds bits 4g.. of every byte
+                typedef unsigned v2u __attribute__((ext_vector_type(2)));
+                const v2u sw = __builtin_amdgcn_permlane32_swap(bits[0], bits[QT - 1], false, false);
+                const int nv = a.nd - w * kDimChunk;       // dimensions of this tile
+                const uint32_t b = (sw[0] | (sw[1] << 4)) & (nv >= 32 ? ~0u : nv > 0 ? (1u << nv) - 1u : 0u);
+                if constexpr (LO)
+                    hw = b;
+                else if (QT == 2 || lane < 32)             // the word of tiles w - 1 and w
+                    *(uint2 *)(hrow + (w - 1)) = make_uint2(hw, b);
+            }
+        }
+        __device__ __forceinline__ void all() const
+        {
+#pragma unroll
+            for (int p = 0; p < EPH; ++p)
+                phase(p);
+        }
+        // as a pass hook: phase p in slot E0 + p * SPD (the uint8 column sums
+        // are on their way through LDS during the first K steps)
+        static constexpr int E0 = U8 && KS > 4 ? 2 * MPS : 0;
+        static constexpr int SPD = (SLOTS - E0) / EPH > 1 ? (SLOTS - E0) / EPH : 1;
+        __device__ __forceinline__ void at(int s) const
+        {
+            if (s >= E0 && (s - E0) % SPD == 0 && (s - E0) / SPD < EPH)
+                phase((s - E0) / SPD);
+        }
+        __device__ __forceinline__ void tail() const
+        {
+#pragma unroll
+            for (int p = (SLOTS - E0 + SPD - 1) / SPD; p < EPH; ++p)
+                phase(p);
+        }
+    };
+
+    // The barrier of a one-row-tile pass.
+    struct BarHook {
+        __device__ __forceinline__ void at(int s) const
+        {
+            if (XPF && s == BAR * MPS + MPS - 1)
+                dma_barrier<(NBUF - 3) * NLOADS, false>();
+        }
+        __device__ __forceinline__ void tail() const
+        {
+            if (!XPF)
+                dma_barrier<(NBUF - 3) * NLOADS, true>();
+        }
+    };
+
+    // Staged loop.  Pass by pass over the row tiles: each has the previous
+    // tile's epilogue and (with two row tiles per chunk: the second pass; with
+    // one: after the barrier) the loads of the chunk NBUF - 1 ahead between
+    // its MFMAs, and reads its class fragments after its last one.  One
+    // barrier per chunk, between the two passes or inside the only one: it
+    // waits for the loads of the next chunk, issued NBUF - 2 chunks ago (only
+    // younger ones may be in flight), and releases the stage of the previous
+    // chunk.  Two accumulator sets alternate.
     static __device__ __forceinline__ void run_dma(const EncodeArgs &a, uint8_t *smem, int64_t qblock,
                                                    v16i (&dacc)[KT][QT])
     {
-        static_assert(RT == 1 || RT == 2 || RT == 3, "one to three row tiles per chunk");
-        const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 5;
+        const int lane = threadIdx.x & 63, g = lane >> 5;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // in a scalar register
         const int64_t qbase = qblock + (int64_t)wave * QPW;
         const int ks_used = (a.F + KSTEP - 1) / KSTEP;
         const int npc = (ks_used * KB + 15) / 16;   // 16-byte pieces of a row holding features
-        const int NC = (a.nd + CH - 1) / CH;
-        // loads issued per step after those of the chunk waited for (stores
-        // of the encode epilogue are not counted: waiting for more is safe);
-        // with two stages the chunk waited for is the one issued last
-        constexpr int G = NBUF == 3 ? NLOADS : 0;
+        const int NC = (a.nd + 63) / 64 * (64 / CH);   // whole 64-dimension words
 
+        lds_u8 *L = (lds_u8 *)smem;
+        auto lp = [&](int i) { return L + i * SSZ; };
+        auto lc = [&](int i) { return L + OFF_C + i * (NCT * 1024); };
+        const Loader ld(a, NC, npc, wave, lane);
+        ld.all(0, lp(0), lc(0));
         xfrag xr[QT][KS];
-        load_x(xr, a, qbase, lane, ks_used);
+        if constexpr (XLDS)
+            load_x_lds(xr, a, L + SSZ + wave * XAREA, qbase, lane, ks_used);
+        else
+            load_x(xr, a, qbase, lane, ks_used);
+        dma_barrier<0, true>();
+#pragma unroll
+        for (int c = 1; c < NBUF - 1; ++c)
+            ld.all(c, lp(c), lc(c));
         acc_t x0[QT];
         shift_start(x0, xr, a.poff);
         if constexpr (kShift && CT == C_FP8) {
@@ -755,101 +1140,108 @@ struct Encoder {
             for (int qt = 0; qt < QT; ++qt)
                 dacc[kt][qt] = v16i{};
 
-        lds_u8 *L = (lds_u8 *)smem;
-        auto lp = [&](int i) { return L + i * SSZ; };
-        auto lc = [&](int i) { return L + OFF_C + i * (NCT * 1024); };
-        const Loader ld(a, NC, npc, wave, lane);
+        // this lane's packed output row: query g * 32 + l % 32 of the wave
+        // (one query tile: l % 32); rows past n repeat row n - 1's store
+        uint32_t *hrow = nullptr;
+        uint32_t hw = 0;
+        if constexpr (MODE == M_ENCODE) {
+            const int64_t q = qbase + (QT == 2 ? lane : (lane & 31));
+            hrow = a.H32 + (q < a.n ? q : a.n - 1) * a.ldh32;
+        }
+
+        const int loff = (lane & 31) * RSB + g * (KB / 2);
+        frag f[PDD];
+        auto fill = [&](const lds_u8 *base) {
 #pragma unroll
-        for (int c = 0; c < NBUF - 1; ++c)
-#pragma unroll
-            for (int i = 0; i < NLOADS; ++i)
-                ld.issue(i, c, lp(c), lc(c));
-        dma_barrier<G>();
+            for (int s = 0; s < PDD; ++s)
+                f[s] = read_frag(base + s * KB);
+        };
+        fill(lp(0) + loff);
 
         v4i cf[KT];
+        v4i cs4[4];
         int b = 0;   // stage of the chunk being multiplied
-        auto read_cf = [&](int rt) {
+        auto nxt = [&](int i) { return i == NBUF - 1 ? 0 : i + 1; };
+        auto base = [&](int st, int rt) { return lp(st) + rt * kDimChunk * RSB + loff; };
+        lds_i32 *lcs = (lds_i32 *)(L + OFF_CS) + wave * kDimChunk;
+        // after a pass: its class fragments, and its column sums through LDS
+        // (lane l holds half of row l % 32's sum; each lane needs 16 rows')
+        auto after = [&](int rt, int cs) {
             if constexpr (MODE == M_CLASSIFY) {
 #pragma unroll
                 for (int kt = 0; kt < KT; ++kt)
                     cf[kt] = *(const lds_v4i *)(lc(b) + ((rt * KT + kt) * 64 + lane) * 16);
             }
-        };
-        // one row-tile pass of the current chunk into cur
-        auto pass = [&](int rt, Parts &cur, const auto &hook) {
-            tile_mma(cur, xr, lp(b) + rt * kDimChunk * RSB, nullptr, false, lane, hook, x0);
-            read_cf(rt);
-        };
-        auto loads = [&](int c) {   // loads of chunk c + NBUF - 1 into the free stage
-            if constexpr (NBUF == 3) {
-                const int b2 = b == 0 ? 2 : b - 1;   // (b + 2) % 3
-                return LoadHook{ld, c + 2, lp(b2), lc(b2)};
-            } else {
-                return LoadHook{ld, c + 1, lp(b ^ 1), lc(b ^ 1)};
+            if constexpr (U8) {
+                typedef unsigned v2u __attribute__((ext_vector_type(2)));
+                const v2u sw = __builtin_amdgcn_permlane32_swap((unsigned)cs, (unsigned)cs, false, false);
+                lcs[lane & 31] = (int)(sw[0] + sw[1]);
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    cs4[j] = *(const lds_v4i *)(lcs + 8 * j + 4 * g);
+                __builtin_amdgcn_wave_barrier();
             }
         };
-        auto epi = [&](Parts &prev, int w) { return EpiHook{Epilogue{a, prev, dacc, cf, w, lane, g, qbase}}; };
-        typedef Both<EpiHook, LoadHook> EpiLoad;
-        typedef Both<NoHook, LoadHook> JustLoad;
-        auto finish_step = [&]() {
-            dma_barrier<G>();
-            b = b == NBUF - 1 ? 0 : b + 1;
+        auto loads = [&](int c, auto s0) {   // loads of chunk c + NBUF - 1 into the stage before b
+            const int b2 = b == 0 ? NBUF - 1 : b - 1;
+            return LoadHook<decltype(s0)::value>{ld, ld.chunk(c + NBUF - 1), lp(b2), lc(b2)};
         };
+        auto epi = [&](auto lo, Parts &prev, int w) {
+            return EpiD<decltype(lo)::value>{a, prev, dacc, cf, cs4, hw, hrow, w, lane};
+        };
+        typedef std::integral_constant<bool, true> Lo;
+        typedef std::integral_constant<bool, false> Hi;
 
         Parts P0, P1;
-        if constexpr (RT == 3) {
-            Parts P2;
-            pass(0, P0, JustLoad{NoHook{}, loads(0)});
-            pass(1, P1, epi(P0, 0));
-            pass(2, P2, epi(P1, 1));
-            finish_step();
+        int cs;
+        if constexpr (RT == 2) {
+            typedef std::integral_constant<int, 0> S0;
+            constexpr int O1 = KS % PDD;
+            // stores the barrier of a step may leave in flight: the one of
+            // the epilogue between the awaited loads and the barrier
+            constexpr int G = MODE == M_ENCODE ? 1 : 0;
+            auto second = [&](int c) {
+                tile_pass<O1>(P1, xr, f, base(b, 1), base(nxt(b), 0), cs,
+                              both(epi(Lo{}, P0, 2 * c), loads(c, S0{})), x0);
+                after(1, cs);
+                b = nxt(b);
+            };
+            tile_pass<0>(P0, xr, f, base(b, 0), base(b, 1), cs, NoHook{}, x0);
+            after(0, cs);
+            dma_barrier<0, false>();
+            second(0);
             for (int c = 1; c < NC; ++c) {
-                pass(0, P0, EpiLoad{epi(P2, 3 * c - 1), loads(c)});
-                pass(1, P1, epi(P0, 3 * c));
-                pass(2, P2, epi(P1, 3 * c + 1));
-                finish_step();
+                tile_pass<0>(P0, xr, f, base(b, 0), base(b, 1), cs, epi(Hi{}, P1, 2 * c - 1), x0);
+                after(0, cs);
+                dma_barrier<G, false>();
+                second(c);
             }
-            run_epilogue(Epilogue{a, P2, dacc, cf, 3 * NC - 1, lane, g, qbase});
-        } else if constexpr (RT == 2) {
-            pass(0, P0, JustLoad{NoHook{}, loads(0)});
-            pass(1, P1, epi(P0, 0));
-            finish_step();
-            for (int c = 1; c < NC; ++c) {
-                pass(0, P0, EpiLoad{epi(P1, 2 * c - 1), loads(c)});
-                pass(1, P1, epi(P0, 2 * c));
-                finish_step();
-            }
-            run_epilogue(Epilogue{a, P1, dacc, cf, 2 * NC - 1, lane, g, qbase});
+            epi(Hi{}, P1, 2 * NC - 1).all();
         } else {
-            pass(0, P0, JustLoad{NoHook{}, loads(0)});
-            finish_step();
-            for (int c = 1;; c += 2) {
-                if (c >= NC) {
-                    run_epilogue(Epilogue{a, P0, dacc, cf, c - 1, lane, g, qbase});
-                    break;
-                }
-                pass(0, P1, EpiLoad{epi(P0, c - 1), loads(c)});
-                finish_step();
-                if (c + 1 >= NC) {
-                    run_epilogue(Epilogue{a, P1, dacc, cf, c, lane, g, qbase});
-                    break;
-                }
-                pass(0, P0, EpiLoad{epi(P1, c), loads(c + 1)});
-                finish_step();
+            // tiles in pairs (an odd last one with a masked partner), so that
+            // the two accumulator sets alternate without exits in between
+            typedef std::integral_constant<int, (XPF ? (BAR + 1) * MPS : SLOTS)> S0;
+            typedef std::integral_constant<int, (XPF ? KS % PDD : 0)> O1;
+            typedef std::integral_constant<int, 0> O0;
+            auto step = [&](auto off, Parts &cur, int c, const auto &e) {
+                tile_pass<decltype(off)::value>(cur, xr, f, base(b, 0), base(nxt(b), 0), cs,
+                                                both(both(e, BarHook{}), loads(c, S0{})), x0);
+                after(0, cs);
+                b = nxt(b);
+                if constexpr (!XPF)
+                    fill(base(b, 0));
+            };
+            step(O0{}, P0, 0, NoHook{});
+            step(O1{}, P1, 1, epi(Lo{}, P0, 0));
+            for (int c = 2; c < NC; c += 2) {
+                step(O0{}, P0, c, epi(Hi{}, P1, c - 1));
+                step(O1{}, P1, c + 1, epi(Lo{}, P0, c));
             }
+            epi(Hi{}, P1, NC - 1).all();
         }
         // no load may still be writing this workgroup's LDS when it exits
         __builtin_amdgcn_s_waitcnt(0);
-        if constexpr (MODE == M_ENCODE && RT == 1) {
-            if (NC & 1) {   // high half of the last word holds no dimension
-#pragma unroll
-                for (int qt = 0; qt < QT; ++qt) {
-                    const int64_t q = qbase + qt * 32 + (lane & 31);
-                    if (g == 0 && q < a.n)
-                        a.H32[q * a.ldh32 + NC] = 0u;
-                }
-            }
-        }
     }
 
     // Argmin over the class accumulators; returns the label of this lane's

@@ -110,10 +110,11 @@ constexpr int kMaxRT = 6;
 inline int64_t table_chunks(int nd) { return (chunks(nd) + kMaxRT - 1) / kMaxRT * kMaxRT; }
 inline size_t class_table_bytes(int nd, int K) { return (size_t)table_chunks(nd) * class_tiles(K) * 1024; }
 
-// Tile variants of the encoder: direct-to-LDS staging of the projection
-// with two query tiles x two row tiles per wave or one of each (int8
-// features on the int8 path), or register staging with one or two query
-// tiles per wave.
+// Tile variants of the encoder: direct-to-LDS staging of the projection with
+// two query tiles per wave or one, or register staging (fp32 features) with
+// one or two query tiles per wave.  Byte features run on the direct-staged
+// shape of their bucket under every id it lists, except that TV_DMA_1X1 is a
+// shape of its own up to 640 int8 features and two class tiles.
 enum TileVariant : int { TV_AUTO = 0, TV_DMA_2X2 = 1, TV_DMA_1X1 = 2, TV_REG_QT1 = 3, TV_REG_QT2 = 4,
                          TV_DMA_2X3 = 5 };
 // Tile variants of the configuration sweep (per configuration): work items of
@@ -126,15 +127,14 @@ enum SweepVariant : int { SV_AUTO = 0, SV_ITEM128 = 1, SV_ITEM256 = 2, SV_ITEM25
 enum KernelKind : int { KK_ENCODE = 0, KK_CLASSIFY = 1, KK_SWEEP = 2 };
 
 // Shape rules shared by the kernel templates and the variant listing.
-// Direct staging with 2x2 tiles fits the registers up to 20 K steps and two
-// class tiles.
+// Both direct-staged shapes (TV_DMA_2X2 and TV_DMA_1X1) are offered up to 20 K
+// steps and two class tiles.
 constexpr bool big_tile(int ks, int kt) { return ks <= 20 && kt <= 2; }
-// The classifier's 2x3 shape (two query tiles x three row tiles, chunks of
-// 96 dimensions in a two-stage ring): one class tile.
+// Buckets that list TV_DMA_2X3.
 constexpr bool big3_tile(int ks, int kt) { return ks <= 20 && kt == 1; }
-// The shifted projection (C_I8S): the 2x2 / 2x3 shapes from 10 K steps (F >
-// 256) up, which run one wave per SIMD and have registers to spare for the
-// start values of their accumulators.
+// The shifted projection (C_I8S): two query tiles and two row tiles, from 10
+// K steps (F > 256) up to 20, which have registers to spare for the start
+// values of their accumulators.
 constexpr bool shift_tile(int ks, int kt) { return ks >= 10 && big_tile(ks, kt); }
 // The E4M3 path on the shifted projection (C_FP8H): the direct-staged 2x2
 // shape from 5 to 10 K steps of 64 features (256 < F <= 640), up to two

@@ -1,0 +1,77 @@
+"""The direct-staged encoder at the edges of its shapes: every feature width
+bucket's first and last sizes (one and two row tiles per chunk), one and two
+query tiles, class tiles, ragged query counts, dimension counts that end
+inside a word, garbage in the pad columns of features and projection, and row
+pitches beyond 32-bit offsets.  Encodings, labels and distances equal the
+oracle's exactly (every sum is exact in its accumulator)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2606_26547_amd import datagen as dg
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hdc():
+    O.build()
+    from paper_2606_26547_amd import hdc as H
+    return H
+
+
+def _padded(a, ld, seed):
+    """Rows of pitch ld on the device, every pad column random bytes."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    out = torch.randint(0, 256, (a.shape[0], ld), dtype=torch.uint8, device="cuda", generator=g)
+    t = torch.as_tensor(a).cuda()
+    out = out.view(t.dtype)
+    out[:, :a.shape[1]] = t
+    return out
+
+
+# n, F, D, K, (start, end, stride)
+SHAPES = [
+    (1, 1, 64, 1, None), (33, 64, 130, 2, None), (257, 65, 200, 33, (3, 199, 2)), (95, 128, 1000, 65, None),
+    (130, 129, 640, 10, (1, 640, 1)), (31, 256, 129, 100, None), (64, 257, 1088, 26, None),
+    (300, 320, 321, 64, (0, 321, 3)), (255, 385, 512, 40, None), (129, 512, 700, 128, (70, 700, 1)),
+    (513, 617, 2080, 26, None), (65, 640, 449, 90, None), (200, 641, 577, 26, None), (97, 784, 1024, 10, (5, 1021, 3)),
+    (258, 832, 96, 64, None), (70, 832, 640, 99, None), (66, 833, 1300, 7, None), (256, 1024, 385, 60, None),
+    (34, 1024, 512, 128, None), (1500, 100, 64, 5, None), (1100, 700, 63, 33, None),
+]
+
+
+@pytest.mark.parametrize("compute", ["int8", "bf16", "fp8", "fp8split"])
+@pytest.mark.parametrize("xt", ["int8", "uint8"])
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_direct_matches_oracle(hdc, shape, xt, compute):
+    n, F, D, K, dims = shape
+    print("[case]", shape, xt, compute, flush=True)
+    X, P = dg.random_case(n, F, D, xt, seed=n + F + D)
+    ld = (F + 63) // 64 * 64
+    Xd, Pd = _padded(X, ld + 64, 1), _padded(P, ld + 64, 2)
+    s, e, k = dims or (0, D, 1)
+    g = np.random.default_rng(K)
+    Cw = g.integers(0, 2 ** 63, size=(K, (D + 63) // 64), dtype=np.int64).view(np.uint64)
+    if D % 64:
+        Cw[:, -1] &= np.uint64((1 << (D % 64)) - 1)
+    H = hdc.encode(Xd, F, Pd, D, compute, start=s, end=e, stride=k)
+    assert np.array_equal(H.cpu().numpy().view(np.uint64), O.encode(X, P, compute, s, e, k))
+    lab, dists = hdc.classify(Xd, F, Pd, D, torch.as_tensor(Cw.view(np.int64)).cuda(), compute, s, e, k,
+                              with_dists=True)
+    lref, dref = O.classify(X, P, Cw, compute, s, e, k, with_dists=True)
+    assert np.array_equal(dists.cpu().numpy(), dref)
+    assert np.array_equal(lab.cpu().numpy(), lref)
+
+
+@pytest.mark.parametrize("compute", ["int8", "fp8"])
+def test_direct_wide_row_pitch(hdc, compute):
+    """Feature rows 2^24 + 64 bytes apart (past the 32-bit offsets within a
+    wave's rows)."""
+    n, F, D = 70, 617, 256
+    X, P = dg.random_case(n, F, D, "int8", seed=3)
+    Xd = torch.empty((n, (1 << 24) + 64), dtype=torch.int8, device="cuda")
+    Xd[:, :F] = torch.as_tensor(X).cuda()
+    H = hdc.encode(Xd, F, hdc.pad_cols(P), D, compute)
+    assert np.array_equal(H.cpu().numpy().view(np.uint64), O.encode(X, P, compute))
