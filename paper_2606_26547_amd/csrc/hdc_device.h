@@ -58,6 +58,27 @@ __device__ __forceinline__ void lds_dma16(const void *addr, const lds_u8 *dst)
                  : "memory", "m0");
 }
 
+// Buffer descriptor of `bytes` bytes at base (raw, no stride).  Loads past
+// the end return zeros, so a buffer load needs no address clamp.
+__device__ __forceinline__ v4i raw_buffer(const void *base, uint32_t bytes)
+{
+    const uint64_t b = (uint64_t)(uintptr_t)base;
+    return v4i{__builtin_amdgcn_readfirstlane((int)(uint32_t)b),
+               __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32) & 0xffff),
+               __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+}
+
+// lds_dma16 from a buffer at voff (per lane) + soff (uniform): no vector
+// arithmetic per load.
+__device__ __forceinline__ void lds_dma16(const v4i &buf, uint32_t voff, uint32_t soff, const lds_u8 *dst)
+{
+    const uint32_t m = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
+    const uint32_t so = __builtin_amdgcn_readfirstlane(soff);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(m), "v"(voff),
+                 "s"(buf), "s"(so)
+                 : "memory", "m0");
+}
+
 // ---------------------------------------------------------------------------
 // Operand traits.  Every compute type uses a 32x32 MFMA (rows = dimensions,
 // columns = queries).  KSTEP features are consumed per instruction; each

@@ -129,9 +129,10 @@ static hipError_t launch_one(const EncodeArgs &a, hipStream_t st)
 // The direct-staged shape of a bucket: two query tiles per wave (one wave per
 // SIMD), so that each projection fragment read from LDS feeds two MFMAs: with
 // one, four waves ask LDS for 128 bytes a cycle, all it has (784 uint8
-// features, n = 60000, 8192 dimensions: 820 us of encoding against 439).  Two row tiles per
+// features, n = 60000, 8192 dimensions: 820 us of encoding against 300).  Two row tiles per
 // chunk (80 MFMAs between barriers at 640 features) while three stages of
-// them fit the LDS, else one.  One query tile where the registers hold no
+// them fit the LDS, else one (uint8 features: always one, whose barrier also
+// publishes the column sums).  One query tile where the registers hold no
 // second beside the accumulators: four class tiles from 833 features, and the
 // split E4M3 type, whose query operand is twice as wide (there each fragment
 // feeds two MFMAs already).
@@ -140,7 +141,8 @@ static hipError_t launch_direct(const EncodeArgs &a, hipStream_t st)
 {
     constexpr int W = KS * Tr<CT>::KSTEP;
     constexpr int QT = CT == C_FP8S || (W > 832 && KT == 4) ? 1 : 2;
-    return launch_one<CT, 0, QT, KS, KT, MODE, true, (W <= 640 ? 2 : 1), SRC>(a, st);
+    constexpr int RT = W > 640 || (CT == C_I8 && SRC == W_ALT) ? 1 : 2;
+    return launch_one<CT, 0, QT, KS, KT, MODE, true, RT, SRC>(a, st);
 }
 
 // One feature-width bucket of byte features: everything is staged directly,

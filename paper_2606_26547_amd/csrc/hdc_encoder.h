@@ -45,15 +45,16 @@ struct Encoder {
     static constexpr int MP = (PIECES + 7) / 8;            // pieces per thread (8 threads / row)
     // DMA: projection rows and class fragments go from global memory
     // straight into LDS (global_load_lds, 16 bytes per lane), a ring of three
-    // or four stages.  Each load fills 1 KiB of LDS contiguously, so a stage is NIW
-    // loads per wave and the units past the chunk's rows land in the stage's
-    // slack.  The rows are copied as they are (bytes on every path).
+    // to six stages.  Each load fills 1 KiB of LDS contiguously, so a stage is NIW
+    // loads per wave (the last ones repeat its last KiB) and the units past
+    // the chunk's rows land in the stage's slack.  The rows are copied as they are (bytes on every path).
     // A chunk is RT row tiles of 32 dimensions (one or two, direct staging
     // only); its class operand is RT * KT KiB.
     static_assert(!DMA || (XF == 0 && (CT == C_I8 || CT == C_FP8 || CT == C_FP8S)),
                   "direct LDS staging is for integer features on the int8 and E4M3 paths");
     static_assert(RT == 1 || (RT == 2 && DMA), "two row tiles per chunk need direct LDS staging");
     static_assert(SRC == W_ROWS || DMA, "weight forms are for direct staging");
+    static_assert(!(DMA && CT == C_I8 && SRC == W_ALT) || RT == 1, "column sums: a barrier per row tile");
     static constexpr bool U8 = DMA && CT == C_I8 && SRC == W_ALT;    // uint8 features: column sums
     static constexpr bool CVT = DMA && CT != C_I8 && SRC == W_ALT;   // int8 rows, E4M3 on read
     static constexpr int CH = kDimChunk * RT;              // dimensions per chunk
@@ -61,14 +62,21 @@ struct Encoder {
     static constexpr int NIW = (CH * UPR + 64 * kWaves - 1) / (64 * kWaves);
     static constexpr int NCT = RT * KT;                    // class tiles per chunk
     static constexpr int NCW = (NCT + kWaves - 1) / kWaves;   // class-tile loads per wave
-    static constexpr int SSZ = DMA ? NIW * kWaves * 1024 : CH * RSB;   // bytes per stage
-    // LDS stages: chunks of one row tile are short, so where one workgroup has
-    // the LDS to itself they are loaded three ahead (else two)
+    static constexpr int NU = (CH * UPR + 63) / 64;        // 1 KiB pieces of a stage
+    static constexpr int SSZ = DMA ? NU * 1024 : CH * RSB; // bytes per stage
+    // LDS stages: chunks of one row tile are short, and the first touch of a
+    // projection row comes from behind the L2, so where one workgroup has the
+    // LDS to itself chunks are loaded up to five ahead (else two)
     static constexpr int CSZ = MODE == M_CLASSIFY ? NCT * 1024 : 0;
-    static constexpr int NBUF = !DMA ? 2 : RT == 1 && QT * KS > 20 && 4 * (SSZ + CSZ) + 512 <= 160 * 1024 ? 4 : 3;
+    static constexpr bool stages_fit(int n) { return RT == 1 && QT * KS > 20 && n * (SSZ + CSZ) + 512 <= 160 * 1024; }
+    static constexpr int NBUF = !DMA ? 2 : stages_fit(6) ? 6 : stages_fit(5) ? 5 : U8 || stages_fit(4) ? 4 : 3;
+    // chunks past the current one whose loads a pass's barrier waits for (the
+    // uint8 kernels sum the columns of the tile two ahead), and the loads that
+    // may stay in flight there
+    static constexpr int VIS = U8 ? 2 : 1;
     static constexpr int OFF_C = NBUF * SSZ;
     static constexpr int OFF_CS = OFF_C + (MODE == M_CLASSIFY ? NBUF * NCT * 1024 : 0);
-    static constexpr int LDS = OFF_CS + (!DMA ? NBUF * kDimChunk * 4 : U8 ? kWaves * kDimChunk * 4 : 0);
+    static constexpr int LDS = OFF_CS + (!DMA ? NBUF * kDimChunk * 4 : U8 ? 2 * kDimChunk * 4 : 0);
     static_assert(LDS <= 160 * 1024, "LDS of one workgroup");
     static constexpr int QPW = QT * 32;                    // queries per wave
     // Waves per SIMD the kernel is compiled for (WV, or by default two where
@@ -93,7 +101,7 @@ struct Encoder {
             for (int e = 0; e < 4; ++e) {
                 uint32_t x = keep_bytes(d[e], k0 + 4 * e, F);
                 if constexpr (U8)
-                    x ^= 0x80808080u;            // x - 128; -128 past F (see column_sum)
+                    x ^= 0x80808080u;            // x - 128; -128 past F (see SumHook)
                 else if (!sgn)
                     x = keep_bytes(d[e] ^ 0x80808080u, k0 + 4 * e, F);
                 r[e] = (int)x;
@@ -220,7 +228,7 @@ struct Encoder {
     // from LDS.
     // Rows past n re-read row n - 1 (their results are not stored, or stored
     // over row n - 1 with the same value).
-    static constexpr int XAREA = (NBUF - 1) * NIW * 1024;  // bytes per wave
+    static constexpr int XAREA = (NBUF - 1) * SSZ / kWaves / 1024 * 1024;   // bytes per wave
     static constexpr int KSX = KS * KSTEP < 128 ? KS : 128 / KSTEP;   // K steps per piece
     static constexpr int UPX = KSX * KSTEP / 16 + 1;       // 16-byte units per row (one of skew)
     static constexpr int NXL = (32 * UPX + 63) / 64;       // loads per piece
@@ -792,18 +800,19 @@ struct Encoder {
     }
 
     // ------------------------------------------------------------ DMA
-    // Source of each of this lane's NIW loads: LDS unit u = (i * 4 + wave) *
-    // 64 + lane of a stage is row u / UPR, piece u % UPR; the skew unit and
+    // Source of each of this lane's NIW loads: LDS unit u = piece * 64 +
+    // lane of a stage is row u / UPR, piece u % UPR; the skew unit and
     // pieces past the features re-read piece 0 (finite weights against zero
     // features), units past the chunk's rows land in slack.  Row r of chunk c
-    // is dimension S_{c*CH + r}; offsets past the last dimension's last piece
-    // are cut to it (those rows' results are masked, or meet zero class
-    // bytes).  Byte offsets fit 32 bits: the projection holds at most 65536
+    // is dimension S_{c*CH + r}; past the last dimension's last piece the
+    // buffer ends and loads give zeros (those rows' results are masked, or
+    // meet zero class bytes).  Byte offsets fit 32 bits: the projection holds at most 65536
     // rows of at most 1024 + padding bytes.
     struct Loader {
         const EncodeArgs &a;
         uint32_t off0[NIW];   // offset of load i in chunk 0
-        uint32_t cbytes, limit;
+        uint32_t cbytes;
+        v4i rows;             // buffer up to the last dimension's last piece
         int NC, lane, wave;
 
         __device__ __forceinline__ Loader(const EncodeArgs &a_, int NC_, int npc, int wave_, int lane_)
@@ -812,13 +821,18 @@ struct Encoder {
             const uint32_t rstep = (uint32_t)a.stride * (uint32_t)a.ldp;
             const uint32_t base = (uint32_t)a.s0 * (uint32_t)a.ldp;
             cbytes = (uint32_t)CH * rstep;
-            limit = base + (uint32_t)(a.nd - 1) * rstep + 16u * (uint32_t)(npc - 1);
+            rows = raw_buffer(a.P, base + (uint32_t)(a.nd - 1) * rstep + 16u * (uint32_t)npc);
 #pragma unroll
             for (int i = 0; i < NIW; ++i) {
-                const int u = (i * kWaves + wave) * 64 + lane;
+                const int u = piece(i) * 64 + lane;
                 const int r = u / UPR < CH ? u / UPR : CH - 1, p = u % UPR;
                 off0[i] = base + (uint32_t)r * rstep + 16u * (uint32_t)(p < npc ? p : 0);
             }
+        }
+        // KiB of the stage that load i of this wave fills
+        __device__ __forceinline__ int piece(int i) const
+        {
+            return i * kWaves + kWaves <= NU || i * kWaves + wave < NU ? i * kWaves + wave : NU - 1;
         }
         // Chunk c's offset, or the last chunk's from there on (the class table
         // holds a whole number of chunks, zero rows past nd), as scalars.
@@ -836,8 +850,7 @@ struct Encoder {
         __device__ __forceinline__ void issue(int i, const Chunk &c, lds_u8 *stage, lds_u8 *lcls) const
         {
             if (i < NIW) {
-                const uint32_t off = off0[i] + c.off;
-                lds_dma16(a.P, off < limit ? off : limit, stage + (i * kWaves + wave) * 1024);
+                lds_dma16(rows, off0[i], c.off, stage + piece(i) * 1024);
             } else if constexpr (MODE == M_CLASSIFY) {
                 const int tile = (wave + kWaves * (i - NIW)) % NCT;   // rt * KT + kt
                 lds_dma16(a.ctab + (c.cc * NCT + tile) * 1024, (uint32_t)(lane * 16), lcls + tile * 1024);
@@ -862,22 +875,23 @@ struct Encoder {
     static_assert(!DMA || CT != C_FP8S || QT == 1, "the split E4M3 type takes one query tile");
     static constexpr int SLOTS = KS * MPS;
 
-    // The loads of one chunk as a pass hook: one per slot from slot SL on, so
-    // that they have the longest time to land.
-    template <int S0> struct LoadHook {
+    // The loads of one chunk as a pass hook: load i in slot SL + i * MPS (the
+    // slots that hold no piece of the epilogue).
+    template <int SL> struct LoadHook {
         const Loader &ld;
         typename Loader::Chunk c;
         lds_u8 *stage, *lcls;
-        static constexpr int SL = S0 + (S0 + 1 < SLOTS ? 1 : 0);
+        static constexpr int LSP = MPS;
+        static constexpr int IN = SL < SLOTS ? (SLOTS - SL + LSP - 1) / LSP : 0;   // loads in slots
         __device__ __forceinline__ void at(int s) const
         {
-            if (s >= SL && s - SL < NLOADS)
-                ld.issue(s - SL, c, stage, lcls);
+            if (s >= SL && (s - SL) % LSP == 0 && (s - SL) / LSP < NLOADS)
+                ld.issue((s - SL) / LSP, c, stage, lcls);
         }
         __device__ __forceinline__ void tail() const
         {
 #pragma unroll
-            for (int i = SLOTS - SL; i < NLOADS; ++i)
+            for (int i = IN; i < NLOADS; ++i)
                 ld.issue(i, c, stage, lcls);
         }
     };
@@ -926,35 +940,90 @@ struct Encoder {
         return f;
     }
 
-    // uint8 features are multiplied as x - 128, so a row tile's sums need
-    // 128 * sum_i p_i added per dimension.  Each wave sums the bytes of the
-    // fragments it reads anyway (4 dot products per K step beside 64 cycles
-    // of MFMAs).  The sum covers every byte multiplied, pad columns included:
-    // there the query operand is -128 and the two terms cancel.
-    static __device__ __forceinline__ int column_sum(const frag &f, int s, int m)
-    {
-        if constexpr (U8) {
-#pragma unroll
-            for (int e = 4 * m / MPS; e < 4 * (m + 1) / MPS; ++e)
-                s = __builtin_amdgcn_sdot4(f[e], 0x01010101, s, false);
+    // uint8 features are multiplied as x - 128, so a row tile's sums start
+    // from 128 * sum_i p_i of each dimension.  The four waves share these sums
+    // as a pass hook two tiles ahead: each takes 8 of the tile's 32 rows, 8
+    // lanes a row, a few 16-byte reads spread over the pass, and leaves them
+    // in LDS, two buffers in turn; the next pass's barrier makes them visible
+    // and that pass reads them as the accumulators of the one after.  Vector
+    // instructions cost about 3 cycles each beside the MFMAs (dot products
+    // 15), so bytes are summed as sad(b ^ 0x80, 0) = b + 128, two operations
+    // per dword, and the shared sums come without any per accumulator: 51.8
+    // cycles per MFMA at 784 features before, 43.8 now.  The sum covers
+    // every byte multiplied, pad columns included: there the query operand is
+    // -128 and the two terms cancel.
+    static constexpr int SJ = (KS * KSTEP / 16 + 7) / 8;   // reads per lane and tile
+    struct SumHook {
+        const lds_u8 *row;           // this lane's row and first piece of the tile
+        lds_i32 *out;                // its sum's place
+        bool last;                   // the last read is within the row
+        bool write;
+        mutable v4i f;
+        mutable uint32_t c;
+        // after the barrier: read j in slot S0 + j * PER, summed two dwords at
+        // a time in slots S0 + j * PER + PER - 2 and the next
+        static constexpr int S0 = XPF ? (BAR + 1) * MPS : SLOTS;
+        static constexpr int PER = (SLOTS - S0) / SJ > 4 ? (SLOTS - S0) / SJ : 4;
+        __device__ __forceinline__ void read(int j) const { f = *(const lds_v4i *)(row + j * 128); }
+        __device__ __forceinline__ void add(int j, int e) const
+        {
+            uint32_t t = j == 0 && e == 0 ? 0u : c;
+            t = __builtin_amdgcn_sad_u8((uint32_t)f[e] ^ 0x80808080u, 0u, t);
+            t = __builtin_amdgcn_sad_u8((uint32_t)f[e + 1] ^ 0x80808080u, 0u, t);
+            c = j < SJ - 1 || last ? t : c;
         }
-        return s;
-    }
+        __device__ __forceinline__ void at(int s) const
+        {
+            if (s < S0 || (s - S0) / PER >= SJ)
+                return;
+            const int j = (s - S0) / PER, r = (s - S0) % PER;
+            if (r == 0)
+                read(j);
+            if (r == PER - 2)
+                add(j, 0);
+            if (r == PER - 1)
+                add(j, 2);
+        }
+        __device__ __forceinline__ void tail() const
+        {
+#pragma unroll
+            for (int j = 0; j < SJ; ++j) {
+                if (S0 + j * PER >= SLOTS)
+                    read(j);
+                if (S0 + j * PER + PER - 2 >= SLOTS)
+                    add(j, 0);
+                if (S0 + j * PER + PER - 1 >= SLOTS)
+                    add(j, 2);
+            }
+            // over the row's 8 lanes: lane ^ 1, lane ^ 2, mirrored eights
+            int t = (int)c;
+            t += __builtin_amdgcn_update_dpp(0, t, 0xB1, 0xF, 0xF, true);
+            t += __builtin_amdgcn_update_dpp(0, t, 0x4E, 0xF, 0xF, true);
+            t += __builtin_amdgcn_update_dpp(0, t, 0x141, 0xF, 0xF, true);
+            if (write)
+                *out = (t - 128 * KS * KSTEP) * 128;
+        }
+        __device__ __forceinline__ void all() const
+        {
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s)
+                at(s);
+            tail();
+        }
+    };
 
     // One pass over a row tile in LDS (base) that ends with the first PDD
     // fragments of the next one (nbase) in the ring; OFF is the ring slot of
     // the pass's first fragment.
     template <int OFF, class Hook>
     static __device__ __forceinline__ void tile_pass(Parts &part, const xfrag (&xr)[QT][KS], frag (&f)[PDD],
-                                                     const lds_u8 *base, const lds_u8 *nbase, int &cs,
-                                                     const Hook &hook, const acc_t (&x0)[QT])
+                                                     const lds_u8 *base, const lds_u8 *nbase, const Hook &hook, const acc_t (&x0)[QT])
     {
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
             for (int k = 0; k < KC; ++k)
-                part[qt][k] = k == 0 ? x0[qt] : acc_t{};
-        cs = 0;
+                part[qt][k] = k == 0 ? x0[U8 ? 0 : qt] : acc_t{};
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const frag cur = weights(f[(OFF + s) % PDD]);
@@ -972,7 +1041,6 @@ struct Encoder {
                 } else {
                     mma(part[m][s % KC], cur, xr[m][s]);
                 }
-                cs = column_sum(cur, cs, m);
                 hook.at(s * MPS + m);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -980,32 +1048,31 @@ struct Encoder {
         hook.tail();
     }
 
-    // Epilogue of row tile w in phases of a few instructions, five per query
-    // tile: four take four dimensions each (adding the partial accumulators
-    // and the uint8 correction, then the signs: bytes {0, -1} of the Hamming
-    // MFMA's B operand, or bits), the fifth runs the Hamming MFMAs or finishes
-    // the word.  Encoding: a lane holds half the signs of a dimension tile for
-    // one query of each query tile; one lane-half swap gives the lower lanes
-    // the first tile's words and the upper lanes the second's, the 32-bit word
-    // of an even tile (LO) waits in hw, and the odd tile's last phase stores
+    // Epilogue of row tile w in phases of a few instructions: per query tile,
+    // EPG of them take four (or, where there is more to do than signs, two)
+    // dimensions each (adding the partial accumulators, then the signs: bytes {0, -1} of the Hamming MFMA's B
+    // operand, or bits), a last one runs the Hamming MFMAs or finishes the
+    // word.  Encoding: a lane holds half the signs of a dimension tile for one
+    // query of each query tile; one lane-half swap gives the lower lanes the
+    // first tile's words and the upper lanes the second's, the 32-bit word of
+    // an even tile (LO) waits in hw, and the odd tile's last phase stores
     // both as one 64-bit word per query (always issued, so that the barriers
     // can count it).
-    static constexpr int EPH = 5 * QT;
+    static constexpr int EPG = KC == 2 ? 8 : 4;
+    static constexpr int EPH = (EPG + 1) * QT;
     template <bool LO> struct EpiD {
         const EncodeArgs &a;
         Parts &part;
         v16i (&dacc)[KT][QT];
         const v4i (&cf)[KT];
-        const v4i (&cs4)[4];         // uint8: column sums of this lane's 16 dimensions
         uint32_t &hw;
         uint32_t *hrow;              // packed row of this lane's query
         int w, lane;
         mutable v4i mb[QT];
         mutable uint32_t bits[QT];
-
         __device__ __forceinline__ void phase(int p) const
         {
-            const int qt = p / 5, ph = p % 5;
+            const int qt = p / (EPG + 1), ph = p % (EPG + 1);
             acc_t &y = part[qt][0];
             if (CT != C_I8 && ph == 0) {
                 // The 16-pass E4M3 MFMA's accumulator was observed to be read
@@ -1015,29 +1082,34 @@ struct Encoder {
                 asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (ph < 4) {
-                const int j = 3 - ph;                      // registers 4j .. 4j + 3
+            if (ph < EPG) {
+                constexpr int NV = 16 / EPG;
+                const int v0 = 16 - NV * (ph + 1);         // registers v0 .. v0 + NV - 1
 #pragma unroll
-                for (int v = 4 * j; v < 4 * j + 4; ++v) {
+                for (int v = v0; v < v0 + NV; ++v) {
                     if constexpr (KC == 2)
                         y[v] += part[qt][1][v];
-                    if constexpr (U8)
-                        y[v] += cs4[j][v & 3] << 7;
                 }
                 if constexpr (MODE == M_CLASSIFY) {
                     // bytes: 0xFF where the projection is negative, else 0
-                    const uint32_t t0 = __builtin_amdgcn_perm(sign_word(y[4 * j + 1]), sign_word(y[4 * j]),
-                                                              0x0C0C0B09u);
-                    const uint32_t t1 = __builtin_amdgcn_perm(sign_word(y[4 * j + 3]), sign_word(y[4 * j + 2]),
-                                                              0x0B090C0Cu);
-                    mb[qt][j] = (int)(t0 | t1);
+                    // (two registers to bytes 0, 1 or 2, 3)
+#pragma unroll
+                    for (int v = v0; v < v0 + NV; v += 2) {
+                        const uint32_t t = __builtin_amdgcn_perm(sign_word(y[v + 1]), sign_word(y[v]),
+                                                                 v & 2 ? 0x0B090C0Cu : 0x0C0C0B09u);
+                        const int e = v >> 2;
+                        mb[qt][e] = (v & 2) == (NV == 2 ? 2 : 0) ? (int)t : mb[qt][e] | (int)t;
+                    }
                 } else {
                     // signs shifted in from the top: register v lands on bit
                     // 8 * (v / 4) + v % 4
-                    uint32_t b = ph == 0 ? 0u : bits[qt] << 4;
+                    uint32_t b = ph == 0 ? 0u : bits[qt];
 #pragma unroll
-                    for (int v = 4 * j + 3; v >= 4 * j; --v)
+                    for (int v = v0 + NV - 1; v >= v0; --v) {
+                        if (v % 4 == 3 && v < 15)
+                            b <<= 4;
                         b = __builtin_amdgcn_alignbit(b, sign_word(y[v]), 31);
+                    }
                     bits[qt] = b;
                 }
             } else if constexpr (MODE == M_CLASSIFY) {
@@ -1062,10 +1134,11 @@ struct Encoder {
             for (int p = 0; p < EPH; ++p)
                 phase(p);
         }
-        // as a pass hook: phase p in slot E0 + p * SPD (the uint8 column sums
-        // are on their way through LDS during the first K steps)
-        static constexpr int E0 = U8 && KS > 4 ? 2 * MPS : 0;
-        static constexpr int SPD = (SLOTS - E0) / EPH > 1 ? (SLOTS - E0) / EPH : 1;
+        // as a pass hook: phase p in slot E0 + p * SPD, the slot after a K
+        // step's last MFMA
+        static constexpr int E0 = MPS - 1;
+        static constexpr int SPA = (SLOTS - E0) / EPH / MPS * MPS;
+        static constexpr int SPD = SPA > MPS ? SPA : MPS;
         __device__ __forceinline__ void at(int s) const
         {
             if (s >= E0 && (s - E0) % SPD == 0 && (s - E0) / SPD < EPH)
@@ -1079,17 +1152,37 @@ struct Encoder {
         }
     };
 
-    // The barrier of a one-row-tile pass.
+    // The barrier of a one-row-tile pass; uint8: and, after it, the read of
+    // the next tile's start values.
+    static constexpr int BG = (NBUF - 2 - VIS) * NLOADS;   // loads it leaves in flight
     struct BarHook {
+        const lds_i32 *sums;
+        acc_t &start;
+        __device__ __forceinline__ void read_start() const
+        {
+            if constexpr (U8) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const v4i v = *(const lds_v4i *)(sums + 8 * j);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        start[4 * j + i] = v[i];
+                }
+            }
+        }
         __device__ __forceinline__ void at(int s) const
         {
             if (XPF && s == BAR * MPS + MPS - 1)
-                dma_barrier<(NBUF - 3) * NLOADS, false>();
+                dma_barrier<BG, false>();
+            if (XPF && s == (BAR + 2) * MPS + MPS - 1)
+                read_start();
         }
         __device__ __forceinline__ void tail() const
         {
-            if (!XPF)
-                dma_barrier<(NBUF - 3) * NLOADS, true>();
+            if (!XPF) {
+                dma_barrier<BG, true>();
+                read_start();
+            }
         }
     };
 
@@ -1159,42 +1252,38 @@ struct Encoder {
         fill(lp(0) + loff);
 
         v4i cf[KT];
-        v4i cs4[4];
         int b = 0;   // stage of the chunk being multiplied
         auto nxt = [&](int i) { return i == NBUF - 1 ? 0 : i + 1; };
         auto base = [&](int st, int rt) { return lp(st) + rt * kDimChunk * RSB + loff; };
-        lds_i32 *lcs = (lds_i32 *)(L + OFF_CS) + wave * kDimChunk;
-        // after a pass: its class fragments, and its column sums through LDS
-        // (lane l holds half of row l % 32's sum; each lane needs 16 rows')
-        auto after = [&](int rt, int cs) {
+        // start values of tile w: buffer w % 2; lane l reads 8 j + 4 (l / 32)
+        // .. + 3, and sums row 8 * wave + l / 8
+        lds_i32 *lcs = (lds_i32 *)(L + OFF_CS);
+        const int srow = 8 * wave + lane / 8;
+        const lds_u8 *sbase = L + srow * RSB + (lane & 7) * 16;
+        const bool slast = (SJ - 1) * 8 + (lane & 7) < KS * KSTEP / 16;
+        auto sum = [&](int w, int st) {
+            return SumHook{sbase + st * SSZ, lcs + (w & 1) * kDimChunk + srow, slast, (lane & 7) == 0};
+        };
+        auto bar = [&](int c) { return BarHook{lcs + ((c + 1) & 1) * kDimChunk + 4 * g, x0[0]}; };
+        // after a pass: its class fragments
+        auto after = [&](int rt) {
             if constexpr (MODE == M_CLASSIFY) {
 #pragma unroll
                 for (int kt = 0; kt < KT; ++kt)
                     cf[kt] = *(const lds_v4i *)(lc(b) + ((rt * KT + kt) * 64 + lane) * 16);
             }
-            if constexpr (U8) {
-                typedef unsigned v2u __attribute__((ext_vector_type(2)));
-                const v2u sw = __builtin_amdgcn_permlane32_swap((unsigned)cs, (unsigned)cs, false, false);
-                lcs[lane & 31] = (int)(sw[0] + sw[1]);
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    cs4[j] = *(const lds_v4i *)(lcs + 8 * j + 4 * g);
-                __builtin_amdgcn_wave_barrier();
-            }
         };
         auto loads = [&](int c, auto s0) {   // loads of chunk c + NBUF - 1 into the stage before b
-            const int b2 = b == 0 ? NBUF - 1 : b - 1;
+            const int b2 = __builtin_amdgcn_readfirstlane(b == 0 ? NBUF - 1 : b - 1);   // (kept scalar)
             return LoadHook<decltype(s0)::value>{ld, ld.chunk(c + NBUF - 1), lp(b2), lc(b2)};
         };
         auto epi = [&](auto lo, Parts &prev, int w) {
-            return EpiD<decltype(lo)::value>{a, prev, dacc, cf, cs4, hw, hrow, w, lane};
+            return EpiD<decltype(lo)::value>{a, prev, dacc, cf, hw, hrow, w, lane};
         };
         typedef std::integral_constant<bool, true> Lo;
         typedef std::integral_constant<bool, false> Hi;
 
         Parts P0, P1;
-        int cs;
         if constexpr (RT == 2) {
             typedef std::integral_constant<int, 0> S0;
             constexpr int O1 = KS % PDD;
@@ -1202,18 +1291,18 @@ struct Encoder {
             // the epilogue between the awaited loads and the barrier
             constexpr int G = MODE == M_ENCODE ? 1 : 0;
             auto second = [&](int c) {
-                tile_pass<O1>(P1, xr, f, base(b, 1), base(nxt(b), 0), cs,
+                tile_pass<O1>(P1, xr, f, base(b, 1), base(nxt(b), 0),
                               both(epi(Lo{}, P0, 2 * c), loads(c, S0{})), x0);
-                after(1, cs);
+                after(1);
                 b = nxt(b);
             };
-            tile_pass<0>(P0, xr, f, base(b, 0), base(b, 1), cs, NoHook{}, x0);
-            after(0, cs);
+            tile_pass<0>(P0, xr, f, base(b, 0), base(b, 1), NoHook{}, x0);
+            after(0);
             dma_barrier<0, false>();
             second(0);
             for (int c = 1; c < NC; ++c) {
-                tile_pass<0>(P0, xr, f, base(b, 0), base(b, 1), cs, epi(Hi{}, P1, 2 * c - 1), x0);
-                after(0, cs);
+                tile_pass<0>(P0, xr, f, base(b, 0), base(b, 1), epi(Hi{}, P1, 2 * c - 1), x0);
+                after(0);
                 dma_barrier<G, false>();
                 second(c);
             }
@@ -1225,13 +1314,24 @@ struct Encoder {
             typedef std::integral_constant<int, (XPF ? KS % PDD : 0)> O1;
             typedef std::integral_constant<int, 0> O0;
             auto step = [&](auto off, Parts &cur, int c, const auto &e) {
-                tile_pass<decltype(off)::value>(cur, xr, f, base(b, 0), base(nxt(b), 0), cs,
-                                                both(both(e, BarHook{}), loads(c, S0{})), x0);
-                after(0, cs);
+                if constexpr (U8)
+                    tile_pass<decltype(off)::value>(cur, xr, f, base(b, 0), base(nxt(b), 0),
+                                                    both(both(both(e, bar(c)), sum(c + 2, nxt(nxt(b)))), loads(c, S0{})), x0);
+                else
+                    tile_pass<decltype(off)::value>(cur, xr, f, base(b, 0), base(nxt(b), 0),
+                                                    both(both(e, bar(c)), loads(c, S0{})), x0);
+                after(0);
                 b = nxt(b);
                 if constexpr (!XPF)
                     fill(base(b, 0));
             };
+            if constexpr (U8) {   // start values of the first two tiles
+                dma_barrier<(NBUF - 3) * NLOADS, false>();
+                sum(0, 0).all();
+                sum(1, 1).all();
+                dma_barrier<(NBUF - 3) * NLOADS, true>();
+                bar(-1).read_start();
+            }
             step(O0{}, P0, 0, NoHook{});
             step(O1{}, P1, 1, epi(Lo{}, P0, 0));
             for (int c = 2; c < NC; c += 2) {
