@@ -71,43 +71,65 @@ void k_encode(EncodeArgs a)
     }
 }
 
-// Distances and argmin of a split classify launch: a workgroup takes 32
-// queries, thread (slot, query) sums the splits' partials of classes slot,
-// slot + 32, ... (coalesced over the queries, all of a class's loads in
-// flight), dist_k = popc_k - sum.  The first smallest distance wins, as in
-// Encoder::finish: the minimum of (distance, class) packed in one integer
-// (distances are at most 65536, classes below 128).
+// Distances and argmin of a split classify launch.  A workgroup takes QB
+// queries: wave w sums classes w, w + 16, .., its lanes 64 / QB splits x QB
+// queries (runs of the class-major partials), dist_k = popc_k - sum.  Few
+// queries are latency bound and go 8 to a workgroup; from 1024 on, 32 (whole
+// lines; 1559 queries, 26 classes, 32 splits: 1.5 us less than with 8).  The
+// first smallest distance wins, as in Encoder::finish: the minimum of
+// (distance, class) packed in one integer (distances are at most 65536,
+// classes below 128).  The distances go out through LDS, whole rows at once.
+template <int QB>
 static __global__ __launch_bounds__(1024) void k_split_argmin(EncodeArgs a, int Z)
 {
-    __shared__ int best[16][32];
-    const int ql = threadIdx.x & 31, slot = threadIdx.x >> 5, wave = threadIdx.x >> 6;
-    const int64_t q = (int64_t)blockIdx.x * 32 + ql, qc = q < a.n ? q : a.n - 1;
+    constexpr int ZL = 64 / QB;
+    __shared__ int best[16][QB];
+    __shared__ int32_t dist[QB * kMaxK];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ql = lane % QB, zl = lane / QB;
+    const int64_t q0 = (int64_t)blockIdx.x * QB, q = q0 + ql, qc = q < a.n ? q : a.n - 1;
     const int64_t zs = a.n * a.K;
     int m = 0x7fffffff;
-    for (int k = slot; k < a.K; k += 32) {
+    for (int k = wave; k < a.K; k += 16) {
         const int32_t *p = a.part + k * a.n + qc;
         int s = 0;
-#pragma unroll 16
-        for (int z = 0; z < Z; ++z)
+#pragma unroll 8
+        for (int z = zl; z < Z; z += ZL)
             s += p[z * zs];
+#pragma unroll
+        for (int o = QB; o < 64; o *= 2)
+            s += __shfl_xor(s, o);
         const int d = a.cpop[k] - s;
-        if (a.dists && q < a.n)
-            a.dists[q * a.K + k] = d;
+        if (zl == 0 && a.dists)
+            dist[ql * a.K + k] = d;
         const int key = d * 128 + k;
         m = key < m ? key : m;
     }
-    const int o = __shfl_xor(m, 32);
-    m = o < m ? o : m;
-    if (threadIdx.x % 64 < 32)
+    if (zl == 0)
         best[wave][ql] = m;
     __syncthreads();
-    if (threadIdx.x < 32) {
+    const int nq = a.n - q0 < QB ? (int)(a.n - q0) : QB;
+    if (a.dists)
+        for (int i = threadIdx.x; i < nq * a.K; i += 1024)
+            a.dists[q0 * a.K + i] = dist[i];
+    if ((int)threadIdx.x < nq) {
+        m = best[0][threadIdx.x];
 #pragma unroll
-        for (int w = 0; w < 16; ++w)
-            m = best[w][ql] < m ? best[w][ql] : m;
-        if (q < a.n)
-            a.labels[q] = m % 128;
+        for (int w = 1; w < 16; ++w)
+            m = best[w][threadIdx.x] < m ? best[w][threadIdx.x] : m;
+        a.labels[q] = m % 128;
     }
+}
+
+// Smallest dimension split (64-dimension words) of a launch.
+constexpr int split_units_min(int mode) { return mode == M_ENCODE ? 1 : kSplitMinUnits; }
+
+// Whether two query tiles per wave would leave half the device idle: then one
+// query tile (128 queries per workgroup) makes twice the workgroups, each
+// with half the features to load and half the MFMAs.
+static bool few_blocks(const EncodeArgs &a, int mode)
+{
+    const int64_t blocks = (a.n + 255) / 256;
+    return 2 * blocks * split_count(blocks, a.nd, a.max_split, 256, split_units_min(mode)) <= 256;
 }
 
 template <int CT, int XF, int QT, int KS, int KT, int MODE, bool DMA = false, int RT = 1, int SRC = W_ROWS>
@@ -116,13 +138,17 @@ static hipError_t launch_one(const EncodeArgs &a, hipStream_t st)
     typedef Encoder<CT, XF, QT, KS, KT, MODE, 0, DMA, RT, SRC> E;
     const int64_t blocks = (a.n + E::QPB - 1) / E::QPB;
     // resident workgroups: one per CU per wave per SIMD the kernel is built for
-    const int Z = split_count(blocks, a.nd, a.max_split, 256 * E::WAVES);
+    const int Z = split_count(blocks, a.nd, a.max_split, 256 * E::WAVES, split_units_min(MODE));
     EncodeArgs b = a;
     b.nsplit = Z;
     const dim3 grid = Z > 1 ? dim3((unsigned)Z, (unsigned)blocks) : dim3((unsigned)blocks);
     hipLaunchKernelGGL((k_encode<CT, XF, QT, KS, KT, MODE, DMA, RT, SRC>), grid, dim3(256), 0, st, b);
-    if (MODE == M_CLASSIFY && Z > 1)
-        hipLaunchKernelGGL(k_split_argmin, dim3((unsigned)((a.n + 31) / 32)), dim3(1024), 0, st, a, Z);
+    if (MODE == M_CLASSIFY && Z > 1) {
+        if (a.n >= 1024)
+            hipLaunchKernelGGL(k_split_argmin<32>, dim3((unsigned)((a.n + 31) / 32)), dim3(1024), 0, st, a, Z);
+        else
+            hipLaunchKernelGGL(k_split_argmin<8>, dim3((unsigned)((a.n + 7) / 8)), dim3(1024), 0, st, a, Z);
+    }
     return hipGetLastError();
 }
 
@@ -142,6 +168,8 @@ static hipError_t launch_direct(const EncodeArgs &a, hipStream_t st)
     constexpr int W = KS * Tr<CT>::KSTEP;
     constexpr int QT = CT == C_FP8S || (W > 832 && KT == 4) ? 1 : 2;
     constexpr int RT = W > 640 || (CT == C_I8 && SRC == W_ALT) ? 1 : 2;
+    if (QT == 2 && !a.poff && few_blocks(a, MODE))
+        return launch_one<CT, 0, 1, KS, KT, MODE, true, 1, SRC>(a, st);
     return launch_one<CT, 0, QT, KS, KT, MODE, true, RT, SRC>(a, st);
 }
 
@@ -204,13 +232,15 @@ static hipError_t launch_bytes(const EncodeArgs &a, int mode, Tile tile, hipStre
 }
 
 // One width of fp32 features, register staged: as many query tiles per wave
-// as fit (the built-in rule), or the variant's.
+// as fit, one where two leave half the device idle (the built-in rule; 200 x
+// 64, 2048 dimensions: 29 us with two), or the variant's.
 template <int CT, int W>
 static hipError_t launch_fp32_bucket(const EncodeArgs &a, int mode, Tile tile, hipStream_t st)
 {
     constexpr int KS = W / Tr<CT>::KSTEP;
     constexpr int QM = qt2_fits(CT, KS) ? 2 : 1;
-    const int qt = (tile.variant == TV_REG_QT1 || QM == 1) ? 1 : 2;
+    const bool one = QM == 1 || tile.variant == TV_REG_QT1 || (tile.variant == TV_AUTO && few_blocks(a, mode));
+    const int qt = one ? 1 : 2;
     if (mode == M_ENCODE) {
         if (qt == 2)
             return launch_one<CT, 1, QM, KS, 1, M_ENCODE>(a, st);

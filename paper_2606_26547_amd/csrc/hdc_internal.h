@@ -57,19 +57,20 @@ struct EncodeArgs {
 // dimensions: as many as keep blocks * splits within `target` workgroups
 // (the device's resident workgroups for the kernel: one round, no tail),
 // each split at least kSplitMinUnits whole 64-dimension words, at most `cap`
-// (1 = no split).  The kernel maps split z of Z to words [z*per, (z+1)*per)
+// (1 = no split).  An encoding has no partial sums to write and add, so its
+// splits go down to one word.  The kernel maps split z of Z to words [z*per, (z+1)*per)
 // with per = split_units(nd, Z) = ceil(words / Z); the count returned is
 // ceil(words / per), so that no split is empty.
 constexpr int kSplitMinUnits = 4;
 constexpr int kQpbMax = 256;        // most queries per encoder workgroup (any variant)
 constexpr int kSplitTargetMax = 512;   // two resident workgroups per CU at most
-__host__ __device__ inline int split_count(int64_t blocks, int nd, int cap, int target)
+__host__ __device__ inline int split_count(int64_t blocks, int nd, int cap, int target, int min_units = kSplitMinUnits)
 {
     const int units = (nd + 63) / 64;
-    if (blocks <= 0 || 2 * blocks > target || units < 2 * kSplitMinUnits || cap < 2)
+    if (blocks <= 0 || 2 * blocks > target || units < 2 * min_units || cap < 2)
         return 1;
     int64_t z = target / blocks;
-    const int zmax = units / kSplitMinUnits;
+    const int zmax = units / min_units;
     z = z < zmax ? z : zmax;
     z = z < cap ? z : cap;
     const int per = (int)((units + z - 1) / z);

@@ -14,13 +14,10 @@ namespace hdc {
 // bytes occupy in lane l: byte b <-> dimension 32c + 8*(b/4) + 4*(l/32) + b%4.
 // Classes >= K and dimensions >= nd are 0.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_class_table(const uint64_t *__restrict__ C, int K, int64_t ldc,
-                                                     int s0, int stride, int nd, int KT, int64_t total,
-                                                     int8_t *__restrict__ tab)
+__device__ __forceinline__ void class_table_entry(const uint64_t *__restrict__ C, int K, int64_t ldc, int s0,
+                                                  int stride, int nd, int KT, int64_t idx,
+                                                  int8_t *__restrict__ tab)
 {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total)
-        return;
     const int lane = (int)(idx & 63);
     const int kt = (int)((idx >> 6) % KT);
     const int64_t c = (idx >> 6) / KT;
@@ -40,12 +37,12 @@ __global__ __launch_bounds__(256) void k_class_table(const uint64_t *__restrict_
     *(uint4 *)(tab + idx * 16) = make_uint4(out[0], out[1], out[2], out[3]);
 }
 
-// popc[k] = number of -1 elements of class k over S (0 for k >= K).
-__global__ __launch_bounds__(256) void k_class_popc(const uint64_t *__restrict__ C, int K, int64_t ldc,
-                                                    int s0, int stride, int nd, int32_t *__restrict__ popc)
+// popc[k] = number of -1 elements of class k over S (0 for k >= K), one
+// workgroup per class.
+__device__ __forceinline__ void class_popc(const uint64_t *__restrict__ C, int K, int64_t ldc, int s0, int stride,
+                                           int nd, int k, int32_t *__restrict__ popc)
 {
     __shared__ int part[256];
-    const int k = blockIdx.x;
     int s = 0;
     if (k < K)
         for (int64_t dl = threadIdx.x; dl < nd; dl += 256) {
@@ -63,6 +60,28 @@ __global__ __launch_bounds__(256) void k_class_popc(const uint64_t *__restrict__
         popc[k] = part[0];
 }
 
+// The table and the counts in one launch (each is shorter than a launch): the
+// first 32 * KT workgroups count, the rest fill.
+__global__ __launch_bounds__(256) void k_class_operand(const uint64_t *__restrict__ C, int K, int64_t ldc, int s0,
+                                                       int stride, int nd, int KT, int64_t total,
+                                                       int8_t *__restrict__ tab, int32_t *__restrict__ popc)
+{
+    const int nk = 32 * KT;
+    if ((int)blockIdx.x < nk) {
+        class_popc(C, K, ldc, s0, stride, nd, (int)blockIdx.x, popc);
+        return;
+    }
+    const int64_t idx = (int64_t)((int)blockIdx.x - nk) * 256 + threadIdx.x;
+    if (idx < total)
+        class_table_entry(C, K, ldc, s0, stride, nd, KT, idx, tab);
+}
+
+__global__ __launch_bounds__(256) void k_class_popc(const uint64_t *__restrict__ C, int K, int64_t ldc, int s0,
+                                                    int stride, int nd, int32_t *__restrict__ popc)
+{
+    class_popc(C, K, ldc, s0, stride, nd, (int)blockIdx.x, popc);
+}
+
 hipError_t launch_class_popc(const uint64_t *C, int K, int64_t ldc, int s0, int stride, int nd, int KT,
                              int32_t *cpop, hipStream_t st)
 {
@@ -75,9 +94,8 @@ hipError_t launch_class_table(const uint64_t *C, int K, int64_t ldc, int s0, int
 {
     const int KT = class_tiles(K);
     const int64_t total = table_chunks(nd) * KT * 64;
-    hipLaunchKernelGGL(k_class_table, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, C, K, ldc,
-                       s0, stride, nd, KT, total, tab);
-    hipLaunchKernelGGL(k_class_popc, dim3(KT * 32), dim3(256), 0, st, C, K, ldc, s0, stride, nd, cpop);
+    hipLaunchKernelGGL(k_class_operand, dim3((unsigned)(32 * KT + (total + 255) / 256)), dim3(256), 0, st, C, K, ldc,
+                       s0, stride, nd, KT, total, tab, cpop);
     return hipGetLastError();
 }
 

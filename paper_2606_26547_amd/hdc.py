@@ -190,8 +190,8 @@ def encode(X: torch.Tensor, F: int, P: torch.Tensor, D: int, compute="int8", sta
     end = D if end is None else end
     nd = dims_count(start, end, stride)
     n = X.shape[0]
-    if out is None:
-        out = torch.zeros((n, words(nd)), dtype=torch.int64, device=X.device)
+    if out is None:   # every word of every row is written by the call
+        out = torch.empty((n, words(nd)), dtype=torch.int64, device=X.device)
     _check(_lib.hdc_encode_tiled(_stream(), _ptr(X), _xtype(X), n, F, X.shape[1], _ptr(P), D, P.shape[1],
                                  DTYPE[compute], Dims(start, end, stride), _ptr(out), out.shape[1], int(tile)),
            "hdc_encode")
