@@ -92,9 +92,15 @@ static __global__ __launch_bounds__(1024) void k_split_argmin(EncodeArgs a, int 
     for (int k = wave; k < a.K; k += 16) {
         const int32_t *p = a.part + k * a.n + qc;
         int s = 0;
-#pragma unroll 8
-        for (int z = zl; z < Z; z += ZL)
-            s += p[z * zs];
+        for (int z0 = zl; z0 < Z; z0 += 8 * ZL) {   // eight loads in flight, also for few splits
+            int v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                v[u] = p[(z0 + u * ZL < Z ? z0 + u * ZL : z0) * zs];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                s += z0 + u * ZL < Z ? v[u] : 0;
+        }
 #pragma unroll
         for (int o = QB; o < 64; o *= 2)
             s += __shfl_xor(s, o);
@@ -120,6 +126,14 @@ static __global__ __launch_bounds__(1024) void k_split_argmin(EncodeArgs a, int 
     }
 }
 
+static void launch_split_argmin(const EncodeArgs &a, int Z, hipStream_t st)
+{
+    if (a.n >= 1024)
+        hipLaunchKernelGGL(k_split_argmin<32>, dim3((unsigned)((a.n + 31) / 32)), dim3(1024), 0, st, a, Z);
+    else
+        hipLaunchKernelGGL(k_split_argmin<8>, dim3((unsigned)((a.n + 7) / 8)), dim3(1024), 0, st, a, Z);
+}
+
 // Smallest dimension split (64-dimension words) of a launch.
 constexpr int split_units_min(int mode) { return mode == M_ENCODE ? 1 : kSplitMinUnits; }
 
@@ -143,12 +157,8 @@ static hipError_t launch_one(const EncodeArgs &a, hipStream_t st)
     b.nsplit = Z;
     const dim3 grid = Z > 1 ? dim3((unsigned)Z, (unsigned)blocks) : dim3((unsigned)blocks);
     hipLaunchKernelGGL((k_encode<CT, XF, QT, KS, KT, MODE, DMA, RT, SRC>), grid, dim3(256), 0, st, b);
-    if (MODE == M_CLASSIFY && Z > 1) {
-        if (a.n >= 1024)
-            hipLaunchKernelGGL(k_split_argmin<32>, dim3((unsigned)((a.n + 31) / 32)), dim3(1024), 0, st, a, Z);
-        else
-            hipLaunchKernelGGL(k_split_argmin<8>, dim3((unsigned)((a.n + 7) / 8)), dim3(1024), 0, st, a, Z);
-    }
+    if (MODE == M_CLASSIFY && Z > 1)
+        launch_split_argmin(a, Z, st);
     return hipGetLastError();
 }
 

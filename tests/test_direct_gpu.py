@@ -75,3 +75,24 @@ def test_direct_wide_row_pitch(hdc, compute):
     Xd[:, :F] = torch.as_tensor(X).cuda()
     H = hdc.encode(Xd, F, hdc.pad_cols(P), D, compute)
     assert np.array_equal(H.cpu().numpy().view(np.uint64), O.encode(X, P, compute))
+
+
+FEW = [(1, 1, 512, 1, None), (33, 63, 2048, 10, None), (200, 64, 2000, 33, (3, 1999, 1)), (31, 65, 1024, 100, None),
+       (129, 128, 4100, 26, (1, 4100, 2)), (64, 200, 1025, 64, None), (250, 256, 2048, 128, None)]
+
+
+@pytest.mark.parametrize("shape", FEW, ids=str)
+def test_few_fp32_queries_equal_the_encoder(hdc, shape):
+    """The fp32 classifier for few queries sums in the register-staged
+    encoder's order: labels and distances equal that kernel's bit for bit."""
+    n, F, D, K, dims = shape
+    s, e, k = dims or (0, D, 1)
+    X, P = dg.random_case(n, F, D, "fp32", seed=n + F + D)
+    g = np.random.default_rng(K)
+    Cw = g.integers(0, 2 ** 63, size=(K, (D + 63) // 64), dtype=np.int64)
+    if D % 64:
+        Cw[:, -1] &= (1 << (D % 64)) - 1
+    Xd, Pd, Cd = hdc.pad_cols(X), _padded(P, (F + 63) // 64 * 64, 2), torch.as_tensor(Cw).cuda()
+    got = hdc.classify(Xd, F, Pd, D, Cd, "fp32", s, e, k, with_dists=True)
+    ref = hdc.classify(Xd, F, Pd, D, Cd, "fp32", s, e, k, with_dists=True, tile=3)
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
