@@ -4,12 +4,12 @@
 //
 // Level-ID: bit d of a row's hypervector is set when more than half of the
 // F bound pairs ID_f xor LV_level(f) have bit d set (the bipolar sum is
-// F - 2*count; a zero sum gives +1).  One thread owns 64 dimensions of one
-// row; per feature it XORs the ID word with the level word (both from LDS;
-// levels come 8 to a 16-byte load) and adds the result to a bit-sliced
-// counter through a carry-save (Harley-Seal) tree: 16 inputs take 15
-// three-operation adders and one ripple add of the weight-16 carries,
-// about four operations per input and 32-bit half.
+// F - 2*count; a zero sum gives +1).  A lane owns two 64-bit words of a few
+// rows; per feature it takes the level words from LDS and adds them, bound to
+// the ID words, to a bit-sliced counter through a carry-save tree (see
+// k_level_id).
+#include <type_traits>
+
 #include "hdc_device.h"
 
 namespace hdc {
@@ -54,96 +54,139 @@ hipError_t launch_gather_cols(const void *X, int elem, int64_t n, int64_t ldx, i
 // level = floor((x - lo) * L / (hi - lo)) in binary32, each step rounded to
 // nearest even (no contraction), 0 for an empty range, a value at or below
 // lo, or NaN; L - 1 at or above the top level.
+//
+// Streaming bound: a thread takes one feature of kLqRows rows, all its loads
+// in flight, the range read once (one element per thread, with a 64-bit
+// division to find it, took 41 us for 32768 x 617; the bytes take 25).
+constexpr int kLqRows = 8;
 __global__ __launch_bounds__(256) void k_level_quantize(const float *__restrict__ X, int64_t n, int F, int64_t ldx,
                                                         const float *__restrict__ lo, const float *__restrict__ hi,
                                                         int L, uint16_t *__restrict__ lev, int64_t ldl)
 {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= n * F)
+    const int f = blockIdx.y * 64 + (threadIdx.x & 63);
+    if (f >= F)
         return;
-    const int64_t i = idx / F;
-    const int f = (int)(idx - i * F);
-    const float t = __fsub_rn(X[i * ldx + f], lo[f]);
-    const float w = __fsub_rn(hi[f], lo[f]);
-    const float v = __fdiv_rn(__fmul_rn(t, (float)L), w);
-    int level;
-    if (!(w > 0.0f) || !(v > 0.0f))
-        level = 0;
-    else if (v >= (float)(L - 1))
-        level = L - 1;
-    else
-        level = (int)floorf(v);
-    lev[i * ldl + f] = (uint16_t)level;
+    const int64_t i0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kLqRows;
+    const float l0 = lo[f], w = __fsub_rn(hi[f], l0);
+    float x[kLqRows];
+#pragma unroll
+    for (int r = 0; r < kLqRows; ++r)
+        x[r] = X[(i0 + r < n ? i0 + r : n - 1) * ldx + f];
+#pragma unroll
+    for (int r = 0; r < kLqRows; ++r) {
+        const float v = __fdiv_rn(__fmul_rn(__fsub_rn(x[r], l0), (float)L), w);
+        int level;
+        if (!(w > 0.0f) || !(v > 0.0f))
+            level = 0;
+        else if (v >= (float)(L - 1))
+            level = L - 1;
+        else
+            level = (int)floorf(v);
+        if (i0 + r < n)
+            lev[(i0 + r) * ldl + f] = (uint16_t)level;
+    }
 }
 
 hipError_t launch_level_quantize(const float *X, int64_t n, int F, int64_t ldx, const float *lo, const float *hi,
                                  int L, uint16_t *lev, int64_t ldl, hipStream_t st)
 {
-    const int64_t total = n * F;
-    hipLaunchKernelGGL(k_level_quantize, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, X, n, F, ldx, lo,
-                       hi, L, lev, ldl);
+    const dim3 grid((unsigned)((n + 4 * kLqRows - 1) / (4 * kLqRows)), (unsigned)((F + 63) / 64));
+    hipLaunchKernelGGL(k_level_quantize, grid, dim3(256), 0, st, X, n, F, ldx, lo, hi, L, lev, ldl);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- Level-ID
-constexpr int kLidWords = 8;    // 64-bit words (512 dimensions) per workgroup
-constexpr int kLidRows = 32;    // rows per pass of a workgroup (256 threads / 8 words)
-constexpr int kLidPasses = 4;   // passes over one staged window (128 rows per workgroup)
-constexpr int kLidLvPitch = 9;  // padded level-row pitch in LDS (64-bit words)
-constexpr int kLidBig = 7;      // planes of the weight-16 counter (F <= 1024 -> count/16 <= 64)
+constexpr int kLidFeat = 32;    // features per ripple of the counters
+constexpr int kLidBig = 6;      // planes of the weight-32 counter (F <= 1024 -> count / 32 <= 32)
 
-size_t lid_lds_bytes(int F, int L) { return ((size_t)F * kLidWords + (size_t)L * kLidLvPitch) * 8; }
-
-// carry-save adder: (h, l) = (majority, parity) of (a, b, c)
-__device__ __forceinline__ void csa(uint64_t &h, uint64_t &l, uint64_t a, uint64_t b, uint64_t c)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
 {
-    const uint64_t u = a ^ b;
-    h = ((a ^ c) & u) ^ a;      // a where a == b, c elsewhere (a bit select)
-    l = u ^ c;
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+// acc + x + y: parity to acc, majority returned
+__device__ __forceinline__ uint32_t csa(uint32_t &acc, uint32_t x, uint32_t y)
+{
+    const uint32_t c = __builtin_amdgcn_bitop3_b32(acc, x, y, 0xE8);
+    acc = xor3(acc, x, y);
+    return c;
+}
+
+// acc + (a xor i) + (b xor j) in three operations: with u = acc ^ a ^ i and
+// s = u ^ b ^ j the carry is the second input where u is set (b ^ j = ~s
+// there), else acc.
+__device__ __forceinline__ uint32_t csa_bound(uint32_t &acc, uint32_t a, uint32_t i, uint32_t b, uint32_t j)
+{
+    const uint32_t u = xor3(acc, a, i), s = xor3(u, b, j);
+    const uint32_t c = __builtin_amdgcn_bitop3_b32(u, s, acc, 0x3A);   // u ? ~s : acc
+    acc = s;
+    return c;
 }
 
 struct LidCounter {
-    uint64_t ones = 0, twos = 0, fours = 0, eights = 0, big[kLidBig] = {};
+    uint32_t ones[4], twos[4], fours[4], eights[4], sixteens[4], big[kLidBig][4];
+    uint32_t f[4], e[4], h[4];   // pending carries of weight 4, 8 and 16
 
-    // add 16 one-bit inputs per dimension
-    __device__ __forceinline__ void add16(const uint64_t (&x)[16])
+    __device__ __forceinline__ void clear()
     {
-        uint64_t ta, tb, fa, fb, ea, eb, sixteens;
-        csa(ta, ones, ones, x[0], x[1]);
-        csa(tb, ones, ones, x[2], x[3]);
-        csa(fa, twos, twos, ta, tb);
-        csa(ta, ones, ones, x[4], x[5]);
-        csa(tb, ones, ones, x[6], x[7]);
-        csa(fb, twos, twos, ta, tb);
-        csa(ea, fours, fours, fa, fb);
-        csa(ta, ones, ones, x[8], x[9]);
-        csa(tb, ones, ones, x[10], x[11]);
-        csa(fa, twos, twos, ta, tb);
-        csa(ta, ones, ones, x[12], x[13]);
-        csa(tb, ones, ones, x[14], x[15]);
-        csa(fb, twos, twos, ta, tb);
-        csa(eb, fours, fours, fa, fb);
-        csa(sixteens, eights, eights, ea, eb);
-        uint64_t c = sixteens;
 #pragma unroll
-        for (int p = 0; p < kLidBig; ++p) {
-            const uint64_t nc = big[p] & c;
-            big[p] ^= c;
-            c = nc;
+        for (int k = 0; k < 4; ++k) {
+            ones[k] = twos[k] = fours[k] = eights[k] = sixteens[k] = f[k] = e[k] = h[k] = 0;
+#pragma unroll
+            for (int p = 0; p < kLidBig; ++p)
+                big[p][k] = 0;
         }
     }
-
-    // count = ones + 2 twos + 4 fours + 8 eights + 16 big: one plane per
-    // weight, i.e. the count's binary digits; returns count > T per bit.
-    __device__ __forceinline__ uint64_t greater(uint32_t T) const
+    // four features (level words a, identity words id), group q of 8
+    __device__ __forceinline__ void add4(int q, const v4i (&a)[4], const v4i (&id)[4])
     {
-        uint64_t cnt[4 + kLidBig] = {ones, twos, fours, eights};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t t0 = csa_bound(ones[k], (uint32_t)a[0][k], (uint32_t)id[0][k], (uint32_t)a[1][k],
+                                          (uint32_t)id[1][k]);
+            const uint32_t t1 = csa_bound(ones[k], (uint32_t)a[2][k], (uint32_t)id[2][k], (uint32_t)a[3][k],
+                                          (uint32_t)id[3][k]);
+            const uint32_t c4 = csa(twos[k], t0, t1);
+            if (q % 2 == 0) {
+                f[k] = c4;
+                continue;
+            }
+            const uint32_t c8 = csa(fours[k], f[k], c4);
+            if (q % 4 == 1) {
+                e[k] = c8;
+                continue;
+            }
+            const uint32_t c16 = csa(eights[k], e[k], c8);
+            if (q == 3) {
+                h[k] = c16;
+                continue;
+            }
+            uint32_t c = csa(sixteens[k], h[k], c16);
+#pragma unroll
+            for (int p = 0; p < kLidBig; ++p) {
+                const uint32_t nc = big[p][k] & c;
+                big[p][k] ^= c;
+                c = nc;
+            }
+        }
+        // in order: later reads, or these sums, moved across here would not
+        // fit the registers
+        asm volatile("" : "+v"(ones[0]), "+v"(ones[1]), "+v"(ones[2]), "+v"(ones[3]), "+v"(twos[0]), "+v"(twos[1]),
+                     "+v"(twos[2]), "+v"(twos[3])::"memory");
+        if (q % 2 == 1)
+            asm volatile("" : "+v"(fours[0]), "+v"(fours[1]), "+v"(fours[2]), "+v"(fours[3]));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // bit set where count > T
+    __device__ __forceinline__ uint32_t greater(int k, uint32_t T) const
+    {
+        uint32_t cnt[5 + kLidBig] = {ones[k], twos[k], fours[k], eights[k], sixteens[k]};
 #pragma unroll
         for (int p = 0; p < kLidBig; ++p)
-            cnt[4 + p] = big[p];
-        uint64_t gt = 0, eq = ~0ull;
+            cnt[5 + p] = big[p][k];
+        uint32_t gt = 0, eq = ~0u;
 #pragma unroll
-        for (int p = 4 + kLidBig - 1; p >= 0; --p) {
+        for (int p = 5 + kLidBig - 1; p >= 0; --p) {
             if ((T >> p) & 1u) {
                 eq &= cnt[p];
             } else {
@@ -155,111 +198,203 @@ struct LidCounter {
     }
 };
 
-// Bit word of one row: dimensions of the thread's word where more than half
-// of the F bound pairs are -1.
-__device__ __forceinline__ uint64_t level_id_word(const uint16_t *__restrict__ lrow, int F, int L,
-                                                  const HDC_LDS uint64_t *sidw, const HDC_LDS uint64_t *slvw)
+// Shape of a launch: LPR lanes of two words share a row (a window of 2 * LPR
+// words), each lane takes R rows.  With LPR = 16 the 16 lanes that LDS
+// serves at a time read one whole 256-byte level row, all 64 banks, whatever
+// its level (8 lanes of one word met bank conflicts).  Identity words come
+// from L2, a group of features ahead: through LDS as well, the two rows'
+// reads would keep LDS busy longer than the vector units.  These bound it: 2.8
+// operations per dword and feature in the tree (the bound inputs enter it in
+// 1.5, see csa_bound; 32 features per ripple) and 1.25 per level address and
+// lane, against 13 per 64-bit word and feature for plain xor and majority on
+// one word per lane.
+template <int LPR, int R> struct LidShape {
+    static constexpr int W = 2 * LPR;                      // words per window
+    static constexpr int RPW = 64 / LPR;                   // rows per wave at a time
+    static constexpr int ROWS = kWaves * RPW * R;      // rows per workgroup
+    static constexpr int PITCH = W * 8 + (LPR == 16 ? 0 : 16);   // bytes per level row in LDS
+    static size_t lds(int L) { return (size_t)(L + 1) * PITCH; }
+};
+
+// base + pitch * the low (HI: high) half of the level pair
+template <bool HI> __device__ __forceinline__ uint32_t lid_addr(uint32_t pair, uint32_t pitch, uint32_t base)
 {
-    const uint4 *lr = (const uint4 *)lrow;                 // 8 levels per 16 bytes
-    LidCounter cnt;
-    const int Ffull = F & ~15;
-    int f0 = 0;
-    for (; f0 < Ffull; f0 += 16) {
-        const uint4 a = lr[f0 / 8], b = lr[f0 / 8 + 1];
-        const uint32_t lw[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        uint64_t x[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const uint32_t l = min((lw[u / 2] >> (16 * (u & 1))) & 0xffffu, (uint32_t)L - 1u);
-            x[u] = sidw[(f0 + u) * kLidWords] ^ slvw[__umul24(l, (uint32_t)kLidLvPitch)];
-        }
-        cnt.add16(x);
-    }
-    if (f0 < F) {                                      // tail: F - f0 < 16 features
-        uint64_t x[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            x[u] = 0;
-            if (f0 + u < F) {
-                const int l = min((int)lrow[f0 + u], L - 1);
-                x[u] = sidw[(f0 + u) * kLidWords] ^ slvw[l * kLidLvPitch];
-            }
-        }
-        cnt.add16(x);
-    }
-    return cnt.greater((uint32_t)F >> 1);
+    uint32_t r;
+    if constexpr (HI)
+        asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(r) : "v"(pair), "v"(pitch), "v"(base));
+    else
+        asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(r) : "v"(pair), "v"(pitch), "v"(base));
+    return r;
 }
 
-__global__ __launch_bounds__(256) void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl,
-                                                  const uint64_t *__restrict__ ID, int64_t ldid,
-                                                  const uint64_t *__restrict__ LV, int L, int64_t ldlv, int D,
-                                                  uint64_t *__restrict__ H, int64_t ldh)
+template <int LPR, int R>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(R == 1 ? 3 : 2)))
+void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl, const uint64_t *__restrict__ ID,
+                int64_t ldid, const uint64_t *__restrict__ LV, int L, int64_t ldlv, int D, uint64_t *__restrict__ H,
+                int64_t ldh)
 {
-    extern __shared__ __align__(16) uint64_t lds_raw[];
+    typedef LidShape<LPR, R> S;
+    typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+    extern __shared__ __align__(16) uint8_t lid_lds[];
+    lds_u8 *slv = (lds_u8 *)lid_lds;
     typedef HDC_LDS uint64_t lds_u64;
-    lds_u64 *sid = (lds_u64 *)lds_raw;                 // [F][kLidWords]
-    lds_u64 *slv = sid + F * kLidWords;                // [L][kLidLvPitch]
-    const int t = threadIdx.x;
-    const int W = (D + 63) / 64;
-    const int w0 = blockIdx.x * kLidWords;
-    const int nw = min(kLidWords, W - w0);
-    // staging: 8 independent loads in flight per thread before their stores
-    {
-        const int ne = (F + L) * kLidWords;
-        for (int e0 = 0; e0 < ne; e0 += 8 * 256) {
-            uint64_t v[8];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int W = (D + 63) / 64, w0 = blockIdx.y * S::W;
+    const int nw = W - w0 < S::W ? W - w0 : S::W;
+
+    // level rows of the window, then a row of zeros (the level of features
+    // past F, whose identity words are zero too)
+    for (int e = t; e < (L + 1) * S::W; e += 256) {
+        const int r = e / S::W, w = e % S::W;
+        *(lds_u64 *)(slv + r * S::PITCH + w * 8) = r < L && w < nw ? LV[(int64_t)r * ldlv + w0 + w] : 0;
+    }
+    const int wl = lane % LPR;                             // this lane's words: w0 + 2 wl, + 1
+    const int64_t row0 = (int64_t)blockIdx.x * S::ROWS + wave * (S::RPW * R) + lane / LPR;
+    const uint16_t *lrow[R];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int e = e0 + j * 256 + t;
-                const int r = e / kLidWords, w = e % kLidWords;
-                v[j] = 0;
-                if (e < ne && w < nw)
-                    v[j] = r < F ? ID[(int64_t)r * ldid + w0 + w] : LV[(int64_t)(r - F) * ldlv + w0 + w];
-            }
+    for (int r = 0; r < R; ++r) {
+        const int64_t row = row0 + r * S::RPW;
+        lrow[r] = lev + (row < n ? row : n - 1) * ldl;
+    }
+    // eight levels of each row from feature f on (past the row: its first)
+    auto lev_load = [&](uint4 (&l)[R], int f) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int e = e0 + j * 256 + t;
-                const int r = e / kLidWords, w = e % kLidWords;
-                if (e < ne) {
-                    if (r < F)
-                        sid[e] = v[j];
-                    else
-                        slv[(r - F) * kLidLvPitch + w] = v[j];
+        for (int r = 0; r < R; ++r)
+            l[r] = *(const uint4 *)(lrow[r] + (f < F ? f : 0));
+    };
+    // this lane's identity words of features f .. f + 3, zero past the row
+    // (a buffer of one row's words: no address past its end is read) or past F
+    auto id_load = [&](v4i (&id)[4], int f) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int fu = f + u;
+            const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(ID + (int64_t)(fu < F ? fu : 0) * ldid), 0, fu < F ? W * 8 : 0, 0x00020000);
+            id[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(row, (w0 + 2 * wl) * 8, 0, 0));
+        }
+    };
+    LidCounter cnt[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        cnt[r].clear();
+    const uint32_t lbase = (uint32_t)(uintptr_t)slv + wl * 16;
+    const uint32_t lmax = (uint32_t)(L - 1) * 0x10001u;
+    uint4 lv[2][R];
+    v4i id[2][4];
+    lev_load(lv[0], 0);
+    id_load(id[0], 0);
+    __syncthreads();
+    // one block of 32 features; TAIL: features past F take the zero row
+    auto block = [&](int f0, auto tail) {
+        constexpr bool TAIL = decltype(tail)::value;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {                      // groups of four features
+            if (q % 2 == 0)
+                lev_load(lv[(q / 2 + 1) & 1], f0 + 4 * q + 8);
+            id_load(id[(q + 1) & 1], f0 + 4 * q + 4);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const uint4 &l4 = lv[(q / 2) & 1][r];
+                v4i a[4];
+#pragma unroll
+                for (int u = 0; u < 4; u += 2) {
+                    const uint32_t p0 = q % 2 ? (u ? l4.w : l4.z) : (u ? l4.y : l4.x);
+                    uint32_t pr = __builtin_bit_cast(
+                        uint32_t, __builtin_elementwise_min(__builtin_bit_cast(v2us, p0), __builtin_bit_cast(v2us, lmax)));
+                    if constexpr (TAIL) {
+                        const int f = f0 + 4 * q + u;
+                        if (f >= F)
+                            pr = (uint32_t)L * 0x10001u;
+                        else if (f + 1 >= F)
+                            pr = (pr & 0xffffu) | ((uint32_t)L << 16);
+                    }
+                    a[u] = *(const lds_v4i *)(uintptr_t)lid_addr<false>(pr, S::PITCH, lbase);
+                    a[u + 1] = *(const lds_v4i *)(uintptr_t)lid_addr<true>(pr, S::PITCH, lbase);
                 }
+                cnt[r].add4(q, a, id[q & 1]);
             }
         }
-    }
-    __syncthreads();
+    };
+    int f0 = 0;
+    for (; f0 + kLidFeat <= F; f0 += kLidFeat)
+        block(f0, std::integral_constant<bool, false>{});
+    if (f0 < F)
+        block(f0, std::integral_constant<bool, true>{});
 
-    const int wi = t % kLidWords;
-    if (wi >= nw)
-        return;
-    const lds_u64 *sidw = sid + wi;
-    const lds_u64 *slvw = slv + wi;
-    const int wg = w0 + wi;
-    const uint64_t tail_mask = (wg == W - 1 && (D & 63)) ? (1ull << (D & 63)) - 1ull : ~0ull;
-    for (int pass = 0; pass < kLidPasses; ++pass) {
-        const int64_t row = ((int64_t)blockIdx.y * kLidPasses + pass) * kLidRows + t / kLidWords;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t row = row0 + r * S::RPW;
         if (row >= n)
-            break;
-        H[row * ldh + wg] = level_id_word(lev + row * ldl, F, L, sidw, slvw) & tail_mask;
+            continue;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int w = w0 + 2 * wl + i;
+            if (w >= W)
+                continue;
+            uint64_t v = (uint64_t)cnt[r].greater(2 * i, (uint32_t)F >> 1) |
+                         ((uint64_t)cnt[r].greater(2 * i + 1, (uint32_t)F >> 1) << 32);
+            if (w == W - 1 && (D & 63))
+                v &= (1ull << (D & 63)) - 1ull;
+            H[row * ldh + w] = v;
+        }
     }
 }
 
-hipError_t launch_level_id(const uint16_t *lev, int64_t n, int F, int64_t ldl, const uint64_t *ID, int64_t ldid,
-                           const uint64_t *LV, int L, int64_t ldlv, int D, uint64_t *H, int64_t ldh, hipStream_t st)
+template <int LPR, int R>
+static hipError_t launch_level_id_rows(const uint16_t *lev, int64_t n, int F, int64_t ldl, const uint64_t *ID,
+                                       int64_t ldid, const uint64_t *LV, int L, int64_t ldlv, int D, uint64_t *H,
+                                       int64_t ldh, hipStream_t st)
 {
-    const size_t lds = lid_lds_bytes(F, L);
-    // once per process (thread-safe static initialisation)
-    static const hipError_t attr = hipFuncSetAttribute((const void *)k_level_id,
+    typedef LidShape<LPR, R> S;
+    // once per process and shape (thread-safe static initialisation)
+    static const hipError_t attr = hipFuncSetAttribute((const void *)k_level_id<LPR, R>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess)
         return attr;
     const int W = (D + 63) / 64;
-    const int64_t rows_per_wg = (int64_t)kLidRows * kLidPasses;
-    const dim3 grid((unsigned)((W + kLidWords - 1) / kLidWords), (unsigned)((n + rows_per_wg - 1) / rows_per_wg));
-    hipLaunchKernelGGL(k_level_id, grid, dim3(256), lds, st, lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh);
+    const dim3 grid((unsigned)((n + S::ROWS - 1) / S::ROWS), (unsigned)((W + S::W - 1) / S::W));
+    hipLaunchKernelGGL((k_level_id<LPR, R>), grid, dim3(256), S::lds(L), st, lev, n, F, ldl, ID, ldid, LV, L, ldlv, D,
+                       H, ldh);
     return hipGetLastError();
+}
+
+// Two rows per lane (each identity word read serves both, two waves per SIMD)
+// once they make four rounds of the device's 512 workgroups; below, one row
+// and three waves per SIMD fill the last rounds better (5555 rows x 389
+// features, 5450 dimensions: 110 us with two rows, 100 with one; 32768 x 617,
+// 10240: 889 and 984).
+template <int LPR>
+static hipError_t launch_level_id_shape(const uint16_t *lev, int64_t n, int F, int64_t ldl, const uint64_t *ID,
+                                        int64_t ldid, const uint64_t *LV, int L, int64_t ldlv, int D, uint64_t *H,
+                                        int64_t ldh, hipStream_t st)
+{
+    typedef LidShape<LPR, 2> S;
+    const int W = (D + 63) / 64;
+    if ((n + S::ROWS - 1) / S::ROWS * ((W + S::W - 1) / S::W) >= 2048)
+        return launch_level_id_rows<LPR, 2>(lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
+    return launch_level_id_rows<LPR, 1>(lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
+}
+
+// Windows of 32, 16 or 8 words: the widest whose level rows leave room for
+// two workgroups per CU (up to 319, 567 levels; 8 words beyond) and
+// whose last window is not mostly empty (an idle lane costs as much as a busy
+// one).
+hipError_t launch_level_id(const uint16_t *lev, int64_t n, int F, int64_t ldl, const uint64_t *ID, int64_t ldid,
+                           const uint64_t *LV, int L, int64_t ldlv, int D, uint64_t *H, int64_t ldh, hipStream_t st)
+{
+    const int W = (D + 63) / 64;
+    auto padded = [&](int w) { return (W + w - 1) / w * w; };
+    const size_t half = 80 * 1024;
+    int w = 8;
+    if (LidShape<8, 2>::lds(L) <= half && padded(16) * 8 <= padded(8) * 9)
+        w = 16;
+    if (LidShape<16, 2>::lds(L) <= half && padded(32) * 8 <= padded(w) * 9)
+        w = 32;
+    if (w == 32)
+        return launch_level_id_shape<16>(lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
+    if (w == 16)
+        return launch_level_id_shape<8>(lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
+    return launch_level_id_shape<4>(lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
 }
 
 }  // namespace hdc
