@@ -32,7 +32,8 @@ FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE,
 # Per-source additions.  The int8-feature encoder keeps its MFMA accumulators
 # in ordinary VGPRs, so the epilogue that reads them between the next tile's
 # MFMAs needs no accumulator-register moves.
-FILE_FLAGS = {"hdc_encode_i8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+FILE_FLAGS = {"hdc_encode_i8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+              "hdc_adc.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str) -> str:

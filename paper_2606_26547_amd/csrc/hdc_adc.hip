@@ -178,12 +178,104 @@ hipError_t launch_adc_prepare(const uint64_t *C, int K, int64_t ldc, int start, 
     const int64_t total = (int64_t)L.nwin * kHmWin * L.KT * 64;
     // E2M1 +1.0 / -1.0
     hipLaunchKernelGGL((k_sign_table<0x2u, 0xAu>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, C, K,
-                       ldc, start, end, stride, L.w_lo, L.KT, total, (int8_t *)ws);
+                       ldc, start, end, stride, L.w_lo, L.KT, total, (int8_t *)ws, (int32_t *)nullptr);
     const int nchunk = L.nwin * (kHmWin / 2);
     hipLaunchKernelGGL(k_adc_chunks, dim3((unsigned)((nchunk + 255) / 256)), dim3(256), 0, st, start, end, stride,
                        L.w_lo / 2, nchunk, (int32_t *)(ws + L.off_nc));
     return hipGetLastError();
 }
+
+// The converter.  A table read per partial kept LDS busy (16 reads of 64
+// scattered words per chunk and tile), so partials go through packed
+// half-precision arithmetic where that gives the table's value for every one
+// of the 257 partials (checked by each workgroup, entry by entry; else the
+// table is read): with code = round((x - floor) / step) of the clipped partial
+// x, at most cmax,
+//     t = clamp(s * k + c, 0, 1),   1024 + code = t * r + 1024 (rounded to the
+// integer by the addition), r = min((ceil - floor) / step, 2^res - 1), two
+// partials per operation, four operations.  The 16-bit patterns 0x6400 + code
+// are summed as integers for up to kAdcFlush chunks (1023 * 64 < 2^16) and
+// then added to the 32-bit code sums; score = floor * chunks + step * codes.
+constexpr int kAdcFlush = 64;
+constexpr int64_t kAdcFewQueries = 16384;   // (see few_pairs)
+struct AdcConv {
+    uint32_t k, c, r;            // each a packed pair of one half
+    static __device__ __forceinline__ uint32_t pair(float x)
+    {
+        typedef __fp16 h2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, h2{(__fp16)x, (__fp16)x});
+    }
+    __device__ __forceinline__ AdcConv(int res, int step, int floor_, int ceil_)
+    {
+        const float top = (float)((1ll << res) - 1);
+        float range = (float)((int64_t)ceil_ - floor_) / (float)step;
+        range = range < top ? range : top;
+        range = range > 0.0f ? range : 1.0f;
+        const float inv = 1.0f / ((float)step * range);
+        k = pair(inv);
+        c = pair((0.25f - (float)floor_) * inv);   // a quarter step up: ties round up
+        r = pair(range);
+    }
+    // bits of 1024 + code (halves) of two partials
+    __device__ __forceinline__ uint32_t operator()(float a, float b) const
+    {
+        const uint32_t s = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a, b));
+        uint32_t t, m;
+        asm("v_pk_fma_f16 %0, %1, %2, %3 clamp" : "=v"(t) : "v"(s), "v"(k), "v"(c));
+        asm("v_pk_fma_f16 %0, %1, %2, %3" : "=v"(m) : "v"(t), "v"(r), "v"(0x64006400u));
+        return m;
+    }
+};
+
+// Fills the table with the value of every partial s in [-128, 128]; returns
+// whether the arithmetic gives all of them (a workgroup barrier).
+__device__ __forceinline__ bool adc_table(int *lut, int t, const AdcConv &conv, int res, int step, int floor_,
+                                          int ceil_)
+{
+    int ok = 1;
+    for (int i = t; i < 257; i += 256) {
+        const int s = i - 128;
+        const int64_t x = s < floor_ ? floor_ : (s > ceil_ ? ceil_ : s);
+        int64_t code = (2 * (x - floor_) + step) / (2 * (int64_t)step);
+        const int64_t top = (1ll << res) - 1;
+        if (code > top)
+            code = top;
+        lut[i] = (int)(floor_ + step * code);
+        ok &= code < 1024 && conv((float)s, (float)s) == 0x64006400u + (uint32_t)code * 0x10001u;
+    }
+    return __syncthreads_and(ok);
+}
+
+// The code sums of one tile: 16 partials per lane in packed halves, moved to
+// 32 bits every kAdcFlush chunks.
+struct AdcCodes {
+    uint32_t h[8];
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            h[i] = 0;
+    }
+    __device__ __forceinline__ void add(const AdcConv &conv, const v16f &part)
+    {
+        typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            h[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(v2us, h[i]) +
+                                                    __builtin_bit_cast(v2us, conv(part[2 * i], part[2 * i + 1])));
+    }
+    // chunks: those added since the last call
+    __device__ __forceinline__ void flush(v16i &sum, int chunks)
+    {
+        const uint32_t base = (uint32_t)chunks * 0x6400u;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            sum[2 * i] += (int)((h[i] - base) & 0xffffu);
+            sum[2 * i + 1] += (int)(((h[i] >> 16) - base) & 0xffffu);
+            h[i] = 0;
+        }
+    }
+};
 
 template <int KT>
 __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K,
@@ -201,16 +293,8 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
     const int64_t rbase = (int64_t)blockIdx.x * ROWS;
     const uint64_t *Qwg = Q + rbase * ldq;
 
-    for (int i = t; i < 257; i += 256) {   // value of every partial s in [-128, 128]
-        const int s = i - 128;
-        const int64_t x = s < floor_ ? floor_ : (s > ceil_ ? ceil_ : s);
-        int64_t code = (2 * (x - floor_) + step) / (2 * (int64_t)step);
-        const int64_t top = (1ll << res) - 1;
-        if (code > top)
-            code = top;
-        lut[i] = (int)(floor_ + step * code);
-    }
-    __syncthreads();
+    const AdcConv conv(res, step, floor_, ceil_);
+    const bool arith = adc_table(lut, t, conv, res, step, floor_, ceil_);
 
     int qrow[S::NQL], qhalf[S::NQL];
 #pragma unroll
@@ -246,15 +330,43 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt)
             sc[kt][qt] = v16i{};
+    AdcCodes codes[KT][QT];
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+            codes[kt][qt].clear();
+    int pending = 0, chunks = 0;   // chunks in codes, and converted in all
+    auto flush = [&]() {
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt)
+                codes[kt][qt].flush(sc[kt][qt], pending);
+        pending = 0;
+    };
 
 #pragma unroll
     for (int v = 0; v < NST - 1; ++v)
         issue(v, v);
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(G * (NST - 2)) : "memory");
 
+    // whether each chunk of the window is converted, read a window ahead (a
+    // scalar load per chunk, waited for on the spot, held up the whole wave)
+    bool conv_now[W / 2], conv_next[W / 2];
+    auto read_nc = [&](int v) {
+#pragma unroll
+        for (int cc = 0; cc < W / 2; ++cc)
+            conv_next[cc] = nc[(v < nwin ? v : nwin - 1) * (W / 2) + cc] != 0;
+    };
+    read_nc(0);
     int st = 0;
     for (int v = 0; v < nwin; ++v) {
         issue(v + NST - 1, st == 0 ? NST - 1 : st - 1);
+#pragma unroll
+        for (int cc = 0; cc < W / 2; ++cc)
+            conv_now[cc] = conv_next[cc];
+        read_nc(v + 1);
         const lds_u8 *sq = L + st * S::SB;
         const lds_u8 *stb = sq + S::QB;
         v4i qv[QT][S::U];
@@ -267,8 +379,10 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
         }
 #pragma unroll
         for (int cc = 0; cc < W / 2; ++cc) {
-            if (nc[v * (W / 2) + cc] == 0)   // uniform: not converted
+            if (!conv_now[cc])   // uniform: not converted
                 continue;
+            ++pending;
+            ++chunks;
             v8i af[2][KT];
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -277,6 +391,9 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
                     const v4i a4 = *(const lds_v4i *)(stb + (((2 * cc + h) * KT + kt) * 64 + lane) * 16);
                     af[h][kt] = v8i{a4[0], a4[1], a4[2], a4[3], 0, 0, 0, 0};
                 }
+            // every tile's products first: a tile's conversion runs while the
+            // next ones' products are on the matrix cores
+            v16f part[QT][KT];
 #pragma unroll
             for (int qt = 0; qt < QT; ++qt) {
                 const v4i u = qv[qt][cc];   // the chunk's two words: dwords 0-1 and 2-3
@@ -284,19 +401,37 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
                 const v8i b1 = query_bipolar((uint32_t)(g ? u[3] : u[2]));
 #pragma unroll
                 for (int kt = 0; kt < KT; ++kt) {
-                    v16f part = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[0][kt], b0, v16f{}, 4, 4, 0, 0,
-                                                                                0, 0);
-                    part = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[1][kt], b1, part, 4, 4, 0, 0, 0, 0);
-#pragma unroll
-                    for (int e = 0; e < 16; ++e)
-                        sc[kt][qt][e] += lut[(int)part[e] + 128];
+                    part[qt][kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[0][kt], b0, v16f{}, 4, 4, 0, 0,
+                                                                                   0, 0);
+                    part[qt][kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[1][kt], b1, part[qt][kt], 4, 4,
+                                                                                   0, 0, 0, 0);
                 }
             }
+            if (arith) {
+#pragma unroll
+                for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+                    for (int kt = 0; kt < KT; ++kt)
+                        codes[kt][qt].add(conv, part[qt][kt]);
+            } else {
+#pragma unroll
+                for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+                    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e)
+                            sc[kt][qt][e] += lut[(int)part[qt][kt][e] + 128];
+            }
         }
+        if (arith && pending > kAdcFlush - W / 2)
+            flush();
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(G * (NST - 2)) : "memory");
         st = st == NST - 1 ? 0 : st + 1;
     }
     __builtin_amdgcn_s_waitcnt(0);
+    const int mul = arith ? step : 1, add = arith ? floor_ * chunks : 0;   // codes to values
+    if (arith)
+        flush();
 
     // argmax: lane holds query l%32 of each tile and classes 8(v/4)+4g+v%4
 #pragma unroll
@@ -309,7 +444,7 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
             for (int e = 0; e < 16; ++e) {
                 const int k = kt * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
                 if (k < K) {
-                    const int val = sc[kt][qt][e];
+                    const int val = sc[kt][qt][e] * mul + add;
                     if (val > best) { best = val; bk = k; }
                     if (scores && q < n)
                         scores[q * K + k] = val;
@@ -325,6 +460,101 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
     }
 }
 
+// The same for few queries (see few_pairs): a pair of words is a chunk; the
+// pairs a block lacks fall on chunk slots that are not converted.
+template <int KT>
+__global__ __launch_bounds__(256) void k_adc_few(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K,
+                                                 int w_lo, int w_hi, const int8_t *__restrict__ tab,
+                                                 const int32_t *__restrict__ nc, int res, int step, int floor_,
+                                                 int ceil_, int32_t *__restrict__ label,
+                                                 int32_t *__restrict__ max_score, int32_t *__restrict__ scores)
+{
+    __shared__ int32_t sums[kWaves][KT * 32][33];
+    __shared__ int lut[257];
+    __shared__ int best[8][32], bestk[8][32];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 5;
+    const AdcConv conv(res, step, floor_, ceil_);
+    const bool arith = adc_table(lut, t, conv, res, step, floor_, ceil_);
+    v16i sc[KT];
+    AdcCodes codes[KT];
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+        sc[kt] = v16i{};
+        codes[kt].clear();
+    }
+    int pending = 0, chunks = 0;   // chunks in codes, and converted by this wave
+    auto flush = [&]() {
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+            codes[kt].flush(sc[kt], pending);
+        pending = 0;
+    };
+    few_pairs(Q, n, ldq, w_lo, w_hi, [&](int p, int p1, const v4i (&u)[kFewPairs]) {
+#pragma unroll
+        for (int i = 0; i < kFewPairs; ++i) {
+            if (p + i >= p1 || nc[p + i] == 0)   // uniform: not converted
+                continue;
+            ++pending;
+            ++chunks;
+            const v8i b0 = query_bipolar((uint32_t)(g ? u[i][1] : u[i][0]));
+            const v8i b1 = query_bipolar((uint32_t)(g ? u[i][3] : u[i][2]));
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt) {
+                const int8_t *e = tab + ((int64_t)(2 * (p + i)) * KT + kt) * 1024 + lane * 16;
+                const v4i a0 = *(const v4i *)e, a1 = *(const v4i *)(e + KT * 1024);
+                v16f part = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                    v8i{a0[0], a0[1], a0[2], a0[3], 0, 0, 0, 0}, b0, v16f{}, 4, 4, 0, 0, 0, 0);
+                part = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(v8i{a1[0], a1[1], a1[2], a1[3], 0, 0, 0, 0}, b1,
+                                                                       part, 4, 4, 0, 0, 0, 0);
+                if (arith) {
+                    codes[kt].add(conv, part);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        sc[kt][v] += lut[(int)part[v] + 128];
+                }
+            }
+        }
+        if (arith && pending > kAdcFlush - kFewPairs)
+            flush();
+    });
+    const int mul = arith ? step : 1, add = arith ? floor_ * chunks : 0;   // codes to values
+    if (arith)
+        flush();
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            sums[wave][kt * 32 + 8 * (v >> 2) + 4 * g + (v & 3)][lane & 31] = sc[kt][v] * mul + add;
+    __syncthreads();
+    const int c = t & 31, slot = t >> 5;
+    const int64_t q = (int64_t)blockIdx.x * 32 + c;
+    int b = INT_MIN, bk = INT_MAX;
+    for (int k = slot; k < K; k += 8) {
+        const int v = sums[0][k][c] + sums[1][k][c] + sums[2][k][c] + sums[3][k][c];
+        if (scores && q < n)
+            scores[q * K + k] = v;
+        if (bk == INT_MAX || v > b) {
+            b = v;
+            bk = k;
+        }
+    }
+    best[slot][c] = b;
+    bestk[slot][c] = bk;
+    __syncthreads();
+    if (t < 32 && q < n) {
+#pragma unroll
+        for (int s = 1; s < 8; ++s)
+            if (bestk[s][c] != INT_MAX && (best[s][c] > b || (best[s][c] == b && bestk[s][c] < bk))) {
+                b = best[s][c];
+                bk = bestk[s][c];
+            }
+        label[q] = bk;
+        if (max_score)
+            max_score[q] = b;
+    }
+}
+
 hipError_t launch_adc_prepared(const uint64_t *Q, int64_t n, int64_t ldq, int K, int start, int end, int res,
                                int step, int floor_, int ceil_, const uint8_t *ws, int32_t *label,
                                int32_t *max_score, int32_t *scores, hipStream_t st)
@@ -333,6 +563,11 @@ hipError_t launch_adc_prepared(const uint64_t *Q, int64_t n, int64_t ldq, int K,
     const int8_t *tab = (const int8_t *)ws;
     const int32_t *nc = (const int32_t *)(ws + L.off_nc);
 #define HDC_ADCP_CASE(KT_)                                                                                     \
+    if (L.KT == KT_ && n <= kAdcFewQueries) {                                                                  \
+        hipLaunchKernelGGL(k_adc_few<KT_>, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, Q, n, ldq, K, L.w_lo, \
+                           L.w_hi, tab, nc, res, step, floor_, ceil_, label, max_score, scores);               \
+        return hipGetLastError();                                                                              \
+    }                                                                                                          \
     if (L.KT == KT_) {                                                                                         \
         typedef HmShape<KT_> S;                                                                                \
         constexpr int NW = kHmWin / S::W;                                                                      \

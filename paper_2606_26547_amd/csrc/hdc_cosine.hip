@@ -25,12 +25,25 @@
 // and rinv_k (double) for 128 classes, max |a_kd| over S per class (int32)
 // and the range flag.
 //
+// Accumulators of at most 255 over S (sums of up to 255 training rows) take a
+// faster operand, chosen by _prepare from the classes' largest entries (flag
+// 2): a_kd = 16 * h + l with 4-bit magnitudes of a's sign, as FP6 (E2M3 holds
+// n / 8 for n = 0..15 in the codes 0..15) against the query bits as FP4 (0.5),
+// block scales 2^4 and 2^8, both parts into one fp32 accumulator: every
+// product is an integer and |sum| <= 255 * 65536 < 2^24, so the sums are
+// exact.  Twice the K per instruction at the same cycles, one accumulator
+// instead of two (two query tiles per wave with four class tiles), 3 KiB per
+// word and class tile instead of 4: for word w, [part (l, h)][kt] 64 lanes x
+// 16 bytes, then [part][kt] 64 lanes x 8 bytes, the 192 bits of lane l being
+// 32 codes of class kt*32 + l%32, code i for dimension 64w + 32*(l/32) +
+// 4*(i%8) + i/8 (the order of the query nibbles).
+//
 // Streaming as in the prepared Hamming search: query words and operand
 // windows go from global memory straight into a two-stage LDS ring
 // (global_load_lds), one barrier per window.
 #include <limits.h>
 
-#include "hdc_device.h"
+#include "hdc_stream.h"
 
 namespace hdc {
 
@@ -49,6 +62,8 @@ template <int KT, int QT_ = (KT == 4 ? 1 : 2), int NST_ = (KT == 1 ? 3 : 2)> str
 };
 constexpr int kCosWin = 8;
 constexpr int kCosMaxAcc = 32639;   // |a| bound of the two-byte split
+constexpr int kCosMaxF6 = 255;      // of the two FP6 digits
+enum CosFlag : int32_t { COS_OUT_OF_RANGE = 0, COS_I8 = 1, COS_F6 = 2 };
 
 struct CosLayout {
     int w_lo, w_hi, nwin, KT;
@@ -74,13 +89,51 @@ __device__ __forceinline__ bool in_set(int64_t d, int start, int end, int stride
     return d >= start && d < end && (d - start) % stride == 0;
 }
 
+// The FP6 operand of (word, class tile, lane, part): index idx counts the
+// entries of both formats' tables (four per word, tile and lane); here two of
+// the four write.
+__device__ __forceinline__ void f6_entry(const int32_t *__restrict__ acc, int K, int64_t lda, int start, int end,
+                                         int stride, int w_lo, int KT, int64_t idx, int8_t *__restrict__ tab)
+{
+    const int lane = (int)(idx & 63);
+    const int kt = (int)((idx >> 6) % KT);
+    const int64_t whp = (idx >> 6) / KT;
+    const int part = (int)(whp & 1);
+    if (whp & 2)
+        return;
+    const int64_t wi = whp >> 2, w = w_lo + wi;
+    const int k = kt * 32 + (lane & 31), g = lane >> 5;
+    uint32_t o[6] = {0, 0, 0, 0, 0, 0};
+    if (k < K) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+            const int64_t d = w * 64 + 32 * g + 4 * (i & 7) + (i >> 3);
+            if (in_set(d, start, end, stride)) {
+                const int a = acc[k * lda + d], m = a < 0 ? -a : a;
+                const uint32_t c = (uint32_t)(part ? m >> 4 : m & 15) | (a < 0 ? 0x20u : 0u);
+                const int bit = 6 * i;
+                o[bit >> 5] |= c << (bit & 31);
+                if ((bit & 31) > 26)
+                    o[(bit >> 5) + 1] |= c >> (32 - (bit & 31));
+            }
+        }
+    }
+    int8_t *word = tab + wi * (3072 * KT);
+    *(uint4 *)(word + (part * KT + kt) * 1024 + lane * 16) = make_uint4(o[0], o[1], o[2], o[3]);
+    *(uint2 *)(word + 2048 * KT + (part * KT + kt) * 512 + lane * 8) = make_uint2(o[4], o[5]);
+}
+
 __global__ __launch_bounds__(256) void k_cos_table(const int32_t *__restrict__ acc, int K, int64_t lda, int start,
                                                    int end, int stride, int w_lo, int KT, int64_t total,
-                                                   int8_t *__restrict__ tab)
+                                                   const int32_t *__restrict__ flag, int8_t *__restrict__ tab)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= total)
         return;
+    if (flag[0] == COS_F6) {
+        f6_entry(acc, K, lda, start, end, stride, w_lo, KT, idx, tab);
+        return;
+    }
     const int lane = (int)(idx & 63);
     const int kt = (int)((idx >> 6) % KT);
     const int64_t whp = (idx >> 6) / KT;   // (word * 2 + half) * 2 + part
@@ -141,15 +194,17 @@ __global__ __launch_bounds__(256) void k_cos_norms(const int32_t *__restrict__ a
 
 __global__ __launch_bounds__(128) void k_cos_flag(const int32_t *__restrict__ amax, int32_t *__restrict__ flag)
 {
-    __shared__ int bad;
+    __shared__ int bad, wide;
     if (threadIdx.x == 0)
-        bad = 0;
+        bad = wide = 0;
     __syncthreads();
     if (amax[threadIdx.x] > kCosMaxAcc)
         atomicOr(&bad, 1);
+    if (amax[threadIdx.x] > kCosMaxF6)
+        atomicOr(&wide, 1);
     __syncthreads();
     if (threadIdx.x == 0)
-        flag[0] = bad ? 0 : 1;
+        flag[0] = bad ? COS_OUT_OF_RANGE : wide ? COS_I8 : COS_F6;
 }
 
 // Query bits as bytes {0, 1}: register r of lane half g holds, in byte i,
@@ -171,6 +226,8 @@ __global__ __launch_bounds__(256) void k_cosine_mfma(const uint64_t *__restrict_
                                                      const int32_t *__restrict__ flag, int32_t *__restrict__ label, double *__restrict__ max_score,
                                                      double *__restrict__ scores)
 {
+    if (flag[0] == COS_F6)   // the other operand: k_cosine_f6's search
+        return;
     typedef CosShape<KT, QT_, NST_> S;
     constexpr int QT = S::QT, W = S::W, NST = S::NST;
     constexpr int G = S::NQL + S::NTL;                 // loads per window and wave
@@ -297,17 +354,277 @@ __global__ __launch_bounds__(256) void k_cosine_mfma(const uint64_t *__restrict_
     }
 }
 
+// The search on the FP6 operand (flag 2).  Two workgroups per CU: one's LDS
+// waits and barriers under the other's MFMAs.
+template <int KT> struct F6Shape {
+    static constexpr int QT = 2;
+    static constexpr int W = KT == 4 ? 2 : 4;          // words per window (divides kCosWin)
+    static constexpr int U = W / 2;                    // 16-byte units per query row
+    static constexpr int RPL = 64 / U;                 // query rows per 1 KiB load
+    static constexpr int ROWS = kWaves * QT * 32;      // queries per workgroup
+    static constexpr int QB = ROWS * W * 8;            // query bytes per stage
+    static constexpr int WB = 3072 * KT;               // operand bytes per word
+    static constexpr int TB = W * WB;
+    static constexpr int NST = 2;
+    static constexpr int NQL = QB / 1024 / kWaves;
+    static constexpr int NTL = TB / 1024 / kWaves;
+    static constexpr int SB = QB + TB;
+    // unit hh of row r sits in slot hh ^ (r / 8 % U): 16 rows' reads on
+    // distinct banks
+    static __device__ __forceinline__ int slot(int r, int hh) { return hh ^ ((r >> 3) & (U - 1)); }
+};
+
+template <int KT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void k_cosine_f6(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K, int w_lo, int w_hi, int nwin,
+                 const int8_t *__restrict__ tab, const int64_t *__restrict__ T, const double *__restrict__ rinv,
+                 const int32_t *__restrict__ flag, int32_t *__restrict__ label, double *__restrict__ max_score,
+                 double *__restrict__ scores)
+{
+    if (flag[0] != COS_F6)
+        return;
+    typedef F6Shape<KT> S;
+    constexpr int QT = S::QT, W = S::W, NST = S::NST, G = S::NQL + S::NTL;
+    __shared__ __align__(16) uint8_t smem[NST * S::SB];
+    lds_u8 *L = (lds_u8 *)smem;
+    const int lane = threadIdx.x & 63, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t rbase = (int64_t)blockIdx.x * S::ROWS;
+    const uint64_t *Qwg = Q + rbase * ldq;
+
+    // query loads: load i of a wave fills rows RPL*j .. (j = i*4 + wave);
+    // rows past n re-read row n-1, words past w_hi the first pair
+    uint32_t qoff[S::NQL];
+    int qunit[S::NQL];
+#pragma unroll
+    for (int i = 0; i < S::NQL; ++i) {
+        const int r = S::RPL * (i * kWaves + wave) + lane / S::U;
+        qunit[i] = 2 * S::slot(r, lane % S::U);
+        qoff[i] = (uint32_t)((rbase + r < n ? r : n - 1 - rbase) * ldq * 8);
+    }
+    auto issue = [&](int v, int st) {
+        const int vc = v < nwin ? v : nwin - 1;
+        lds_u8 *sq = L + st * S::SB;
+#pragma unroll
+        for (int i = 0; i < S::NQL; ++i) {
+            const int w = w_lo + vc * W + qunit[i];
+            lds_dma16(Qwg, qoff[i] + 8u * (uint32_t)(w < w_hi ? w : w_lo), sq + (i * kWaves + wave) * 1024);
+        }
+#pragma unroll
+        for (int i = 0; i < S::NTL; ++i)
+            lds_dma16(tab + (int64_t)vc * S::TB + (i * kWaves + wave) * 1024, (uint32_t)lane * 16,
+                      sq + S::QB + (i * kWaves + wave) * 1024);
+    };
+
+    v16f acc[KT][QT];
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+            acc[kt][qt] = v16f{};
+    issue(0, 0);
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    int st = 0;
+    for (int v = 0; v < nwin; ++v) {
+        issue(v + 1, st ^ 1);
+        const lds_u8 *sq = L + st * S::SB;
+        const lds_u8 *stb = sq + S::QB;
+        v4i qv[QT][S::U];
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) {
+            const int r = (wave * QT + qt) * 32 + (lane & 31);
+#pragma unroll
+            for (int hh = 0; hh < S::U; ++hh)
+                qv[qt][hh] = *(const lds_v4i *)(sq + r * (W * 8) + 16 * S::slot(r, hh));
+        }
+#pragma unroll
+        for (int ww = 0; ww < W; ++ww) {
+            v8i bf[QT];
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt) {
+                const v4i u = qv[qt][ww >> 1];
+                bf[qt] = query_nibbles((uint32_t)(g ? u[2 * (ww & 1) + 1] : u[2 * (ww & 1)]));
+            }
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                for (int part = 0; part < 2; ++part) {
+                    typedef int v2i __attribute__((ext_vector_type(2)));
+                    const lds_u8 *e = stb + ww * S::WB;
+                    const v4i lo = *(const lds_v4i *)(e + (part * KT + kt) * 1024 + lane * 16);
+                    const v2i hi = *(const HDC_LDS v2i *)(e + 2048 * KT + (part * KT + kt) * 512 + lane * 8);
+                    const v8i af = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], 0, 0};
+                    // A: E2M3 (format 2) scaled by 2^4 or 2^8, B: E2M1 (4)
+#pragma unroll
+                    for (int qt = 0; qt < QT; ++qt)
+                        acc[kt][qt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                            af, bf[qt], acc[kt][qt], 2, 4, 0, part ? 127 + 8 : 127 + 4, 0, 127);
+                }
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        st ^= 1;
+    }
+
+    // argmax: lane holds query l%32 of each tile and classes 8(v/4)+4g+v%4
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+        const int64_t q = rbase + (wave * QT + qt) * 32 + (lane & 31);
+        double best = -1.0 / 0.0;
+        int bk = 0;
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int k = kt * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+                if (k < K) {
+                    const long long sum = (long long)(int)acc[kt][qt][v];
+                    const double sc = __dmul_rn((double)(T[k] - 2 * sum), rinv[k]);
+                    if (sc > best) { best = sc; bk = k; }
+                    if (scores && q < n)
+                        scores[q * K + k] = sc;
+                }
+            }
+        const double ob = __shfl_xor(best, 32);
+        const int obk = __shfl_xor(bk, 32);
+        if (ob > best || (ob == best && obk < bk)) { best = ob; bk = obk; }
+        if (g == 0 && q < n) {
+            label[q] = bk;
+            if (max_score)
+                max_score[q] = best;
+        }
+    }
+}
+
+// The search of few queries (see few_pairs) on either operand: one kernel, the
+// sums of the int8 parts taken as 256 * hi + lo.
+template <int KT>
+__global__ __launch_bounds__(256) void k_cosine_few(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K,
+                                                    int w_lo, int w_hi, const int8_t *__restrict__ tab,
+                                                    const int64_t *__restrict__ T, const double *__restrict__ rinv,
+                                                    const int32_t *__restrict__ flag, int32_t *__restrict__ label,
+                                                    double *__restrict__ max_score, double *__restrict__ scores)
+{
+    __shared__ long long sums[KT * 32][33];
+    __shared__ double best[8][32];
+    __shared__ int bestk[8][32];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 5;
+    const int fl = flag[0];
+    long long s[KT][16];
+    if (fl == COS_F6) {
+        v16f acc[KT];
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+            acc[kt] = v16f{};
+        few_pairs(Q, n, ldq, w_lo, w_hi, [&](int p, int p1, const v4i (&u)[kFewPairs]) {
+#pragma unroll
+            for (int i = 0; i < kFewPairs; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    typedef int v2i __attribute__((ext_vector_type(2)));
+                    const int w = 2 * (p + i < p1 ? p + i : p1 - 1) + h;
+                    const int8_t *e = tab + (int64_t)w * (3072 * KT);
+                    const v8i bf = query_nibbles((uint32_t)(g ? u[i][2 * h + 1] : u[i][2 * h]));
+#pragma unroll
+                    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                        for (int part = 0; part < 2; ++part) {
+                            const v4i lo = *(const v4i *)(e + (part * KT + kt) * 1024 + lane * 16);
+                            const v2i hi = *(const v2i *)(e + 2048 * KT + (part * KT + kt) * 512 + lane * 8);
+                            acc[kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                                v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], 0, 0}, bf, acc[kt], 2, 4, 0,
+                                part ? 127 + 8 : 127 + 4, 0, 127);
+                        }
+                }
+        });
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                s[kt][v] = (long long)(int)acc[kt][v];
+    } else {
+        v16i alo[KT], ahi[KT];
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) {
+            alo[kt] = v16i{};
+            ahi[kt] = v16i{};
+        }
+        few_pairs(Q, n, ldq, w_lo, w_hi, [&](int p, int p1, const v4i (&u)[kFewPairs]) {
+#pragma unroll
+            for (int i = 0; i < kFewPairs; ++i)
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    const int64_t wh = 4 * (int64_t)(p + i < p1 ? p + i : p1 - 1) + h;   // dword of the words
+                    const v4i bf = spread_bits((uint32_t)u[i][h], 4u * (uint32_t)g);
+#pragma unroll
+                    for (int kt = 0; kt < KT; ++kt) {
+                        const v4i lo = *(const v4i *)(tab + (((wh * 2) * KT + kt) * 64 + lane) * 16);
+                        const v4i hi = *(const v4i *)(tab + (((wh * 2 + 1) * KT + kt) * 64 + lane) * 16);
+                        alo[kt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(lo, bf, alo[kt], 0, 0, 0);
+                        ahi[kt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(hi, bf, ahi[kt], 0, 0, 0);
+                    }
+                }
+        });
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                s[kt][v] = 256ll * ahi[kt][v] + alo[kt][v];
+    }
+    // the waves' sums, one after the other
+    for (int w = 0; w < kWaves; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    long long &x = sums[kt * 32 + 8 * (v >> 2) + 4 * g + (v & 3)][lane & 31];
+                    x = w == 0 ? s[kt][v] : x + s[kt][v];
+                }
+        }
+        __syncthreads();
+    }
+    const int c = t & 31, slot = t >> 5;
+    const int64_t q = (int64_t)blockIdx.x * 32 + c;
+    const bool in_range = fl != COS_OUT_OF_RANGE;
+    const double nan = __builtin_nan("");
+    double b = -1.0 / 0.0;
+    int bk = 0;
+    for (int k = slot; k < K; k += 8) {
+        const double sc = in_range ? __dmul_rn((double)(T[k] - 2 * sums[k][c]), rinv[k]) : nan;
+        if (sc > b) {
+            b = sc;
+            bk = k;
+        }
+        if (scores && q < n)
+            scores[q * K + k] = sc;
+    }
+    best[slot][c] = b;
+    bestk[slot][c] = bk;
+    __syncthreads();
+    if (t < 32 && q < n) {
+#pragma unroll
+        for (int w = 1; w < 8; ++w)
+            if (best[w][c] > b || (best[w][c] == b && bestk[w][c] < bk)) {
+                b = best[w][c];
+                bk = bestk[w][c];
+            }
+        label[q] = in_range ? bk : -1;
+        if (max_score)
+            max_score[q] = in_range ? b : nan;
+    }
+}
+
 hipError_t launch_cos_prepare(const int32_t *acc, int K, int64_t lda, int start, int end, int stride, uint8_t *ws,
                               hipStream_t st)
 {
     const CosLayout L(start, end, K);
     const int64_t total = (int64_t)L.nwin * kCosWin * 4 * L.KT * 64;
-    hipLaunchKernelGGL(k_cos_table, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, acc, K, lda, start, end,
-                       stride, L.w_lo, L.KT, total, (int8_t *)ws);
     hipLaunchKernelGGL(k_cos_norms, dim3(128), dim3(256), 0, st, acc, K, lda, start, end, stride,
                        (int64_t *)(ws + L.off_T), (double *)(ws + L.off_rinv), (int32_t *)(ws + L.off_amax));
     hipLaunchKernelGGL(k_cos_flag, dim3(1), dim3(128), 0, st, (const int32_t *)(ws + L.off_amax),
                        (int32_t *)(ws + L.off_flag));
+    hipLaunchKernelGGL(k_cos_table, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, acc, K, lda, start, end,
+                       stride, L.w_lo, L.KT, total, (const int32_t *)(ws + L.off_flag), (int8_t *)ws);
     return hipGetLastError();
 }
 
@@ -320,12 +637,22 @@ hipError_t launch_cos_prepared(const uint64_t *Q, int64_t n, int64_t ldq, int K,
     const double *rinv = (const double *)(ws + L.off_rinv);
     const int32_t *flag = (const int32_t *)(ws + L.off_flag);
 #define HDC_COS_CASE(KT_)                                                                                      \
+    if (L.KT == KT_ && n <= kFewQueries) {                                                                     \
+        hipLaunchKernelGGL(k_cosine_few<KT_>, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, Q, n, ldq, K,   \
+                           L.w_lo, L.w_hi, tab, T, rinv, flag, label, max_score, scores);                      \
+        return hipGetLastError();                                                                              \
+    }                                                                                                          \
     if (L.KT == KT_) {                                                                                         \
         typedef CosShape<KT_> S;                                                                               \
         constexpr int R = S::ROWS, NW = kCosWin / S::W;                                                        \
         hipLaunchKernelGGL((k_cosine_mfma<KT_, S::QT, S::NST>), dim3((unsigned)((n + R - 1) / R)), dim3(256), 0, \
                            st, Q, n, ldq,                                                                      \
                            K, L.w_lo, L.w_hi, L.nwin * NW, tab, T, rinv, flag, label, max_score, scores);            \
+        /* one of the two returns at once, by the operand _prepare chose */                                    \
+        typedef F6Shape<KT_> S6;                                                                               \
+        hipLaunchKernelGGL(k_cosine_f6<KT_>, dim3((unsigned)((n + S6::ROWS - 1) / S6::ROWS)), dim3(256), 0, st, \
+                           Q, n, ldq, K, L.w_lo, L.w_hi, L.nwin * (kCosWin / S6::W), tab, T, rinv, flag, label, \
+                           max_score, scores);                                                                 \
         return hipGetLastError();                                                                              \
     }
     HDC_COS_CASE(1)

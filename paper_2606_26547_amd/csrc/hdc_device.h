@@ -215,4 +215,45 @@ __device__ __forceinline__ uint32_t keep_bytes(uint32_t w, int k0, int F)
     return w & ((1u << (8 * v)) - 1u);
 }
 
+// Dimensions of the set {start + j * stride < end} among d0 .. d0 + 31, as a
+// bit mask.
+__device__ __forceinline__ uint32_t set_mask(int d0, int start, int end, int stride)
+{
+    if (d0 >= end || d0 + 32 <= start)
+        return 0u;
+    if (stride == 1) {
+        const uint32_t lo = d0 < start ? ~0u << (start - d0) : ~0u;
+        const uint32_t hi = end - d0 < 32 ? (1u << (end - d0)) - 1u : ~0u;
+        return lo & hi;
+    }
+    int64_t d = start;
+    if (d0 > start)
+        d += (int64_t)((d0 - start + stride - 1) / stride) * stride;
+    uint32_t m = 0;
+    for (; d < d0 + 32 && d < end; d += stride)
+        m |= 1u << (int)(d - d0);
+    return m;
+}
+
+// popc[k] = number of -1 elements of class k over the set (0 for k >= K), by
+// one workgroup of 256.
+__device__ __forceinline__ void class_popc(const uint64_t *__restrict__ C, int K, int64_t ldc, int start, int end,
+                                           int stride, int k, int32_t *__restrict__ popc)
+{
+    __shared__ int part[256];
+    int s = 0;
+    if (k < K)
+        for (int h = 2 * (start >> 6) + threadIdx.x; 32 * h < end; h += 256)   // dwords
+            s += __popc((uint32_t)(C[k * ldc + (h >> 1)] >> (32 * (h & 1))) & set_mask(32 * h, start, end, stride));
+    part[threadIdx.x] = s;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+        if (threadIdx.x < h)
+            part[threadIdx.x] += part[threadIdx.x + h];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0)
+        popc[k] = part[0];
+}
+
 }  // namespace hdc

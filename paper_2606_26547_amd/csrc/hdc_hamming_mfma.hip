@@ -177,19 +177,75 @@ __global__ __launch_bounds__(256) void k_hamming_mfma(const uint64_t *__restrict
     }
 }
 
+// The same for few queries (see few_pairs): zero query words add nothing.
+template <int KT>
+__global__ __launch_bounds__(256) void k_hamming_few(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K,
+                                                     int w_lo, int w_hi, const int8_t *__restrict__ tab,
+                                                     const int32_t *__restrict__ popc, int32_t *__restrict__ argmin,
+                                                     int32_t *__restrict__ min_dist, int32_t *__restrict__ dists)
+{
+    __shared__ int32_t sums[kWaves][KT * 32][33];
+    __shared__ int best[8][32];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 5;
+    v16f acc[KT];
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+        acc[kt] = v16f{};
+    few_pairs(Q, n, ldq, w_lo, w_hi, [&](int p, int p1, const v4i (&u)[kFewPairs]) {
+#pragma unroll
+        for (int i = 0; i < kFewPairs; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int w = 2 * (p + i < p1 ? p + i : p1 - 1) + h;
+                const v8i bf = query_nibbles((uint32_t)(g ? u[i][2 * h + 1] : u[i][2 * h]));
+#pragma unroll
+                for (int kt = 0; kt < KT; ++kt) {
+                    const v4i a = *(const v4i *)(tab + ((int64_t)w * KT + kt) * 1024 + lane * 16);
+                    acc[kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                        v8i{a[0], a[1], a[2], a[3], 0, 0, 0, 0}, bf, acc[kt], 4, 4, 0, 0, 0, 0);
+                }
+            }
+    });
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            sums[wave][kt * 32 + 8 * (v >> 2) + 4 * g + (v & 3)][lane & 31] = (int)acc[kt][v];
+    __syncthreads();
+    // thread (slot, query): classes slot, slot + 8, ..; the minimum of
+    // (distance, class) in one integer is the first minimum
+    const int c = t & 31, slot = t >> 5;
+    const int64_t q = (int64_t)blockIdx.x * 32 + c;
+    int m = INT_MAX;
+    for (int k = slot; k < K; k += 8) {
+        const int d = popc[k] + sums[0][k][c] + sums[1][k][c] + sums[2][k][c] + sums[3][k][c];
+        if (dists && q < n)
+            dists[q * K + k] = d;
+        const int key = d * 128 + k;
+        m = key < m ? key : m;
+    }
+    best[slot][c] = m;
+    __syncthreads();
+    if (t < 32 && q < n) {
+#pragma unroll
+        for (int s = 1; s < 8; ++s)
+            m = best[s][c] < m ? best[s][c] : m;
+        argmin[q] = m % 128;
+        if (min_dist)
+            min_dist[q] = m / 128;
+    }
+}
+
 hipError_t launch_ham_prepare(const uint64_t *C, int K, int64_t ldc, int start, int end, int stride, uint8_t *ws,
                               hipStream_t st)
 {
     const HamLayout L(start, end, K);
     const int64_t total = (int64_t)L.nwin * kHmWin * L.KT * 64;
     // E2M1 +2.0 / -2.0
-    hipLaunchKernelGGL((k_sign_table<0x4u, 0xCu>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, C, K,
-                       ldc, start, end, stride, L.w_lo, L.KT, total, (int8_t *)ws);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    const int nd = (end - start + stride - 1) / stride;
-    return launch_class_popc(C, K, ldc, start, stride, nd, L.KT, (int32_t *)(ws + L.off_popc), st);
+    hipLaunchKernelGGL((k_sign_table<0x4u, 0xCu>), dim3((unsigned)(32 * L.KT + (total + 255) / 256)), dim3(256), 0, st,
+                       C, K, ldc, start, end, stride, L.w_lo, L.KT, total, (int8_t *)ws,
+                       (int32_t *)(ws + L.off_popc));
+    return hipGetLastError();
 }
 
 hipError_t launch_ham_prepared(const uint64_t *Q, int64_t n, int64_t ldq, int K, int start, int end,
@@ -200,6 +256,11 @@ hipError_t launch_ham_prepared(const uint64_t *Q, int64_t n, int64_t ldq, int K,
     const int8_t *tab = (const int8_t *)ws;
     const int32_t *popc = (const int32_t *)(ws + L.off_popc);
 #define HDC_HM_CASE(KT_)                                                                                       \
+    if (L.KT == KT_ && n <= kFewQueries) {                                                                     \
+        hipLaunchKernelGGL(k_hamming_few<KT_>, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, Q, n, ldq, K,  \
+                           L.w_lo, L.w_hi, tab, popc, argmin, min_dist, dists);                                \
+        return hipGetLastError();                                                                              \
+    }                                                                                                          \
     if (L.KT == KT_) {                                                                                         \
         constexpr int R = HmShape<KT_>::ROWS, NW = kHmWin / HmShape<KT_>::W;                                   \
         hipLaunchKernelGGL(k_hamming_mfma<KT_>, dim3((unsigned)((n + R - 1) / R)), dim3(256), 0, st, Q, n, ldq, \

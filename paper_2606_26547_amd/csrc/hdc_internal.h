@@ -169,8 +169,6 @@ bool tile_compiled(int kind, int x_type, int ct, int F, int K, int variant);
 hipError_t launch_encode(const EncodeArgs &a, int compute, int mode, Tile tile, hipStream_t st);
 hipError_t launch_class_table(const uint64_t *C, int K, int64_t ldc, int s0, int stride, int nd,
                               int8_t *tab, int32_t *cpop, hipStream_t st);
-hipError_t launch_class_popc(const uint64_t *C, int K, int64_t ldc, int s0, int stride, int nd, int KT,
-                             int32_t *cpop, hipStream_t st);
 size_t ham_workspace_bytes(int start, int end, int K);
 hipError_t launch_ham_prepare(const uint64_t *C, int K, int64_t ldc, int start, int end, int stride, uint8_t *ws,
                               hipStream_t st);

@@ -23,7 +23,29 @@ __device__ __forceinline__ void class_table_entry(const uint64_t *__restrict__ C
     const int64_t c = (idx >> 6) / KT;
     const int k = kt * 32 + (lane & 31), g = lane >> 5;
     uint32_t out[4] = {0, 0, 0, 0};
-    if (k < K) {
+    if (k < K && stride == 1) {
+        // the chunk's 32 bits from one or two words; byte b of dword e is bit
+        // 8e + 4g + b: 0x01, or 0xff where it is set, 0 past nd
+        const int64_t d = s0 + c * kDimChunk;
+        const int nv = nd - (int)c * kDimChunk;
+        uint32_t bits = 0;
+        if (nv > 0) {
+            const uint64_t *row = C + k * ldc + (d >> 6);
+            const int sh = (int)(d & 63);
+            uint64_t v = row[0] >> sh;
+            if (sh > 32 && 64 - sh < nv)
+                v |= row[1] << (64 - sh);
+            bits = (uint32_t)v;
+        }
+        const uint32_t m = nv >= 32 ? ~0u : nv > 0 ? (1u << nv) - 1u : 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t x = (bits & m) >> (8 * e + 4 * g), y = m >> (8 * e + 4 * g);
+            const uint32_t x4 = (x & 1u) | (x & 2u) << 7 | (x & 4u) << 14 | (x & 8u) << 21;
+            const uint32_t y4 = (y & 1u) | (y & 2u) << 7 | (y & 4u) << 14 | (y & 8u) << 21;
+            out[e] = y4 | x4 * 0xFEu;
+        }
+    } else if (k < K) {
 #pragma unroll
         for (int b = 0; b < 16; ++b) {
             const int64_t dl = c * kDimChunk + 8 * (b >> 2) + 4 * g + (b & 3);
@@ -37,29 +59,6 @@ __device__ __forceinline__ void class_table_entry(const uint64_t *__restrict__ C
     *(uint4 *)(tab + idx * 16) = make_uint4(out[0], out[1], out[2], out[3]);
 }
 
-// popc[k] = number of -1 elements of class k over S (0 for k >= K), one
-// workgroup per class.
-__device__ __forceinline__ void class_popc(const uint64_t *__restrict__ C, int K, int64_t ldc, int s0, int stride,
-                                           int nd, int k, int32_t *__restrict__ popc)
-{
-    __shared__ int part[256];
-    int s = 0;
-    if (k < K)
-        for (int64_t dl = threadIdx.x; dl < nd; dl += 256) {
-            const int64_t d = s0 + dl * stride;
-            s += (int)((C[k * ldc + (d >> 6)] >> (d & 63)) & 1u);
-        }
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if (threadIdx.x < h)
-            part[threadIdx.x] += part[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        popc[k] = part[0];
-}
-
 // The table and the counts in one launch (each is shorter than a launch): the
 // first 32 * KT workgroups count, the rest fill.
 __global__ __launch_bounds__(256) void k_class_operand(const uint64_t *__restrict__ C, int K, int64_t ldc, int s0,
@@ -68,25 +67,12 @@ __global__ __launch_bounds__(256) void k_class_operand(const uint64_t *__restric
 {
     const int nk = 32 * KT;
     if ((int)blockIdx.x < nk) {
-        class_popc(C, K, ldc, s0, stride, nd, (int)blockIdx.x, popc);
+        class_popc(C, K, ldc, s0, s0 + (nd - 1) * stride + 1, stride, (int)blockIdx.x, popc);
         return;
     }
     const int64_t idx = (int64_t)((int)blockIdx.x - nk) * 256 + threadIdx.x;
     if (idx < total)
         class_table_entry(C, K, ldc, s0, stride, nd, KT, idx, tab);
-}
-
-__global__ __launch_bounds__(256) void k_class_popc(const uint64_t *__restrict__ C, int K, int64_t ldc, int s0,
-                                                    int stride, int nd, int32_t *__restrict__ popc)
-{
-    class_popc(C, K, ldc, s0, stride, nd, (int)blockIdx.x, popc);
-}
-
-hipError_t launch_class_popc(const uint64_t *C, int K, int64_t ldc, int s0, int stride, int nd, int KT,
-                             int32_t *cpop, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_class_popc, dim3(KT * 32), dim3(256), 0, st, C, K, ldc, s0, stride, nd, cpop);
-    return hipGetLastError();
 }
 
 hipError_t launch_class_table(const uint64_t *C, int K, int64_t ldc, int s0, int stride, int nd,
