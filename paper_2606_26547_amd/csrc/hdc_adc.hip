@@ -196,8 +196,12 @@ hipError_t launch_adc_prepare(const uint64_t *C, int K, int64_t ldc, int start, 
 // partials per operation, four operations.  The 16-bit patterns 0x6400 + code
 // are summed as integers for up to kAdcFlush chunks (1023 * 64 < 2^16) and
 // then added to the 32-bit code sums; score = floor * chunks + step * codes.
+// 100003 x 4096 against 26 classes, 6 bits: 132 us by the table, 106 so; the
+// conversion's vector operations, four a partial, bound it.
 constexpr int kAdcFlush = 64;
-constexpr int64_t kAdcFewQueries = 16384;   // (see few_pairs)
+// (see few_pairs; 24000 x 10240 against 26 classes: 37 us streaming, 21 so; 16384
+// x 8192 against 100, from where on the few-queries kernel only grows: 45 and 45)
+constexpr int64_t adc_few_queries(int kt) { return kt == 1 ? 32768 : 16384; }
 struct AdcConv {
     uint32_t k, c, r;            // each a packed pair of one half
     static __device__ __forceinline__ uint32_t pair(float x)
@@ -563,7 +567,7 @@ hipError_t launch_adc_prepared(const uint64_t *Q, int64_t n, int64_t ldq, int K,
     const int8_t *tab = (const int8_t *)ws;
     const int32_t *nc = (const int32_t *)(ws + L.off_nc);
 #define HDC_ADCP_CASE(KT_)                                                                                     \
-    if (L.KT == KT_ && n <= kAdcFewQueries) {                                                                  \
+    if (L.KT == KT_ && n <= adc_few_queries(KT_)) {                                                            \
         hipLaunchKernelGGL(k_adc_few<KT_>, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, Q, n, ldq, K, L.w_lo, \
                            L.w_hi, tab, nc, res, step, floor_, ceil_, label, max_score, scores);               \
         return hipGetLastError();                                                                              \

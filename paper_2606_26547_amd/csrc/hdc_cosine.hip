@@ -47,20 +47,32 @@
 
 namespace hdc {
 
-template <int KT, int QT_ = (KT == 4 ? 1 : 2), int NST_ = (KT == 1 ? 3 : 2)> struct CosShape {
-    static constexpr int QT = QT_;
-    static constexpr int W = 4;                        // words per window (divides kCosWin)
+template <int KT, int QT_> struct CosShape {
+    static constexpr int QT = KT == 4 ? 1 : QT_;
+    static constexpr int W = KT == 4 ? 2 : 4;          // words per window (divides kCosWin)
     static constexpr int U = W / 2;                    // 16-byte units per query row
     static constexpr int RPL = 64 / U;                 // query rows per 1 KiB load
     static constexpr int ROWS = kWaves * QT * 32;      // queries per workgroup
     static constexpr int QB = ROWS * W * 8;            // query bytes per stage
     static constexpr int TB = W * 4 * KT * 1024;       // operand bytes per window
-    static constexpr int NST = NST_;
-    static constexpr int NQL = QB / 1024 / kWaves;
+    static constexpr int NST = KT == 1 ? 3 : 2;        // LDS stages
+    // loads per wave (a short last one: its waves past QB load nothing)
+    static constexpr int NQL = (QB / 1024 + kWaves - 1) / kWaves;
     static constexpr int NTL = TB / 1024 / kWaves;
     static constexpr int SB = QB + TB;
+    static_assert(NST == 2 || QB % (1024 * kWaves) == 0, "waits count the loads of a window");
 };
 constexpr int kCosWin = 8;
+// Up to here the workgroups take 128 queries, one tile per wave: at 256 they
+// would be fewer than the CUs (50000 x 8192 against 50 classes: 56 us at 256,
+// 36 here; 25000 x 6208 against 10: 24 and 14).  Past it two tiles share each
+// operand read.
+constexpr int64_t kCosNarrow = 65536;
+// The few-queries kernel (see few_pairs) with four class tiles: its registers
+// leave one workgroup per CU, so past 256 workgroups it takes a second round
+// (16000 x 8192 against 100 int8 classes: 71 us, 66 streaming; 1000: 32 and
+// 62).
+constexpr int64_t cos_few_queries(int kt) { return kt == 4 ? 8192 : kFewQueries; }
 constexpr int kCosMaxAcc = 32639;   // |a| bound of the two-byte split
 constexpr int kCosMaxF6 = 255;      // of the two FP6 digits
 enum CosFlag : int32_t { COS_OUT_OF_RANGE = 0, COS_I8 = 1, COS_F6 = 2 };
@@ -219,23 +231,23 @@ __device__ __forceinline__ v4i spread_bits(uint32_t d, uint32_t sh)
     return b;
 }
 
-template <int KT, int QT_, int NST_>
-__global__ __launch_bounds__(256) void k_cosine_mfma(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K,
-                                                     int w_lo, int w_hi, int nwin, const int8_t *__restrict__ tab,
-                                                     const int64_t *__restrict__ T, const double *__restrict__ rinv,
-                                                     const int32_t *__restrict__ flag, int32_t *__restrict__ label, double *__restrict__ max_score,
-                                                     double *__restrict__ scores)
+// One search on the int8 operand: the workgroup's CosShape ROWS queries from
+// rbase.
+template <int KT, int QT_>
+__device__ __forceinline__ void cosine_i8(uint8_t *smem, int64_t rbase, const uint64_t *__restrict__ Q, int64_t n,
+                                          int64_t ldq, int K, int w_lo, int w_hi, int nwin,
+                                          const int8_t *__restrict__ tab, const int64_t *__restrict__ T,
+                                          const double *__restrict__ rinv, const int32_t *__restrict__ flag,
+                                          int32_t *__restrict__ label, double *__restrict__ max_score,
+                                          double *__restrict__ scores)
 {
-    if (flag[0] == COS_F6)   // the other operand: k_cosine_f6's search
-        return;
-    typedef CosShape<KT, QT_, NST_> S;
+    typedef CosShape<KT, QT_> S;
     constexpr int QT = S::QT, W = S::W, NST = S::NST;
     constexpr int G = S::NQL + S::NTL;                 // loads per window and wave
-    __shared__ __align__(16) uint8_t smem[NST * S::SB];
     lds_u8 *L = (lds_u8 *)smem;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 5;
+    const int lane = threadIdx.x & 63, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t sh = 4u * (uint32_t)g;
-    const int64_t rbase = (int64_t)blockIdx.x * S::ROWS;
     const uint64_t *Qwg = Q + rbase * ldq;
 
     // query loads: load i of a wave fills rows RPL*j .. (j = i*4 + wave),
@@ -260,7 +272,8 @@ __global__ __launch_bounds__(256) void k_cosine_mfma(const uint64_t *__restrict_
             int w = w_lo + vc * W + 2 * qunit[i];
             if (w >= w_hi)
                 w = w_lo;
-            lds_dma16(Qwg, (uint32_t)(((int64_t)qrow[i] * ldq + w) * 8), sq + (i * kWaves + wave) * 1024);
+            if ((i * kWaves + wave) * 1024 < S::QB)
+                lds_dma16(Qwg, (uint32_t)(((int64_t)qrow[i] * ldq + w) * 8), sq + (i * kWaves + wave) * 1024);
         }
 #pragma unroll
         for (int i = 0; i < S::NTL; ++i) {
@@ -354,10 +367,9 @@ __global__ __launch_bounds__(256) void k_cosine_mfma(const uint64_t *__restrict_
     }
 }
 
-// The search on the FP6 operand (flag 2).  Two workgroups per CU: one's LDS
-// waits and barriers under the other's MFMAs.
-template <int KT> struct F6Shape {
-    static constexpr int QT = 2;
+// The search on the FP6 operand (flag 2).
+template <int KT, int QT_> struct F6Shape {
+    static constexpr int QT = QT_;
     static constexpr int W = KT == 4 ? 2 : 4;          // words per window (divides kCosWin)
     static constexpr int U = W / 2;                    // 16-byte units per query row
     static constexpr int RPL = 64 / U;                 // query rows per 1 KiB load
@@ -366,7 +378,8 @@ template <int KT> struct F6Shape {
     static constexpr int WB = 3072 * KT;               // operand bytes per word
     static constexpr int TB = W * WB;
     static constexpr int NST = 2;
-    static constexpr int NQL = QB / 1024 / kWaves;
+    // loads per wave (a short last one: its waves past QB load nothing)
+    static constexpr int NQL = (QB / 1024 + kWaves - 1) / kWaves;
     static constexpr int NTL = TB / 1024 / kWaves;
     static constexpr int SB = QB + TB;
     // unit hh of row r sits in slot hh ^ (r / 8 % U): 16 rows' reads on
@@ -374,22 +387,18 @@ template <int KT> struct F6Shape {
     static __device__ __forceinline__ int slot(int r, int hh) { return hh ^ ((r >> 3) & (U - 1)); }
 };
 
-template <int KT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-void k_cosine_f6(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K, int w_lo, int w_hi, int nwin,
-                 const int8_t *__restrict__ tab, const int64_t *__restrict__ T, const double *__restrict__ rinv,
-                 const int32_t *__restrict__ flag, int32_t *__restrict__ label, double *__restrict__ max_score,
-                 double *__restrict__ scores)
+template <int KT, int QT_>
+__device__ __forceinline__ void cosine_f6(uint8_t *smem, int64_t rbase, const uint64_t *__restrict__ Q, int64_t n,
+                                          int64_t ldq, int K, int w_lo, int w_hi, int nwin,
+                                          const int8_t *__restrict__ tab, const int64_t *__restrict__ T,
+                                          const double *__restrict__ rinv, int32_t *__restrict__ label,
+                                          double *__restrict__ max_score, double *__restrict__ scores)
 {
-    if (flag[0] != COS_F6)
-        return;
-    typedef F6Shape<KT> S;
-    constexpr int QT = S::QT, W = S::W, NST = S::NST, G = S::NQL + S::NTL;
-    __shared__ __align__(16) uint8_t smem[NST * S::SB];
+    typedef F6Shape<KT, QT_> S;
+    constexpr int QT = S::QT, W = S::W;
     lds_u8 *L = (lds_u8 *)smem;
     const int lane = threadIdx.x & 63, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t rbase = (int64_t)blockIdx.x * S::ROWS;
     const uint64_t *Qwg = Q + rbase * ldq;
 
     // query loads: load i of a wave fills rows RPL*j .. (j = i*4 + wave);
@@ -408,7 +417,8 @@ void k_cosine_f6(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K, 
 #pragma unroll
         for (int i = 0; i < S::NQL; ++i) {
             const int w = w_lo + vc * W + qunit[i];
-            lds_dma16(Qwg, qoff[i] + 8u * (uint32_t)(w < w_hi ? w : w_lo), sq + (i * kWaves + wave) * 1024);
+            if ((i * kWaves + wave) * 1024 < S::QB)
+                lds_dma16(Qwg, qoff[i] + 8u * (uint32_t)(w < w_hi ? w : w_lo), sq + (i * kWaves + wave) * 1024);
         }
 #pragma unroll
         for (int i = 0; i < S::NTL; ++i)
@@ -492,6 +502,35 @@ void k_cosine_f6(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K, 
             if (max_score)
                 max_score[q] = best;
         }
+    }
+}
+
+// The streaming search on the operand _prepare chose.  Two workgroups per CU:
+// one's LDS waits and barriers under the other's MFMAs.  100003 x 16384
+// against 100 classes: 518 us on the int8 operand (its four products per 64
+// dimensions and class tile the bound), 218 on FP6, the matrix cores about half
+// busy, the rest the operand's LDS reads (24 bytes per lane and two products)
+// and the barriers.  One kernel for both operands: a launch of each, the
+// unwanted one returning at once, cost 2 us.
+template <int KT, int QT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void k_cosine(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K, int w_lo, int w_hi, int words,
+              const int8_t *__restrict__ tab, const int64_t *__restrict__ T, const double *__restrict__ rinv,
+              const int32_t *__restrict__ flag, int32_t *__restrict__ label, double *__restrict__ max_score,
+              double *__restrict__ scores)
+{
+    typedef CosShape<KT, QT> S8;
+    typedef F6Shape<KT, QT> S6;
+    constexpr int B8 = S8::NST * S8::SB, B6 = S6::NST * S6::SB;
+    __shared__ __align__(16) uint8_t smem[B8 > B6 ? B8 : B6];
+    const int64_t rbase = (int64_t)blockIdx.x * S6::ROWS;
+    if (flag[0] == COS_F6) {
+        cosine_f6<KT, QT>(smem, rbase, Q, n, ldq, K, w_lo, w_hi, words / S6::W, tab, T, rinv, label, max_score, scores);
+        return;
+    }
+    for (int64_t r = rbase; r < rbase + S6::ROWS && r < n; r += S8::ROWS) {
+        cosine_i8<KT, QT>(smem, r, Q, n, ldq, K, w_lo, w_hi, words / S8::W, tab, T, rinv, flag, label, max_score, scores);
+        __syncthreads();   // LDS reads done before the next rows' loads
     }
 }
 
@@ -637,22 +676,19 @@ hipError_t launch_cos_prepared(const uint64_t *Q, int64_t n, int64_t ldq, int K,
     const double *rinv = (const double *)(ws + L.off_rinv);
     const int32_t *flag = (const int32_t *)(ws + L.off_flag);
 #define HDC_COS_CASE(KT_)                                                                                      \
-    if (L.KT == KT_ && n <= kFewQueries) {                                                                     \
+    if (L.KT == KT_ && n <= cos_few_queries(KT_)) {                                                             \
         hipLaunchKernelGGL(k_cosine_few<KT_>, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, Q, n, ldq, K,   \
                            L.w_lo, L.w_hi, tab, T, rinv, flag, label, max_score, scores);                      \
         return hipGetLastError();                                                                              \
     }                                                                                                          \
+    if (L.KT == KT_ && n <= kCosNarrow) {                                                                      \
+        hipLaunchKernelGGL((k_cosine<KT_, 1>), dim3((unsigned)((n + 127) / 128)), dim3(256), 0, st, Q, n, ldq,   \
+                           K, L.w_lo, L.w_hi, L.nwin * kCosWin, tab, T, rinv, flag, label, max_score, scores); \
+        return hipGetLastError();                                                                              \
+    }                                                                                                          \
     if (L.KT == KT_) {                                                                                         \
-        typedef CosShape<KT_> S;                                                                               \
-        constexpr int R = S::ROWS, NW = kCosWin / S::W;                                                        \
-        hipLaunchKernelGGL((k_cosine_mfma<KT_, S::QT, S::NST>), dim3((unsigned)((n + R - 1) / R)), dim3(256), 0, \
-                           st, Q, n, ldq,                                                                      \
-                           K, L.w_lo, L.w_hi, L.nwin * NW, tab, T, rinv, flag, label, max_score, scores);            \
-        /* one of the two returns at once, by the operand _prepare chose */                                    \
-        typedef F6Shape<KT_> S6;                                                                               \
-        hipLaunchKernelGGL(k_cosine_f6<KT_>, dim3((unsigned)((n + S6::ROWS - 1) / S6::ROWS)), dim3(256), 0, st, \
-                           Q, n, ldq, K, L.w_lo, L.w_hi, L.nwin * (kCosWin / S6::W), tab, T, rinv, flag, label, \
-                           max_score, scores);                                                                 \
+        hipLaunchKernelGGL((k_cosine<KT_, 2>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, Q, n, ldq,   \
+                           K, L.w_lo, L.w_hi, L.nwin * kCosWin, tab, T, rinv, flag, label, max_score, scores); \
         return hipGetLastError();                                                                              \
     }
     HDC_COS_CASE(1)

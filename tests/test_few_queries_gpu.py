@@ -1,6 +1,8 @@
-"""The prepared searches on both sides of the few-queries rule (16384): the
-kernel that splits words over a workgroup's waves and the streaming one, at
-every class-tile count, dimension sets that start and end inside words, and
+"""The prepared searches on both sides of the rules on the number of queries
+(16384; the ADC search's 32768 up to 32 classes; the cosine search's 8192 from
+65 classes and 65536):
+the kernel that splits words over a workgroup's waves and the streaming ones,
+at every class-tile count, dimension sets that start and end inside words, and
 ragged last blocks.  Labels, minima / maxima and all scores equal the oracle's
 exactly."""
 import numpy as np
@@ -11,7 +13,7 @@ from oracle import oracle as O
 
 pytestmark = pytest.mark.gpu
 
-NS = [1, 33, 16384, 16385, 16700]
+NS = [1, 33, 8192, 8193, 16384, 16385, 16700, 32768, 32769, 65536, 65537]
 SETS = [  # nbits, K, (start, end, stride)
     (1088, 3, (0, 1088, 1)), (2048, 40, (65, 2001, 2)), (640, 100, (130, 639, 1)), (64, 32, (0, 64, 1)),
 ]
