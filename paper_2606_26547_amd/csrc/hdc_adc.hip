@@ -196,7 +196,7 @@ hipError_t launch_adc_prepare(const uint64_t *C, int K, int64_t ldc, int start, 
 // partials per operation, four operations.  The 16-bit patterns 0x6400 + code
 // are summed as integers for up to kAdcFlush chunks (1023 * 64 < 2^16) and
 // then added to the 32-bit code sums; score = floor * chunks + step * codes.
-// 100003 x 4096 against 26 classes, 6 bits: 132 us by the table, 106 so; the
+// 262144 x 10240 against 26 classes, 6 bits: 132 us by the table, 106 so; the
 // conversion's vector operations, four a partial, bound it.
 constexpr int kAdcFlush = 64;
 // (see few_pairs; 24000 x 10240 against 26 classes: 37 us streaming, 21 so; 16384

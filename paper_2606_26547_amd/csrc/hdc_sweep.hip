@@ -5,19 +5,22 @@
 // The host validates the configurations, orders them longest first, lays
 // out their work items and finds the distinct dimension sets (configurations
 // of the same start, end and stride share one class operand), and sends all
-// of it up in one copy.  Workspace layout (all offsets 256-byte aligned):
+// of it up in one copy of what this launch needs (256 shared configurations:
+// 21 KB; laid out for any configurations it was 67 KB).  Workspace layout (all
+// offsets 256-byte aligned):
 //   [0]            queue counter (uint32)
 //   [256]          slot descriptors, ncfg x SlotDesc
 //   [..]           slot order (longest first), ncfg x int32
 //   [..]           first work item of each slot in that order, ncfg + 1 x int32
 //   [..]           per-slot counters (correct, n, device ticks), zeroed
-//   [..]           distinct dimension sets, up to ncfg x TableDesc
+//   [..]           distinct dimension sets, TableDesc each
+//   [..]           shared search items, ShItem each
+//   [..]           shared end counters (correct, device ticks), zeroed, a line
+//                  each
 //   [..]           per-slot results as returned (correct, n, device_us)
 //   [..]           class operand regions of fixed size, one per distinct
 //                  dimension set (chunks(D) * KT KiB table + 128 int32
 //                  popcounts)
-//   [..]           shared search items, up to ncfg x ShItem
-//   [..]           shared end counters (correct, device ticks), zeroed
 //   [..]           projection rows converted to E4M3 (direct-staged body)
 //   [..]           packed encodings of the shared path: one region per
 //                  encoding (int8, E4M3), kShQueries rows of ceil(D / 64)
@@ -43,6 +46,7 @@
 #include <vector>
 
 #include "hdc_encoder.h"
+#include "hdc_stream.h"
 
 namespace hdc {
 
@@ -65,9 +69,10 @@ struct SlotCount {
     uint64_t ticks;
 };
 
-// Shared path: ends per search item, words per LDS chunk, queries per pass.
+// Shared path: ends per search item, words per LDS chunk (whole lines of a
+// row), queries per pass.
 constexpr int kShEnds = 16;
-constexpr int kShWords = 16;
+constexpr int kShWords = 32;
 constexpr int kShQueries = 4096;
 
 // A search item: one chain (compute type region, start, stride) and up to
@@ -82,7 +87,9 @@ struct ShItem {
     int32_t slot[kShEnds];        // its end counter
 };
 
-struct EndCount {
+// On a line of its own: every workgroup of an item adds to each of its ends
+// (2000 queries, 8 items of 5 ends: 7.6 us of the search with 16 bytes each).
+struct alignas(128) EndCount {
     int32_t correct, pad;
     uint64_t ticks;
 };
@@ -108,10 +115,7 @@ struct SweepLayout {
         off_items = align256(off_order + (size_t)ncfg * 4);
         off_count = align256(off_items + (size_t)(ncfg + 1) * 4);
         off_tabs = align256(off_count + (size_t)ncfg * sizeof(SlotCount));
-        off_sh = align256(off_tabs + (size_t)ncfg * sizeof(TableDesc));
-        off_end = align256(off_sh + (size_t)ncfg * sizeof(ShItem));
-        off_res = align256(off_end + (size_t)ncfg * sizeof(EndCount));
-        off_regions = align256(off_res + (size_t)ncfg * sizeof(hdc_config_result));
+        place(ncfg, ncfg, ncfg, (size_t)ncfg * 16);
         region = align256(sweep_table_bytes(D, K) + 128 * 4);
         ldp_conv = conv_pitch(F);
         off_p8 = align256(off_regions + region * (size_t)ncfg);
@@ -119,6 +123,16 @@ struct SweepLayout {
         hreg = align256((size_t)kShQueries * wd * 8);
         off_h = align256(off_p8 + (size_t)D * ldp_conv);
         total = off_h + 2 * hreg;
+    }
+    // What a launch needs of the parts sized by their number: the copy up ends
+    // at off_res.  A shared configuration has no dimension set, so its region,
+    // never under 1536 bytes, holds the line of its end counter.
+    void place(int ncfg, size_t ntab, size_t nsh, size_t end_bytes)
+    {
+        off_sh = align256(off_tabs + ntab * sizeof(TableDesc));
+        off_end = align256(off_sh + nsh * sizeof(ShItem));
+        off_res = align256(off_end + end_bytes);
+        off_regions = align256(off_res + (size_t)ncfg * sizeof(hdc_config_result));
     }
 };
 
@@ -241,141 +255,178 @@ __device__ __forceinline__ uint64_t chain_mask(int a, int s0, int stride, int en
     return rem < 64 ? m & ((1ull << rem) - 1) : m;
 }
 
-// Shared search: workgroup (query block of 64, item).  Each of the NW
-// waves takes KCW classes of the same 64 queries (one query per lane).
-// Chunks of kShWords words of the queries' encodings and of the class words
-// go through registers (the next chunk's loads are in flight while the
-// current one is counted) into LDS, both cut to the chain's set by masks
-// computed one chunk ahead.  Per word, a lane adds popcount(h ^ c) to each
-// of its classes' distances.  At the last word of a set's end, the
-// distances up to that end (that word cut below the end) are ranked by the
-// key distance * 128 + class, whose minimum is the first smallest distance;
-// the waves meet in an LDS minimum.  The 64 labels of each end are then
-// compared with the truth and counted into the end's counter.
-template <int KCW, int NW>
-__global__ __launch_bounds__(64 * NW) void k_sweep_shared(const uint64_t *__restrict__ C, int K, int64_t ldc,
-                                                          const int32_t *__restrict__ truth, int nq,
-                                                          uint8_t *__restrict__ ws, SweepLayout L)
+// Shared search: workgroup (32 queries, item), KT class tiles.  Chunks of
+// kShWords words of the queries' encodings and of the class words go through
+// registers (the next chunk's loads are in flight while the current one is
+// counted) into LDS, whole lines of each row.  Per word a wave builds the
+// queries' FP4 operand (-1, +1, and 0 outside the chain's set, whose mask is
+// computed one chunk ahead) and the classes' (-1, +1) and adds their products;
+// wave w takes the words w mod 4.  Up to a set's end the products add up to its
+// dimensions less twice the distance: there the waves' sums (the end's word
+// cut below the end) meet in LDS and are ranked by the key distance * 128 +
+// class, whose minimum is the first smallest distance.  The 32 labels of each
+// end are then compared with the truth and counted into the end's counter.
+//
+// On the matrix cores because population counts (a lane per query, four
+// classes per wave, five LDS reads a word) kept LDS and its latency busy.  2000
+// queries x 10240 x 26 classes, 8 items of 5 ends: 30 us by counts, 25 by
+// products with 16-byte end counters and each end ranked as it came, 21 with a
+// line per counter and up to eight ends ranked together; of those the words take
+// 4, the counters' atomics 2.5, their loads 1 and launch, first loads and
+// ranking the rest.
+template <int KT>
+__global__ __launch_bounds__(256) void k_sweep_shared(const uint64_t *__restrict__ C, int K, int64_t ldc,
+                                                      const int32_t *__restrict__ truth, int nq,
+                                                      uint8_t *__restrict__ ws, SweepLayout L)
 {
-    constexpr int T = 64 * NW;
-    constexpr int CW = kShWords * NW * KCW / T;      // class words per thread and chunk
-    constexpr int HW = kShWords * 64 / T;            // encoding words per thread and chunk
-    static_assert(CW >= 1 && HW >= 1 && kShWords % HW == 0, "chunk split");
-    __shared__ uint64_t cm[kShWords][NW * KCW];
-    __shared__ uint64_t hs[64][kShWords + 1];
-    __shared__ uint64_t msk[2][kShWords];
-    __shared__ int best[kShEnds][64];
-    __shared__ int ends[kShEnds];
+    constexpr int ROW = 2 * kShWords + 1;            // dwords per LDS row: rows on distinct banks
+    constexpr int PT = 256 / kShWords;               // rows per pass of the workgroup
+    constexpr int HW = 32 / PT, CW = KT * 32 / PT;   // words per thread and chunk
+    constexpr int NS = 8 / KT;                       // ends summed before they are ranked
+    __shared__ uint32_t hs[32 * ROW], cm[KT * 32 * ROW];
+    __shared__ uint32_t msk[2][2 * kShWords];
+    __shared__ int sums[NS][KT * 32][33];
+    __shared__ int best[kShEnds][32];
     const ShItem &it = ((const ShItem *)(ws + L.off_sh))[blockIdx.y];
     const uint64_t *H = (const uint64_t *)(ws + L.off_h + L.hreg * it.reg);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int qb = blockIdx.x * 64;
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int qb = blockIdx.x * 32;
     const int nend = it.nend, s0 = it.s0, stride = it.stride, wlo = it.wlo, a0 = it.a0, a1 = it.a1;
     const int end_max = it.end[nend - 1];
     const uint64_t t0 = wall_clock64();
-    for (int i = tid; i < kShEnds * 64; i += T)
-        best[i >> 6][i & 63] = 0x7fffffff;
-    if (tid < nend)
-        ends[tid] = it.end[tid];
-    // this thread's share of a chunk: words hw .. hw + HW - 1 of query row
-    // hq, and class words (word i % kShWords, class i / kShWords) for
-    // i = tid + T r
-    const int hq = tid / (kShWords / HW), hw = HW * (tid % (kShWords / HW));
-    const bool hrow = qb + hq < nq;
-    const uint64_t *hp = H + (int64_t)(qb + hq) * L.wd - wlo + hw;
+    for (int i = tid; i < kShEnds * 32; i += 256)
+        best[i >> 5][i & 31] = 0x7fffffff;
+    for (int i = tid; i < NS * KT * 32 * 33; i += 256)
+        (&sums[0][0][0])[i] = 0;
+    // this thread's share of a chunk: word fw of rows fr + PT r
+    const int fw = tid % kShWords, fr = tid / kShWords;
     uint64_t rh[HW], rc[CW];
     auto fetch = [&](int c0) {
+        const bool in = c0 + fw < a1;
 #pragma unroll
-        for (int x = 0; x < HW; ++x)
-            rh[x] = hrow && c0 + hw + x < a1 ? hp[c0 + x] : 0;
+        for (int r = 0; r < HW; ++r) {
+            const int q = qb + fr + PT * r;
+            rh[r] = in && q < nq ? H[(int64_t)q * L.wd - wlo + c0 + fw] : 0;
+        }
 #pragma unroll
         for (int r = 0; r < CW; ++r) {
-            const int i = tid + T * r, ww = i & (kShWords - 1), k = i / kShWords;
-            rc[r] = k < K && c0 + ww < a1 ? C[(int64_t)k * ldc + c0 + ww] : 0;
+            const int k = fr + PT * r;
+            rc[r] = in && k < K ? C[(int64_t)k * ldc + c0 + fw] : 0;
         }
     };
-    if (tid < kShWords)
-        msk[0][tid] = chain_mask(a0 + tid, s0, stride, end_max);
+    auto mask = [&](int b, int c0) {
+        if (tid < kShWords) {
+            const uint64_t m = chain_mask(c0 + tid, s0, stride, end_max);
+            msk[b][2 * tid] = (uint32_t)m;
+            msk[b][2 * tid + 1] = (uint32_t)(m >> 32);
+        }
+    };
+    mask(0, a0);
     fetch(a0);
-    __syncthreads();
-    const int kb = wave * KCW;
-    int acc[KCW];
+    v16f acc[KT];
 #pragma unroll
-    for (int j = 0; j < KCW; ++j)
-        acc[j] = 0;
-    int e = 0;    // next end to emit, and the word of its last dimension
-    int elw = __builtin_amdgcn_readfirstlane((ends[0] - 1) / 64);
+    for (int kt = 0; kt < KT; ++kt)
+        acc[kt] = v16f{};
+    // the products of word w of the chunk, its mask cut by pm
+    auto word = [&](v16f (&s)[KT], int b, int w, uint32_t pm) {
+        const uint32_t m = msk[b][2 * w + g] & pm;
+        const uint32_t h = hs[(lane & 31) * ROW + 2 * w + g] & m;
+        v8i qf = {};
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            qf[r] = (int)(((h << (3 - r)) & 0x88888888u) | ((r ? m >> (r - 1) : m << 1) & 0x22222222u));
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+            s[kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                query_bipolar(cm[(kt * 32 + (lane & 31)) * ROW + 2 * w + g]), qf, s[kt], 4, 4, 0, 0, 0, 0);
+    };
+    // ranks ends [e0, e1) and clears their sums
+    auto rank = [&](int e0, int e1) {
+        __syncthreads();
+        const int c = tid & 31;
+        for (int x = e0; x < e1; ++x) {
+            const int cnt = (it.end[x] - 1 - s0) / stride + 1;
+            int key = 0x7fffffff;
+#pragma unroll
+            for (int i = 0; i < KT * 4; ++i) {
+                const int k = (tid >> 5) + 8 * i;
+                if (k < K)
+                    key = min(key, (cnt - sums[x - e0][k][c]) / 2 * 128 + k);
+                sums[x - e0][k][c] = 0;
+            }
+            atomicMin(&best[x][c], key);
+        }
+        __syncthreads();
+    };
+    int e = 0, e0 = 0;   // next end to emit, first one not ranked yet
+    int elw = (it.end[0] - 1) / 64;   // word of its last dimension
     int b = 0;
     for (int c0 = a0; c0 < a1; c0 += kShWords, b ^= 1) {
         const int nw = a1 - c0 < kShWords ? a1 - c0 : kShWords;
 #pragma unroll
-        for (int x = 0; x < HW; ++x)
-            hs[hq][hw + x] = rh[x] & msk[b][hw + x];
+        for (int r = 0; r < HW; ++r) {
+            uint32_t *p = hs + (fr + PT * r) * ROW + 2 * fw;
+            p[0] = (uint32_t)rh[r];
+            p[1] = (uint32_t)(rh[r] >> 32);
+        }
 #pragma unroll
         for (int r = 0; r < CW; ++r) {
-            const int i = tid + T * r, ww = i & (kShWords - 1), k = i / kShWords;
-            cm[ww][k] = rc[r] & msk[b][ww];
+            uint32_t *p = cm + (fr + PT * r) * ROW + 2 * fw;
+            p[0] = (uint32_t)rc[r];
+            p[1] = (uint32_t)(rc[r] >> 32);
         }
         if (c0 + kShWords < a1) {
-            if (tid < kShWords)
-                msk[b ^ 1][tid] = chain_mask(c0 + kShWords + tid, s0, stride, end_max);
+            mask(b ^ 1, c0 + kShWords);
             fetch(c0 + kShWords);
         }
         __syncthreads();
-        for (int w = 0; w < nw;) {
-            if (c0 + w == elw) {
-                // sets whose last dimension lies in this word
-                const int a = c0 + w;
-                const uint64_t h = hs[lane][w];
-                while (e < nend && (ends[e] - 1) / 64 == a) {
-                    const int rem = ends[e] - 64 * a;
-                    const uint64_t pm = rem >= 64 ? ~0ull : (1ull << rem) - 1;
-                    int key = 0x7fffffff;
-#pragma unroll
-                    for (int j = 0; j < KCW; ++j) {
-                        const int k = kb + j;
-                        const int d = acc[j] + (int)__popcll((h ^ cm[w][k]) & pm);
-                        if (k < K)
-                            key = min(key, d * 128 + k);
-                    }
-                    atomicMin(&best[e][lane], key);
-                    ++e;
-                }
-                elw = e < nend ? __builtin_amdgcn_readfirstlane((ends[e] - 1) / 64) : 0x7fffffff;
-#pragma unroll
-                for (int j = 0; j < KCW; ++j)
-                    acc[j] += (int)__popcll(h ^ cm[w][kb + j]);
-                ++w;
-                continue;
-            }
-            // words up to the next set's last word: four at a time, their
-            // LDS reads issued together
+        int w = wave;
+        for (;;) {
+            // this wave's words up to the next set's last word
             const int stop = elw - c0 < nw ? elw - c0 : nw;
-            for (; w + 4 <= stop; w += 4) {
-                uint64_t h[4];
+            for (; w + 12 < stop; w += 16)
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    h[u] = hs[lane][w + u];
+                    word(acc, b, w + 4 * u, ~0u);
+            for (; w < stop; w += 4)
+                word(acc, b, w, ~0u);
+            if (elw - c0 >= nw)
+                break;
+            // sets whose last dimension lies in word elw
+            const int a = elw;
+            do {
+                const int end = it.end[e];
+                v16f part[KT];
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+                for (int kt = 0; kt < KT; ++kt)
+                    part[kt] = acc[kt];
+                if (w == a - c0) {
+                    const int rem = end - 64 * a - 32 * g;   // dimensions of this half
+                    word(part, b, w, rem >= 32 ? ~0u : rem > 0 ? (1u << rem) - 1u : 0u);
+                }
 #pragma unroll
-                    for (int j = 0; j < KCW; ++j)
-                        acc[j] += (int)__popcll(h[u] ^ cm[w + u][kb + j]);
-            }
-            for (; w < stop; ++w) {
-                const uint64_t h = hs[lane][w];
+                for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-                for (int j = 0; j < KCW; ++j)
-                    acc[j] += (int)__popcll(h ^ cm[w][kb + j]);
-            }
+                    for (int v = 0; v < 16; ++v)
+                        atomicAdd(&sums[e - e0][kt * 32 + 8 * (v >> 2) + 4 * g + (v & 3)][lane & 31],
+                                  (int)part[kt][v]);
+                if (e - e0 == NS - 1) {
+                    rank(e0, e + 1);
+                    e0 = e + 1;
+                }
+                ++e;
+                elw = e < nend ? (it.end[e] - 1) / 64 : 0x7fffffff;
+            } while (elw == a);
         }
         __syncthreads();    // the chunk's LDS reads are done
     }
+    rank(e0, nend);
     EndCount *cnt = (EndCount *)(ws + L.off_end);
     const uint64_t dt = wall_clock64() - t0;
-    for (int x = wave; x < nend; x += NW) {
+    for (int x = wave; x < nend; x += 4) {
         const int q = qb + lane;
-        const bool ok = q < nq && (best[x][lane] & 127) == truth[q];
+        const bool ok = lane < 32 && q < nq && (best[x][lane & 31] & 127) == truth[q];
         const uint64_t m = __ballot(ok);
         if (lane == 0) {
             if (m)
@@ -599,16 +650,16 @@ static hipError_t launch_sweep_fb(const EncodeArgs &base, const SweepArgs &a, co
 
 hipError_t launch_sweep(const SweepArgs &a, hipStream_t st)
 {
-    const SweepLayout L(a.ncfg, a.F, a.D, a.K);
+    SweepLayout L(a.ncfg, a.F, a.D, a.K);
     const int KT = sweep_kt(a.K);
     const size_t table_bytes = sweep_table_bytes(a.D, a.K);
     // ---- host setup: slot descriptors, order, work items, distinct sets
-    std::vector<uint8_t> blob(L.off_regions, 0);
+    std::vector<uint8_t> blob(L.off_tabs, 0);
     SlotDesc *desc = (SlotDesc *)(blob.data() + L.off_desc);
     int32_t *order = (int32_t *)(blob.data() + L.off_order);
     int32_t *items = (int32_t *)(blob.data() + L.off_items);
     SlotCount *cnt = (SlotCount *)(blob.data() + L.off_count);
-    TableDesc *tabs = (TableDesc *)(blob.data() + L.off_tabs);
+    std::vector<TableDesc> tabs;
     std::vector<int64_t> cost(a.ncfg);
     std::map<std::tuple<int, int, int>, int> seen;
     // shared configurations: chains (compute type, start, stride) -> end ->
@@ -657,7 +708,7 @@ hipError_t launch_sweep(const SweepArgs &a, hipStream_t st)
             if (it == seen.end()) {
                 const int t = (int)seen.size();
                 it = seen.emplace(key, t).first;
-                tabs[t] = TableDesc{s.s0, s.stride, s.nd, 0};
+                tabs.push_back(TableDesc{s.s0, s.stride, s.nd, 0});
             }
             s.table = it->second;
             direct |= s.iq == 3 && s.ct == C_FP8;
@@ -669,7 +720,8 @@ hipError_t launch_sweep(const SweepArgs &a, hipStream_t st)
         cnt[i].ticks = 0;
         order[i] = i;
     }
-    std::stable_sort(order, order + a.ncfg, [&](int x, int y) { return cost[x] > cost[y]; });
+    if (!seen.empty())
+        std::stable_sort(order, order + a.ncfg, [&](int x, int y) { return cost[x] > cost[y]; });
     int32_t run = 0;
     for (int r = 0; r < a.ncfg; ++r) {
         items[r] = run;
@@ -707,9 +759,13 @@ hipError_t launch_sweep(const SweepArgs &a, hipStream_t st)
         }
     }
     std::stable_sort(sh.begin(), sh.end(), [](const ShItem &x, const ShItem &y) { return x.a1 - x.a0 > y.a1 - y.a0; });
+    L.place(a.ncfg, tabs.size(), sh.size(), (size_t)nslots * sizeof(EndCount));
+    blob.resize(L.off_res, 0);
+    if (!tabs.empty())
+        memcpy(blob.data() + L.off_tabs, tabs.data(), tabs.size() * sizeof(TableDesc));
     if (!sh.empty())
         memcpy(blob.data() + L.off_sh, sh.data(), sh.size() * sizeof(ShItem));
-    // the queue counter (offset 0) goes up as 0 with the rest
+    // the queue counter (offset 0) and the end counters go up as 0 with the rest
     hipError_t e = hipMemcpyAsync(a.ws, blob.data(), blob.size(), hipMemcpyHostToDevice, st);
     if (e != hipSuccess)
         return e;
@@ -768,17 +824,13 @@ hipError_t launch_sweep(const SweepArgs &a, hipStream_t st)
             if (e != hipSuccess)
                 return e;
         }
-        const dim3 grid((unsigned)((nq + 63) / 64), (unsigned)sh.size());
-        // eight waves per query block, K / 8 classes each (rounded up to 4, 8, 16)
+        const dim3 grid((unsigned)((nq + 31) / 32), (unsigned)sh.size());
         if (a.K <= 32)
-            hipLaunchKernelGGL((k_sweep_shared<4, 8>), grid, dim3(512), 0, st, a.C, a.K, a.ldc, a.truth + q0, nq,
-                               a.ws, L);
+            hipLaunchKernelGGL(k_sweep_shared<1>, grid, dim3(256), 0, st, a.C, a.K, a.ldc, a.truth + q0, nq, a.ws, L);
         else if (a.K <= 64)
-            hipLaunchKernelGGL((k_sweep_shared<8, 8>), grid, dim3(512), 0, st, a.C, a.K, a.ldc, a.truth + q0, nq,
-                               a.ws, L);
+            hipLaunchKernelGGL(k_sweep_shared<2>, grid, dim3(256), 0, st, a.C, a.K, a.ldc, a.truth + q0, nq, a.ws, L);
         else
-            hipLaunchKernelGGL((k_sweep_shared<16, 8>), grid, dim3(512), 0, st, a.C, a.K, a.ldc, a.truth + q0, nq,
-                               a.ws, L);
+            hipLaunchKernelGGL(k_sweep_shared<4>, grid, dim3(256), 0, st, a.C, a.K, a.ldc, a.truth + q0, nq, a.ws, L);
         e = hipGetLastError();
         if (e != hipSuccess)
             return e;
