@@ -165,9 +165,9 @@ static hipError_t launch_one(const EncodeArgs &a, hipStream_t st)
 // The direct-staged shape of a bucket: two query tiles per wave (one wave per
 // SIMD), so that each projection fragment read from LDS feeds two MFMAs: with
 // one, four waves ask LDS for 128 bytes a cycle, all it has (784 uint8
-// features, n = 60000, 8192 dimensions: 820 us of encoding against 300).  Two row tiles per
-// chunk (80 MFMAs between barriers at 640 features) while three stages of
-// them fit the LDS, else one (uint8 features: always one, whose barrier also
+// features, n = 60000, 8192 dimensions: 820 us of encoding against 300).  Two
+// row tiles per chunk (80 MFMAs between barriers at 640 features) while three
+// stages of them fit the LDS, else one (uint8 features: always one, whose barrier also
 // publishes the column sums).  One query tile where the registers hold no
 // second beside the accumulators: four class tiles from 833 features, and the
 // split E4M3 type, whose query operand is twice as wide (there each fragment

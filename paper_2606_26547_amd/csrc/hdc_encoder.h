@@ -47,7 +47,8 @@ struct Encoder {
     // straight into LDS (global_load_lds, 16 bytes per lane), a ring of three
     // to six stages.  Each load fills 1 KiB of LDS contiguously, so a stage is NIW
     // loads per wave (the last ones repeat its last KiB) and the units past
-    // the chunk's rows land in the stage's slack.  The rows are copied as they are (bytes on every path).
+    // the chunk's rows land in the stage's slack.  The rows are copied as they
+    // are (bytes on every path).
     // A chunk is RT row tiles of 32 dimensions (one or two, direct staging
     // only); its class operand is RT * KT KiB.
     static_assert(!DMA || (XF == 0 && (CT == C_I8 || CT == C_FP8 || CT == C_FP8S)),
@@ -495,9 +496,11 @@ struct Encoder {
     }
 
     // ------------------------------------------------------------ compute
-    // A dependent MFMA chain issues at half rate on gfx950 (the result
-    // latency is twice the issue interval), so a single-tile wave alternates
-    // its K steps between KC = 2 accumulators, added in the epilogue: exact
+    // A single-tile wave of the register-staged loop alternates its K steps
+    // between KC = 2 accumulators, added in the epilogue, so that a product
+    // does not wait for the one before it (back to back the int8 32x32x32 form
+    // keeps its 32 cycles in one chain as well; with LDS waits between them
+    // two chains measured faster): exact
     // for int32, and order-free for the float rungs on integer-valued
     // features (sums below 2^24).  Register-staged kernels compiled for two
     // waves per SIMD have no room for the second set and rely on the other
@@ -870,7 +873,13 @@ struct Encoder {
     // or 64 cycles, so between two of them a wave can issue about 7 (15) other
     // instructions for free and more than that stalls it.  The work beside
     // the MFMAs is therefore cut into pieces of a few instructions, handed
-    // out by slot: slot s * MPS + m follows MFMA m of K step s.
+    // out by slot: slot s * MPS + m follows MFMA m of K step s; the first
+    // fragments of the next pass are read before this one ends, so passes
+    // follow each other without an LDS wait.  Per MFMA of 32 cycles at 617
+    // features: 42 cycles with a loop that drained at each row tile, 38 so
+    // (classify), 52 and 37 (encode); on large batches the clock, which falls
+    // as the cores fill, takes most of that back (262144 x 617, 10240
+    // dimensions: 1209 us, 1160 so).
     static constexpr int MPS = CT == C_FP8S ? 2 : QT;      // MFMAs per K step
     static_assert(!DMA || CT != C_FP8S || QT == 1, "the split E4M3 type takes one query tile");
     static constexpr int SLOTS = KS * MPS;

@@ -21,9 +21,10 @@ def fit(H: torch.Tensor, nbits: int, labels: torch.Tensor, K: int, epochs: int =
     acc, Cw = hdc.class_acc(H, nbits, labels, K, ws)
     pred = torch.empty(H.shape[0], dtype=torch.int32, device=H.device)
     wrong = []
+    new = torch.empty if H.shape[0] else torch.zeros   # an epoch over rows writes its count
     for _ in range(epochs):
         hdc.HammingPrepared(Cw, 0, nbits, 1)(H, out=pred)
-        w = torch.zeros(1, dtype=torch.int32, device=H.device)
+        w = new(1, dtype=torch.int32, device=H.device)
         hdc.retrain_epoch(H, nbits, labels, pred, acc, Cw, w, ws)
         wrong.append(w)
     return Cw, acc, wrong
