@@ -693,8 +693,10 @@ def cosine_similarity(dev, hdc, torch, event_loop, ds, Xtr, ytr, Xte, Pd, F, K, 
     _, ms, _ = event_loop(lambda: cp(Q, out=lab), 10, 2)
     res["search_2^20"] = {"ms": ms, "GB_s": nq * D / 8 / (ms / 1e3) / 1e9, "queries_per_s": nq / (ms / 1e3),
                           "int8_tops": 2 * nq * D * 32 * 2 / (ms / 1e3) / 1e12}
-    # matrix cores: two int8 32x32x32 MFMAs per (32 queries, 32 dimensions,
-    # class tile of 32): 2 * 2 * n * D * 32 ops executed for K <= 32
+    # matrix cores: two parts of each class sum times 32 queries, 32 dimensions
+    # and a class tile of 32, 2 * 2 * n * D * 32 ops executed for K <= 32: on
+    # FP6 digits while the sums over S stay within +-255, else in int8 (the
+    # peak the rate is put against)
     ops = 2 * 2 * nq * D * 32
     res["roofline"] = {"bound": "mfma", "achieved": ops / (ms / 1e3) / 1e12, "peak": MFMA_INT8_PEAK_TOPS,
                        "unit": "TOP/s", "frac": ops / (ms / 1e3) / 1e12 / MFMA_INT8_PEAK_TOPS, "ops_per_launch": ops,
