@@ -290,6 +290,7 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
 {
     typedef HmShape<KT> S;
     constexpr int QT = S::QT, W = S::W, ROWS = S::ROWS, NST = S::NST;
+    constexpr int QG = KT == 2 ? 1 : QT;   // query tiles of a group (registers for two waves per SIMD)
     __shared__ __align__(16) uint8_t smem[NST * S::SB];
     __shared__ int lut[257];
     lds_u8 *L = (lds_u8 *)smem;
@@ -395,36 +396,39 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
                     const v4i a4 = *(const lds_v4i *)(stb + (((2 * cc + h) * KT + kt) * 64 + lane) * 16);
                     af[h][kt] = v8i{a4[0], a4[1], a4[2], a4[3], 0, 0, 0, 0};
                 }
-            // every tile's products first: a tile's conversion runs while the
-            // next ones' products are on the matrix cores
-            v16f part[QT][KT];
+            // a group of tiles' products first: a tile's conversion runs while
+            // the next ones' products are on the matrix cores
 #pragma unroll
-            for (int qt = 0; qt < QT; ++qt) {
-                const v4i u = qv[qt][cc];   // the chunk's two words: dwords 0-1 and 2-3
-                const v8i b0 = query_bipolar((uint32_t)(g ? u[1] : u[0]));
-                const v8i b1 = query_bipolar((uint32_t)(g ? u[3] : u[2]));
+            for (int q0 = 0; q0 < QT; q0 += QG) {
+                v16f part[QG][KT];
 #pragma unroll
-                for (int kt = 0; kt < KT; ++kt) {
-                    part[qt][kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[0][kt], b0, v16f{}, 4, 4, 0, 0,
-                                                                                   0, 0);
-                    part[qt][kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[1][kt], b1, part[qt][kt], 4, 4,
-                                                                                   0, 0, 0, 0);
+                for (int qt = 0; qt < QG; ++qt) {
+                    const v4i u = qv[q0 + qt][cc];   // the chunk's two words: dwords 0-1 and 2-3
+                    const v8i b0 = query_bipolar((uint32_t)(g ? u[1] : u[0]));
+                    const v8i b1 = query_bipolar((uint32_t)(g ? u[3] : u[2]));
+#pragma unroll
+                    for (int kt = 0; kt < KT; ++kt) {
+                        part[qt][kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[0][kt], b0, v16f{}, 4, 4, 0,
+                                                                                       0, 0, 0);
+                        part[qt][kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[1][kt], b1, part[qt][kt], 4,
+                                                                                       4, 0, 0, 0, 0);
+                    }
                 }
-            }
-            if (arith) {
+                if (arith) {
 #pragma unroll
-                for (int qt = 0; qt < QT; ++qt)
+                    for (int qt = 0; qt < QG; ++qt)
 #pragma unroll
-                    for (int kt = 0; kt < KT; ++kt)
-                        codes[kt][qt].add(conv, part[qt][kt]);
-            } else {
+                        for (int kt = 0; kt < KT; ++kt)
+                            codes[kt][q0 + qt].add(conv, part[qt][kt]);
+                } else {
 #pragma unroll
-                for (int qt = 0; qt < QT; ++qt)
+                    for (int qt = 0; qt < QG; ++qt)
 #pragma unroll
-                    for (int kt = 0; kt < KT; ++kt)
+                        for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            sc[kt][qt][e] += lut[(int)part[qt][kt][e] + 128];
+                            for (int e = 0; e < 16; ++e)
+                                sc[kt][q0 + qt][e] += lut[(int)part[qt][kt][e] + 128];
+                }
             }
         }
         if (arith && pending > kAdcFlush - W / 2)
