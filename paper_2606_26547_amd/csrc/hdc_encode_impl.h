@@ -137,13 +137,19 @@ static void launch_split_argmin(const EncodeArgs &a, int Z, hipStream_t st)
 // Smallest dimension split (64-dimension words) of a launch.
 constexpr int split_units_min(int mode) { return mode == M_ENCODE ? 1 : kSplitMinUnits; }
 
-// Whether two query tiles per wave would leave half the device idle: then one
-// query tile (128 queries per workgroup) makes twice the workgroups, each
-// with half the features to load and half the MFMAs.
+// Whether two query tiles per wave would leave much of the device idle: then
+// one query tile (128 queries per workgroup) makes twice the workgroups, each
+// with half the features to load and half the MFMAs a word.  It pays while its
+// splits, over twice the blocks, are not over a quarter longer (both are
+// bounded by the shortest split, see split_units_min): 3000 x 771, 3418
+// dimensions, 10 classes, 22.4 us with two tiles and 17.8 with one; at 4500,
+// where one tile's splits are 7 words against 5, 24 with one and 23 with two.
 static bool few_blocks(const EncodeArgs &a, int mode)
 {
     const int64_t blocks = (a.n + 255) / 256;
-    return 2 * blocks * split_count(blocks, a.nd, a.max_split, 256, split_units_min(mode)) <= 256;
+    const int z2 = split_count(blocks, a.nd, a.max_split, 256, split_units_min(mode));
+    const int z1 = split_count(2 * blocks, a.nd, a.max_split, 256, split_units_min(mode));
+    return 2 * blocks * z1 <= 256 && 4 * split_units(a.nd, z1) <= 5 * split_units(a.nd, z2);
 }
 
 template <int CT, int XF, int QT, int KS, int KT, int MODE, bool DMA = false, int RT = 1, int SRC = W_ROWS>
