@@ -395,7 +395,7 @@ def main():
                                             "ops_per_launch": shared_ops,
                                             "note": "shared path: the two encodings of the union (2 F D x "
                                                     "queries each) over the whole call; the masked Hamming "
-                                                    "search is VALU work and not counted"}}
+                                                    "search (FP4 matrix cores) is not counted"}}
         d, k, s, tdt = best.cfg
         t_form = cls_form if tdt == "int8" else tdt
         if tdt == "fp8" and cls_form == "int8shift" and "fp8" in shifted_P:
