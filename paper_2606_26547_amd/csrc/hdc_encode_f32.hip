@@ -11,9 +11,9 @@ namespace hdc {
 // each wave through 8 row tiles of 32 MFMAs of 64 cycles (17.5 us); here 56
 // workgroups with two row tiles per wave.  Projection rows and class operand
 // come straight from global memory (each is read once per workgroup), the
-// int8 +-1 weights become fp32 as they are multiplied, and the K order per
-// accumulator is the encoder's, so the signs are the same bit for bit.  The
-// four waves' class sums meet in LDS.
+// int8 +-1 weights become fp32 as they are multiplied, and the K steps go to the
+// encoder's chains in the encoder's order (fp32_chains), so the signs are the
+// same bit for bit.  The four waves' class sums meet in LDS.
 template <int KS, int KT>
 __global__ __launch_bounds__(256) void k_classify_f32_few(EncodeArgs a)
 {
@@ -41,7 +41,8 @@ __global__ __launch_bounds__(256) void k_classify_f32_few(EncodeArgs a)
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
             cf[kt] = *(const v4i *)(a.ctab + ((int64_t)t * KT + kt) * 1024 + lane * 16);
-        v16f y{};
+        constexpr int KC = fp32_chains(C_F32, KS);
+        v16f y{}, y1{};                                    // chains of the even and odd K steps (KC == 2)
         constexpr int NB = KS / 8 < 8 ? KS / 8 : 8;        // pieces in flight
 #pragma unroll
         for (int j0 = 0; j0 < KS / 8; j0 += NB) {
@@ -57,9 +58,11 @@ __global__ __launch_bounds__(256) void k_classify_f32_few(EncodeArgs a)
                     const uint32_t d = (e == 0 ? w[j].x : e == 1 ? w[j].y : e == 2 ? w[j].z : w[j].w) << (8 * (1 - g));
                     const int s = 8 * (j0 + j) + 2 * e;
                     mma(y, __uint_as_float(((d << 16) & 0x80000000u) | 0x3F800000u), x[s]);
-                    mma(y, __uint_as_float((d & 0x80000000u) | 0x3F800000u), x[s + 1]);
+                    mma(KC == 2 ? y1 : y, __uint_as_float((d & 0x80000000u) | 0x3F800000u), x[s + 1]);
                 }
         }
+        if constexpr (KC == 2)
+            y += y1;
         v4i mb;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {

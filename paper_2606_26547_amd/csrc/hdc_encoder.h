@@ -496,18 +496,20 @@ struct Encoder {
     }
 
     // ------------------------------------------------------------ compute
-    // A single-tile wave of the register-staged loop alternates its K steps
-    // between KC = 2 accumulators, added in the epilogue, so that a product
-    // does not wait for the one before it (back to back the int8 32x32x32 form
-    // keeps its 32 cycles in one chain as well; with LDS waits between them
-    // two chains measured faster): exact
-    // for int32, and order-free for the float rungs on integer-valued
-    // features (sums below 2^24).  Register-staged kernels compiled for two
-    // waves per SIMD have no room for the second set and rely on the other
+    // Accumulator chains of a row tile, K step s in chain s % KC, added in the
+    // epilogue.  fp32 features round, so their order is that of the width
+    // (fp32_chains).  Integer features are exact in any order; there a
+    // single-tile wave alternates between two, so that a product does not wait
+    // for the one before it (back to back the int8 32x32x32 form keeps its 32
+    // cycles in one chain as well; with LDS waits between them two chains
+    // measured faster), unless it is register staged and compiled for two waves
+    // per SIMD, which has no room for the second set and relies on the other
     // wave instead; two query tiles are two chains already.
     // The split E4M3 type always has two: its high parts accumulate in the
     // first, its low parts in the second (|sums| < 2^24, exact).
-    static constexpr int KC = CT == C_FP8S ? 2 : (QT == 1 && (WAVES == 1 || DMA) && KS >= 2) ? 2 : 1;   // chains
+    static constexpr int KC = XF == 1         ? fp32_chains(CT, KS)
+                              : CT == C_FP8S ? 2
+                              : (QT == 1 && (WAVES == 1 || DMA) && KS >= 2) ? 2 : 1;
     typedef acc_t Parts[QT][KC];             // accumulators of one row tile
     static constexpr int kPhases = 4 * QT;   // epilogue phases (see Epilogue)
 

@@ -149,6 +149,13 @@ constexpr int kstep_of(int ct)
     return ct == C_I8 || ct == C_I8S ? 32 : (ct == C_FP8 || ct == C_FP8S || ct == C_FP8H) ? 64 : ct == C_BF16 ? 16 : 2;
 }
 
+// Accumulator chains of the fp32-feature encoders (K steps s mod chains, added
+// at the end).  fp32 features round as they are summed, so a query's signs
+// depend on this order: it is a rule of the compute type and the width alone
+// (ks K steps), the same in every kernel shape, encoding and classifying, split
+// or not.
+constexpr int fp32_chains(int ct, int ks) { return (ct == C_F32 && ks > 64) || (ct == C_FP8 && ks >= 2) ? 2 : 1; }
+
 // Compiled feature widths of the encoder (integer features / fp32
 // features); a launch uses the smallest width >= F.
 constexpr int kIntWidths[] = {64, 128, 192, 256, 320, 384, 512, 640, 832, 1024};
