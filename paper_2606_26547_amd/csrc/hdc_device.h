@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "hdc_internal.h"
+#include "hdc_ranges.h"
 
 namespace hdc {
 
@@ -213,26 +214,6 @@ __device__ __forceinline__ uint32_t keep_bytes(uint32_t w, int k0, int F)
     if (v >= 4) return w;
     if (v <= 0) return 0u;
     return w & ((1u << (8 * v)) - 1u);
-}
-
-// Dimensions of the set {start + j * stride < end} among d0 .. d0 + 31, as a
-// bit mask.
-__device__ __forceinline__ uint32_t set_mask(int d0, int start, int end, int stride)
-{
-    if (d0 >= end || d0 + 32 <= start)
-        return 0u;
-    if (stride == 1) {
-        const uint32_t lo = d0 < start ? ~0u << (start - d0) : ~0u;
-        const uint32_t hi = end - d0 < 32 ? (1u << (end - d0)) - 1u : ~0u;
-        return lo & hi;
-    }
-    int64_t d = start;
-    if (d0 > start)
-        d += (int64_t)((d0 - start + stride - 1) / stride) * stride;
-    uint32_t m = 0;
-    for (; d < d0 + 32 && d < end; d += stride)
-        m |= 1u << (int)(d - d0);
-    return m;
 }
 
 // popc[k] = number of -1 elements of class k over the set (0 for k >= K), by

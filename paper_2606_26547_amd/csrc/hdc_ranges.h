@@ -1,0 +1,33 @@
+// Index arithmetic of the kernels that has to hold over every size the entry
+// points take, apart from them so that the host can run it: plain functions of
+// integers.
+#pragma once
+
+#include <stdint.h>
+
+namespace hdc {
+
+// Dimensions of the set {start + j * stride < end} among d0 .. d0 + 31, as a
+// bit mask.  d0, start >= 0 and stride >= 1, any of them and end up to the
+// largest int: offsets from d0, unsigned, never pass 2^31 + 31.
+__host__ __device__ inline uint32_t set_mask(int d0, int start, int end, int stride)
+{
+    if (d0 >= end || start - d0 >= 32)
+        return 0u;
+    const uint32_t lim = end - d0 < 32 ? (uint32_t)(end - d0) : 32u;
+    uint32_t o = 0;   // the set's first dimension at or past d0
+    if (d0 < start) {
+        o = (uint32_t)(start - d0);
+    } else if (stride > 1) {
+        const uint32_t r = (uint32_t)(d0 - start) % (uint32_t)stride;
+        o = r ? (uint32_t)stride - r : 0u;
+    }
+    if (stride == 1)
+        return (lim < 32 ? (1u << lim) - 1u : ~0u) & ~0u << o;
+    uint32_t m = 0;
+    for (; o < lim; o += (uint32_t)stride)
+        m |= 1u << o;
+    return m;
+}
+
+}  // namespace hdc

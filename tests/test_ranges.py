@@ -1,0 +1,48 @@
+"""Index arithmetic of the kernels (csrc/hdc_ranges.h), compiled for the host
+and compared with its definition in unbounded integers, at the ends of what the
+entry points take."""
+import ctypes as C
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2606_26547_amd", "csrc")
+SOURCE = r"""
+#include "hdc_ranges.h"
+using namespace hdc;
+extern "C" uint32_t t_set_mask(int d0, int start, int end, int stride) { return set_mask(d0, start, end, stride); }
+"""
+MAX = 2 ** 31 - 1
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("ranges")
+    (d / "t.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-fPIC", "-shared", "-D__host__=", "-D__device__=",
+                    "-I", CSRC, "-o", str(d / "t.so"), str(d / "t.cpp")], check=True)
+    L = C.CDLL(str(d / "t.so"))
+    L.t_set_mask.restype = C.c_uint32
+    return L
+
+
+def _mask(d0, start, end, stride):
+    return sum(1 << i for i in range(32) if start <= d0 + i < end and (d0 + i - start) % stride == 0)
+
+
+def test_set_mask(lib):
+    r = random.Random(1)
+    strides = [1, 2, 3, 5, 31, 32, 33, 63, 64, 65, 1000, 10241, 2147418113, MAX - 10240, 2147483000, MAX - 1, MAX]
+    for stride in strides:
+        for start, end in [(0, 10240), (70, 10001), (1, 33), (31, 64), (5, 6), (64, 65536)]:
+            for d0 in list(range(0, 256, 32)) + [32 * r.randrange(2048) for _ in range(40)]:
+                assert lib.t_set_mask(d0, start, end, stride) == _mask(d0, start, end, stride), (d0, start, end, stride)
+        # sets that end at the largest int
+        for _ in range(200):
+            end = MAX - r.randrange(100)
+            start = r.choice([0, 1, r.randrange(end), end - 1 - r.randrange(90)])
+            d0 = r.choice([start // 32 * 32, end // 32 * 32, (end - 64) // 32 * 32, 32 * r.randrange(2 ** 26)])
+            assert lib.t_set_mask(d0, start, end, stride) == _mask(d0, start, end, stride), (d0, start, end, stride)

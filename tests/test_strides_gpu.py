@@ -1,0 +1,39 @@
+"""Dimension sets whose stride goes past the hypervector, up to the largest
+int, hold their first dimension only: every search gives what it gives on the
+set {start, start + 1, 1}, and equals the oracle's distances."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+MAX = 2 ** 31 - 1
+
+
+@pytest.mark.parametrize("stride", [2049, 2 ** 30, MAX - 2000, MAX])
+@pytest.mark.parametrize("start", [0, 70])
+def test_searches_of_one_dimension(start, stride):
+    from paper_2606_26547_amd import hdc
+    O.build()
+    print("[case] stride", start, stride, flush=True)
+    n, K, nbits = 300, 40, 2048
+    g = np.random.default_rng(start)
+    Q = g.integers(-2 ** 63, 2 ** 63, size=(n, nbits // 64), dtype=np.int64)
+    C = g.integers(-2 ** 63, 2 ** 63, size=(K, nbits // 64), dtype=np.int64)
+    acc = torch.as_tensor(g.integers(-300, 300, size=(K, nbits), dtype=np.int32)).cuda()
+    Qd, Cd = torch.as_tensor(Q).cuda(), torch.as_tensor(C).cuda()
+    wide, one = (start, nbits, stride), (start, start + 1, 1)
+    dref = O.hamming(Q.view(np.uint64), C.view(np.uint64), *one)
+    lab, mn, dist = hdc.HammingPrepared(Cd, *wide)(Qd, True, True)
+    assert np.array_equal(dist.cpu().numpy(), dref) and np.array_equal(lab.cpu().numpy(), dref.argmin(1))
+    assert np.array_equal(mn.cpu().numpy(), dref.min(1))
+    assert np.array_equal(hdc.hamming_argmin(Qd, Cd, *wide, with_dists=True)[2].cpu().numpy(), dref)
+    adc = (8, 1, -127, 128)
+    sref = O.adc_scores(Q.view(np.uint64), C.view(np.uint64), *one, *adc)
+    assert np.array_equal(hdc.AdcPrepared(Cd, *wide)(Qd, adc, with_scores=True)[2].cpu().numpy(), sref)
+    assert np.array_equal(hdc.adc_argmax(Qd, Cd, *wide, adc, with_scores=True)[2].cpu().numpy(), sref)
+    got = hdc.CosinePrepared(acc, *wide)(Qd, True, True)
+    ref = hdc.CosinePrepared(acc, *one)(Qd, True, True)
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))
