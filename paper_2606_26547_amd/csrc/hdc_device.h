@@ -222,11 +222,7 @@ __device__ __forceinline__ void class_popc(const uint64_t *__restrict__ C, int K
                                            int stride, int k, int32_t *__restrict__ popc)
 {
     __shared__ int part[256];
-    int s = 0;
-    if (k < K)
-        for (int h = 2 * (start >> 6) + threadIdx.x; 32 * h < end; h += 256)   // dwords
-            s += __popc((uint32_t)(C[k * ldc + (h >> 1)] >> (32 * (h & 1))) & set_mask(32 * h, start, end, stride));
-    part[threadIdx.x] = s;
+    part[threadIdx.x] = k < K ? set_popc(C + k * ldc, start, end, stride, threadIdx.x, 256) : 0;
     __syncthreads();
     for (int h = 128; h > 0; h >>= 1) {
         if (threadIdx.x < h)

@@ -30,4 +30,17 @@ __host__ __device__ inline uint32_t set_mask(int d0, int start, int end, int str
     return m;
 }
 
+// Set bits of the dimensions of {start + j * stride < end} in a packed row,
+// over its dwords first + k * step, first counted from the start's word: the
+// share of one of `step` threads.  (The dwords are counted, not their
+// dimensions: 32 * dword passes the largest int within a step of an end there.)
+__host__ __device__ inline int set_popc(const uint64_t *row, int start, int end, int stride, int first, int step)
+{
+    const int n = (end - 1) / 32 + 1;
+    int s = 0;
+    for (int h = 2 * (start >> 6) + first; h < n; h += step)
+        s += __builtin_popcount((uint32_t)(row[h >> 1] >> (32 * (h & 1))) & set_mask(32 * h, start, end, stride));
+    return s;
+}
+
 }  // namespace hdc

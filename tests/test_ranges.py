@@ -6,6 +6,7 @@ import os
 import random
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -14,6 +15,13 @@ SOURCE = r"""
 #include "hdc_ranges.h"
 using namespace hdc;
 extern "C" uint32_t t_set_mask(int d0, int start, int end, int stride) { return set_mask(d0, start, end, stride); }
+extern "C" int t_set_popc(const uint64_t *row, int start, int end, int stride, int threads)
+{
+    int s = 0;
+    for (int t = 0; t < threads; ++t)
+        s += set_popc(row, start, end, stride, t, threads);
+    return s;
+}
 """
 MAX = 2 ** 31 - 1
 
@@ -46,3 +54,19 @@ def test_set_mask(lib):
             start = r.choice([0, 1, r.randrange(end), end - 1 - r.randrange(90)])
             d0 = r.choice([start // 32 * 32, end // 32 * 32, (end - 64) // 32 * 32, 32 * r.randrange(2 ** 26)])
             assert lib.t_set_mask(d0, start, end, stride) == _mask(d0, start, end, stride), (d0, start, end, stride)
+
+
+@pytest.mark.timeout(60)
+@pytest.mark.parametrize("end", [1, 64, 10240, MAX - 8192, MAX - 31, MAX])
+def test_set_popc_ends(lib, end):
+    """Counts over the last dimensions of a row, up to the longest: every
+    thread's loop ends, within the row."""
+    first = max(0, end - 5000) // 64 * 64
+    W = (end + 63) // 64 - first // 64
+    row = np.random.default_rng(end).integers(-2 ** 63, 2 ** 63, size=W, dtype=np.int64)
+    bits = np.unpackbits(row.view(np.uint8), bitorder="little")
+    base = row.ctypes.data - first // 8          # dwords before the start's word are not read
+    for start in {first, min(first + 70, end - 1)}:
+        for stride in (1, 3, 4999, MAX):
+            want = int(bits[start - first:end - first:stride].sum())
+            assert lib.t_set_popc(C.c_void_p(base), start, end, stride, 256) == want, (start, stride)

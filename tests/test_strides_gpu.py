@@ -37,3 +37,16 @@ def test_searches_of_one_dimension(start, stride):
     got = hdc.CosinePrepared(acc, *wide)(Qd, True, True)
     ref = hdc.CosinePrepared(acc, *one)(Qd, True, True)
     assert all(torch.equal(a, b) for a, b in zip(got, ref))
+
+
+def test_prepare_counts_the_longest_rows():
+    """hdc_classify_prepare over a set that ends at the largest int: the class
+    counts (the workspace's last 128 integers) hold its two dimensions."""
+    from paper_2606_26547_amd import hdc
+    C = torch.zeros((2, 2 ** 25), dtype=torch.int64, device="cuda")
+    C[0, 0] = 1                                 # dimension 0
+    C[:, 2 ** 24] = 5                           # dimensions 2^30 and 2^30 + 2
+    C[1, -1] = -1                               # past the set
+    p = hdc.Prepared(C, MAX, "int8", stride=2 ** 30)
+    assert p.nd == 2
+    assert p.ws[-512:].view(torch.int32)[:3].tolist() == [2, 1, 0]
