@@ -59,8 +59,11 @@ __device__ __forceinline__ void lds_dma16(const void *addr, const lds_u8 *dst)
                  : "memory", "m0");
 }
 
-// Buffer descriptor of `bytes` bytes at base (raw, no stride).  Loads past
-// the end return zeros, so a buffer load needs no address clamp.
+// Buffer descriptor of `bytes` bytes at base (raw, no stride).  A load's
+// per-lane offset is checked against the size, dword by dword: what is past the
+// end is not read, and a buffer load needs no clamp of that offset.  (Whether a
+// scalar offset takes part in the check is not documented alike everywhere: the
+// kernels use none.)
 __device__ __forceinline__ v4i raw_buffer(const void *base, uint32_t bytes)
 {
     const uint64_t b = (uint64_t)(uintptr_t)base;
@@ -69,14 +72,12 @@ __device__ __forceinline__ v4i raw_buffer(const void *base, uint32_t bytes)
                __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
 }
 
-// lds_dma16 from a buffer at voff (per lane) + soff (uniform): no vector
-// arithmetic per load.
-__device__ __forceinline__ void lds_dma16(const v4i &buf, uint32_t voff, uint32_t soff, const lds_u8 *dst)
+// lds_dma16 from a buffer at voff (per lane).
+__device__ __forceinline__ void lds_dma16(const v4i &buf, uint32_t voff, const lds_u8 *dst)
 {
     const uint32_t m = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
-    const uint32_t so = __builtin_amdgcn_readfirstlane(soff);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(m), "v"(voff),
-                 "s"(buf), "s"(so)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(m), "v"(voff),
+                 "s"(buf)
                  : "memory", "m0");
 }
 

@@ -809,29 +809,30 @@ struct Encoder {
     // lane of a stage is row u / UPR, piece u % UPR; the skew unit and
     // pieces past the features re-read piece 0 (finite weights against zero
     // features), units past the chunk's rows land in slack.  Row r of chunk c
-    // is dimension S_{c*CH + r}; past the last dimension's last piece the
-    // buffer ends and loads give zeros (those rows' results are masked, or
-    // meet zero class bytes).  Byte offsets fit 32 bits: the projection holds at most 65536
-    // rows of at most 1024 + padding bytes.
+    // is dimension S_{c*CH + r}.  Each chunk is a buffer of its own, from its
+    // first row to the last dimension's last piece (row_window): offsets past
+    // it are refused by the load's range check, which covers the per-lane
+    // offset, so no address outside the projection is formed; those rows'
+    // results are masked, or meet zero class bytes.  (The chunk offset in the
+    // scalar offset instead, over one buffer of all rows, is not known to be
+    // checked.)  Byte offsets fit 32 bits: the projection is below 2^32 bytes.
     struct Loader {
         const EncodeArgs &a;
-        uint32_t off0[NIW];   // offset of load i in chunk 0
-        uint32_t cbytes;
-        v4i rows;             // buffer up to the last dimension's last piece
+        uint32_t off0[NIW];   // offset of load i in a chunk
+        const int8_t *first;  // row of the set's first dimension
+        uint32_t rstep, rbytes;
         int NC, lane, wave;
 
         __device__ __forceinline__ Loader(const EncodeArgs &a_, int NC_, int npc, int wave_, int lane_)
-            : a(a_), NC(NC_), lane(lane_), wave(wave_)
+            : a(a_), first(a_.P + (uint32_t)a_.s0 * (uint32_t)a_.ldp),
+              rstep((uint32_t)a_.stride * (uint32_t)a_.ldp), rbytes(16u * (uint32_t)npc), NC(NC_), lane(lane_),
+              wave(wave_)
         {
-            const uint32_t rstep = (uint32_t)a.stride * (uint32_t)a.ldp;
-            const uint32_t base = (uint32_t)a.s0 * (uint32_t)a.ldp;
-            cbytes = (uint32_t)CH * rstep;
-            rows = raw_buffer(a.P, base + (uint32_t)(a.nd - 1) * rstep + 16u * (uint32_t)npc);
 #pragma unroll
             for (int i = 0; i < NIW; ++i) {
                 const int u = piece(i) * 64 + lane;
                 const int r = u / UPR < CH ? u / UPR : CH - 1, p = u % UPR;
-                off0[i] = base + (uint32_t)r * rstep + 16u * (uint32_t)(p < npc ? p : 0);
+                off0[i] = (uint32_t)r * rstep + 16u * (uint32_t)(p < npc ? p : 0);
             }
         }
         // KiB of the stage that load i of this wave fills
@@ -839,15 +840,16 @@ struct Encoder {
         {
             return i * kWaves + kWaves <= NU || i * kWaves + wave < NU ? i * kWaves + wave : NU - 1;
         }
-        // Chunk c's offset, or the last chunk's from there on (the class table
-        // holds a whole number of chunks, zero rows past nd), as scalars.
+        // Chunk c, or the last chunk from there on (the class table holds a
+        // whole number of chunks, zero rows past nd), as scalars.
         struct Chunk {
-            uint32_t cc, off;
+            uint32_t cc;
+            v4i rows;
         };
         __device__ __forceinline__ Chunk chunk(int c) const
         {
-            const uint32_t cc = (uint32_t)(c < NC ? c : NC - 1);
-            return Chunk{cc, cc * cbytes};
+            const RowWindow w = row_window(c, CH, a.nd, rstep, rbytes);
+            return Chunk{(uint32_t)(c < NC ? c : NC - 1), raw_buffer(first + w.off, w.bytes)};
         }
         // Load i (< NIW + NCW) of a chunk: the projection rows, then the class
         // fragments (wave w loads class tiles (w + 4j) % NCT; duplicate tiles
@@ -855,7 +857,7 @@ struct Encoder {
         __device__ __forceinline__ void issue(int i, const Chunk &c, lds_u8 *stage, lds_u8 *lcls) const
         {
             if (i < NIW) {
-                lds_dma16(rows, off0[i], c.off, stage + piece(i) * 1024);
+                lds_dma16(c.rows, off0[i], stage + piece(i) * 1024);
             } else if constexpr (MODE == M_CLASSIFY) {
                 const int tile = (wave + kWaves * (i - NIW)) % NCT;   // rt * KT + kt
                 lds_dma16(a.ctab + (c.cc * NCT + tile) * 1024, (uint32_t)(lane * 16), lcls + tile * 1024);

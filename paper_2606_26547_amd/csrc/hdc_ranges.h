@@ -43,4 +43,22 @@ __host__ __device__ inline int set_popc(const uint64_t *row, int start, int end,
     return s;
 }
 
+// The projection rows a direct-staged kernel reads for a chunk of ch dimensions:
+// offset of the chunk's first row from the row of the set's first dimension,
+// and the bytes from there to the end of the last dimension's row.  rstep is
+// the offset from one dimension's row to the next, row_bytes what is read of a
+// row.  A chunk past the last dimension (the partner of an odd last one, or one
+// loaded ahead) gives the last chunk that holds one.  A buffer of `bytes` at
+// `off` thus lies within the projection whatever the offsets into it, which are
+// checked against its size (a chunk's rows past the last dimension are past its
+// end, or wrap to others of its rows).
+struct RowWindow {
+    uint32_t off, bytes;
+};
+__host__ __device__ inline RowWindow row_window(int c, int ch, int nd, uint32_t rstep, uint32_t row_bytes)
+{
+    const int last = (nd - 1) / ch, cc = c < last ? c : last;
+    return RowWindow{(uint32_t)(cc * ch) * rstep, (uint32_t)(nd - 1 - cc * ch) * rstep + row_bytes};
+}
+
 }  // namespace hdc

@@ -15,6 +15,12 @@ SOURCE = r"""
 #include "hdc_ranges.h"
 using namespace hdc;
 extern "C" uint32_t t_set_mask(int d0, int start, int end, int stride) { return set_mask(d0, start, end, stride); }
+extern "C" void t_row_window(int c, int ch, int nd, uint32_t rstep, uint32_t row_bytes, uint32_t *out)
+{
+    const RowWindow w = row_window(c, ch, nd, rstep, row_bytes);
+    out[0] = w.off;
+    out[1] = w.bytes;
+}
 extern "C" int t_set_popc(const uint64_t *row, int start, int end, int stride, int threads)
 {
     int s = 0;
@@ -70,3 +76,33 @@ def test_set_popc_ends(lib, end):
         for stride in (1, 3, 4999, MAX):
             want = int(bits[start - first:end - first:stride].sum())
             assert lib.t_set_popc(C.c_void_p(base), start, end, stride, 256) == want, (start, stride)
+
+
+def test_row_window(lib):
+    """The buffer of every chunk a direct-staged kernel loads (chunks past the
+    last one among them) lies within the projection, so no offset its range
+    check lets through reaches past it; the rows that count are all in it, at
+    their place."""
+    r = random.Random(2)
+    out = (C.c_uint32 * 2)()
+    for i in range(4000):
+        F = r.choice([1, 64, 65, 617, 640, 641, 1000, 1024])
+        ldp = (F + 63) // 64 * 64 + 16 * r.choice([0, 0, 4, 1000])
+        D = r.choice([r.randrange(1, 200), r.randrange(200, 20000), (2 ** 32 - 1 - ldp) // ldp])
+        start = r.choice([0, 0, r.randrange(D)])
+        end = D if r.random() < 0.5 else r.randrange(start + 1, D + 1)
+        stride = r.choice([1, 1, 2, 3, 17, r.randrange(1, 2 * D), MAX])
+        nd = (end - start + stride - 1) // stride
+        rb = (F + 31) // 32 * 32
+        base, rstep = start * ldp, stride * ldp % 2 ** 32
+        for ch in (32, 64):
+            chunks = (nd + 63) // 64 * (64 // ch)             # whole 64-dimension words
+            for c in {0, 1, nd // ch - 1, nd // ch, chunks - 2, chunks - 1, chunks, chunks + 6}:
+                if c < 0:
+                    continue
+                lib.t_row_window(c, ch, nd, rstep, rb, out)
+                off, size = out
+                assert size >= rb and base + off + size <= (D - 1) * ldp + rb, (F, ldp, D, start, end, stride, ch, c)
+                for d in range(c * ch, min((c + 1) * ch, nd)):
+                    at = (d - c * ch) * rstep                 # the lane's offset
+                    assert at < 2 ** 32 and at + rb <= size and base + off + at == (start + d * stride) * ldp

@@ -50,3 +50,24 @@ def test_prepare_counts_the_longest_rows():
     p = hdc.Prepared(C, MAX, "int8", stride=2 ** 30)
     assert p.nd == 2
     assert p.ws[-512:].view(torch.int32)[:3].tolist() == [2, 1, 0]
+
+
+@pytest.mark.parametrize("F, xt, compute", [(64, "int8", "int8"), (617, "int8", "int8"), (784, "uint8", "int8"),
+                                            (641, "int8", "fp8"), (300, "uint8", "fp8split"), (100, "fp32", "fp32")])
+@pytest.mark.parametrize("stride", [700, MAX - 2000, MAX])
+def test_encode_and_classify_one_dimension(F, xt, compute, stride):
+    from paper_2606_26547_amd import datagen as dg
+    from paper_2606_26547_amd import hdc
+    print("[case] encode stride", F, xt, compute, stride, flush=True)
+    n, D, K = 70, 700, 5
+    X, P = dg.random_case(n, F, D, xt, seed=F)
+    C = np.random.default_rng(F).integers(0, 2 ** 63, size=(K, 11), dtype=np.int64)
+    C[:, -1] &= (1 << (D % 64)) - 1
+    Xd, Pd, Cd = hdc.pad_cols(X), hdc.pad_cols(P), torch.as_tensor(C).cuda()
+    for start in (0, 699):
+        one = (start, start + 1, 1)
+        H = hdc.encode(Xd, F, Pd, D, compute, start, D, stride)
+        assert np.array_equal(H.cpu().numpy().view(np.uint64), O.encode(X, P, compute, *one))
+        lab, dists = hdc.classify(Xd, F, Pd, D, Cd, compute, start, D, stride, with_dists=True)
+        lref, dref = O.classify(X, P, C.view(np.uint64), compute, *one, with_dists=True)
+        assert np.array_equal(dists.cpu().numpy(), dref) and np.array_equal(lab.cpu().numpy(), lref)
