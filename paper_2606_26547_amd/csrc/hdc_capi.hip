@@ -9,6 +9,7 @@ namespace hdc {
 hipError_t launch_encode_i8(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
 hipError_t launch_encode_u8(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
 hipError_t launch_encode_fp8(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
+hipError_t launch_encode_fp8f(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
 hipError_t launch_encode_bf16(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
 hipError_t launch_encode_f32(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
 hipError_t launch_encode_fp8s(const EncodeArgs &a, int mode, Tile tile, hipStream_t st);
@@ -26,7 +27,7 @@ hipError_t launch_encode(const EncodeArgs &a, int compute, int mode, Tile tile, 
     }
     switch (compute) {
     case C_I8: return a.x_type == X_UINT8 ? launch_encode_u8(a, mode, tile, st) : launch_encode_i8(a, mode, tile, st);
-    case C_FP8: return launch_encode_fp8(a, mode, tile, st);
+    case C_FP8: return a.x_type == X_FP32 ? launch_encode_fp8f(a, mode, tile, st) : launch_encode_fp8(a, mode, tile, st);
     case C_BF16: return launch_encode_bf16(a, mode, tile, st);
     case C_F32: return launch_encode_f32(a, mode, tile, st);
     case C_FP8S: return launch_encode_fp8s(a, mode, tile, st);
