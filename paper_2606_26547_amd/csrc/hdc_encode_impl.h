@@ -19,7 +19,7 @@ namespace hdc {
 // finishes.
 template <int CT, int XF, int QT, int KS, int KT, int MODE, bool DMA, int RT, int SRC>
 __global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(Encoder<CT, XF, QT, KS, KT, MODE, 0, DMA, RT, SRC>::WAVES)))
+__attribute__((amdgpu_waves_per_eu(Encoder<CT, XF, QT, KS, KT, MODE, 0, DMA, RT, SRC>::REGW)))
 void k_encode(EncodeArgs a)
 {
     typedef Encoder<CT, XF, QT, KS, KT, MODE, 0, DMA, RT, SRC> E;
@@ -177,14 +177,22 @@ static hipError_t launch_one(const EncodeArgs &a, hipStream_t st)
 // publishes the column sums).  One query tile where the registers hold no
 // second beside the accumulators: four class tiles from 833 features, and the
 // split E4M3 type, whose query operand is twice as wide (there each fragment
-// feeds two MFMAs already).
+// feeds two MFMAs already); and the shifted E4M3 type at up to 320 features and
+// two class tiles, where two take 297 registers, one wave per SIMD, and the last
+// round of workgroups costs a whole one (200000 x 300, 4096 dimensions, 40
+// classes: 298 us with two, 259 with one; 65536: 75 and 79).
+// Few query blocks take one query tile (few_blocks), except the shifted int8
+// type, whose start values need the registers of one wave per SIMD (20000 x
+// 617, 8192 dimensions on the shifted E4M3 form without scratch: 190 us with
+// two, 144 with one).
 template <int CT, int KS, int KT, int MODE, int SRC>
 static hipError_t launch_direct(const EncodeArgs &a, hipStream_t st)
 {
     constexpr int W = KS * Tr<CT>::KSTEP;
-    constexpr int QT = CT == C_FP8S || (W > 832 && KT == 4) ? 1 : 2;
-    constexpr int RT = W > 640 || (CT == C_I8 && SRC == W_ALT) ? 1 : 2;
-    if (QT == 2 && !a.poff && few_blocks(a, MODE))
+    constexpr bool SHIFT1 = CT == C_FP8 && SRC == W_ROWS && W <= 320 && KT == 2;
+    constexpr int QT = CT == C_FP8S || (W > 832 && KT == 4) || SHIFT1 ? 1 : 2;
+    constexpr int RT = QT == 1 || W > 640 || (CT == C_I8 && SRC == W_ALT) ? 1 : 2;
+    if (QT == 2 && (CT == C_FP8 || !a.poff) && few_blocks(a, MODE))
         return launch_one<CT, 0, 1, KS, KT, MODE, true, 1, SRC>(a, st);
     return launch_one<CT, 0, QT, KS, KT, MODE, true, RT, SRC>(a, st);
 }

@@ -88,6 +88,11 @@ struct Encoder {
                                         ((CT == C_I8 && KS <= 20) || (CT == C_BF16 && KS <= 16) ||
                                          (CT == C_F32 && KS <= 64))) ? 2 : 1);
     static constexpr int QPB = QPW * kWaves;               // queries per workgroup
+    // Waves per SIMD the registers are kept to: the E4M3 path up to 320 features
+    // and two class tiles (the shifted one: one) is near two already (200000 x
+    // 300, 4096 dimensions, 40 classes: 375 us with 259 registers, 281 with 256;
+    // shifted, 10 classes: 275 with 262, 212 with 254).
+    static constexpr int REGW = DMA && CT == C_FP8 && QT == 2 && KS <= 5 && KT <= (SRC == W_ROWS ? 1 : 2) ? 2 : WAVES;
 
     // ---------------------------------------------------------------- X
     // One K step of byte features (16 bytes at k0 on the int8 path, 32 on
@@ -352,10 +357,10 @@ struct Encoder {
     // the sum of its rounded features from the matrix cores (an all -1.0
     // operand against the query fragments; integers below 2^24, exact in
     // fp32).  Only the shapes the shifted types launch take the shifted
-    // projection (two query tiles, shift_tile / shift8_tile); the others
+    // projection (shift_tile with two query tiles, shift8_tile); the others
     // start from 0.
-    static constexpr bool kShift = DMA && SRC == W_ROWS && QT == 2 && ((CT == C_I8 && shift_tile(KS, KT)) ||
-                                                                       (CT == C_FP8 && shift8_tile(KS, KT)));
+    static constexpr bool kShift = DMA && SRC == W_ROWS && ((QT == 2 && CT == C_I8 && shift_tile(KS, KT)) ||
+                                                            (CT == C_FP8 && shift8_tile(KS, KT)));
     static __device__ __forceinline__ void shift_start(acc_t (&x0)[QT], const xfrag (&xr)[QT][KS], int poff)
     {
 #pragma unroll
