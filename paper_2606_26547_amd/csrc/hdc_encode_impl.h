@@ -77,18 +77,18 @@ void k_encode(EncodeArgs a)
 // queries are latency bound and go 8 to a workgroup; from 1024 on, 32 (whole
 // lines; 1559 queries, 26 classes, 32 splits: 1.5 us less than with 8).  The
 // first smallest distance wins, as in Encoder::finish: the minimum of
-// (distance, class) packed in one integer (distances are at most 65536,
-// classes below 128).  The distances go out through LDS, whole rows at once.
+// (distance, class) packed in one 64-bit integer (a projection may have over
+// 2^24 dimensions).  The distances go out through LDS, whole rows at once.
 template <int QB>
 static __global__ __launch_bounds__(1024) void k_split_argmin(EncodeArgs a, int Z)
 {
     constexpr int ZL = 64 / QB;
-    __shared__ int best[16][QB];
+    __shared__ int64_t best[16][QB];
     __shared__ int32_t dist[QB * kMaxK];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ql = lane % QB, zl = lane / QB;
     const int64_t q0 = (int64_t)blockIdx.x * QB, q = q0 + ql, qc = q < a.n ? q : a.n - 1;
     const int64_t zs = a.n * a.K;
-    int m = 0x7fffffff;
+    int64_t m = INT64_MAX;
     for (int k = wave; k < a.K; k += 16) {
         const int32_t *p = a.part + k * a.n + qc;
         int s = 0;
@@ -107,7 +107,7 @@ static __global__ __launch_bounds__(1024) void k_split_argmin(EncodeArgs a, int 
         const int d = a.cpop[k] - s;
         if (zl == 0 && a.dists)
             dist[ql * a.K + k] = d;
-        const int key = d * 128 + k;
+        const int64_t key = (int64_t)d * 128 + k;
         m = key < m ? key : m;
     }
     if (zl == 0)
@@ -122,7 +122,7 @@ static __global__ __launch_bounds__(1024) void k_split_argmin(EncodeArgs a, int 
 #pragma unroll
         for (int w = 1; w < 16; ++w)
             m = best[w][threadIdx.x] < m ? best[w][threadIdx.x] : m;
-        a.labels[q] = m % 128;
+        a.labels[q] = (int32_t)(m % 128);
     }
 }
 
