@@ -57,40 +57,44 @@ hipError_t launch_gather_cols(const void *X, int elem, int64_t n, int64_t ldx, i
 //
 // Streaming bound: a thread takes one feature of kLqRows rows, all its loads
 // in flight, the range read once (one element per thread, with a 64-bit
-// division to find it, took 41 us for 32768 x 617; the bytes take 25).
+// division to find it, took 41 us for 32768 x 617; the bytes take 25).  The
+// grid's limits are covered by striding.
 constexpr int kLqRows = 8;
 __global__ __launch_bounds__(256) void k_level_quantize(const float *__restrict__ X, int64_t n, int F, int64_t ldx,
                                                         const float *__restrict__ lo, const float *__restrict__ hi,
                                                         int L, uint16_t *__restrict__ lev, int64_t ldl)
 {
-    const int f = blockIdx.y * 64 + (threadIdx.x & 63);
-    if (f >= F)
-        return;
-    const int64_t i0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kLqRows;
-    const float l0 = lo[f], w = __fsub_rn(hi[f], l0);
-    float x[kLqRows];
+    constexpr int FW = 64, RW = 256 / FW;
+    for (int64_t f = (int64_t)blockIdx.y * FW + threadIdx.x % FW; f < F; f += (int64_t)gridDim.y * FW) {
+        const float l0 = lo[f], w = __fsub_rn(hi[f], l0);
+        for (int64_t i0 = (int64_t)blockIdx.x * (RW * kLqRows) + threadIdx.x / FW; i0 < n;
+             i0 += (int64_t)gridDim.x * (RW * kLqRows)) {
+            float x[kLqRows];
 #pragma unroll
-    for (int r = 0; r < kLqRows; ++r)
-        x[r] = X[(i0 + r < n ? i0 + r : n - 1) * ldx + f];
+            for (int r = 0; r < kLqRows; ++r)
+                x[r] = X[(i0 + r * RW < n ? i0 + r * RW : n - 1) * ldx + f];
 #pragma unroll
-    for (int r = 0; r < kLqRows; ++r) {
-        const float v = __fdiv_rn(__fmul_rn(__fsub_rn(x[r], l0), (float)L), w);
-        int level;
-        if (!(w > 0.0f) || !(v > 0.0f))
-            level = 0;
-        else if (v >= (float)(L - 1))
-            level = L - 1;
-        else
-            level = (int)floorf(v);
-        if (i0 + r < n)
-            lev[(i0 + r) * ldl + f] = (uint16_t)level;
+            for (int r = 0; r < kLqRows; ++r) {
+                const float v = __fdiv_rn(__fmul_rn(__fsub_rn(x[r], l0), (float)L), w);
+                int level;
+                if (!(w > 0.0f) || !(v > 0.0f))
+                    level = 0;
+                else if (v >= (float)(L - 1))
+                    level = L - 1;
+                else
+                    level = (int)floorf(v);
+                if (i0 + r * RW < n)
+                    lev[(i0 + r * RW) * ldl + f] = (uint16_t)level;
+            }
+        }
     }
 }
 
 hipError_t launch_level_quantize(const float *X, int64_t n, int F, int64_t ldx, const float *lo, const float *hi,
                                  int L, uint16_t *lev, int64_t ldl, hipStream_t st)
 {
-    const dim3 grid((unsigned)((n + 4 * kLqRows - 1) / (4 * kLqRows)), (unsigned)((F + 63) / 64));
+    const int64_t x = (n + 4 * kLqRows - 1) / (4 * kLqRows), y = ((int64_t)F + 63) / 64;
+    const dim3 grid((unsigned)(x < (1 << 22) ? x : 1 << 22), (unsigned)(y < 65535 ? y : 65535));
     hipLaunchKernelGGL(k_level_quantize, grid, dim3(256), 0, st, X, n, F, ldx, lo, hi, L, lev, ldl);
     return hipGetLastError();
 }
