@@ -57,14 +57,17 @@ hipError_t launch_gather_cols(const void *X, int elem, int64_t n, int64_t ldx, i
 //
 // Streaming bound: a thread takes one feature of kLqRows rows, all its loads
 // in flight, the range read once (one element per thread, with a 64-bit
-// division to find it, took 41 us for 32768 x 617; the bytes take 25).  The
-// grid's limits are covered by striding.
+// division to find it, took 41 us for 32768 x 617; the bytes take 25).  A
+// workgroup's lanes cover FW features of 256 / FW rows: 64, or for narrow rows
+// the power of two that holds them, so that no lane is without a feature (4194304
+// x 1: 197 us with 64, 17.6 so).  The grid's limits are covered by striding.
 constexpr int kLqRows = 8;
+template <int FW>
 __global__ __launch_bounds__(256) void k_level_quantize(const float *__restrict__ X, int64_t n, int F, int64_t ldx,
                                                         const float *__restrict__ lo, const float *__restrict__ hi,
                                                         int L, uint16_t *__restrict__ lev, int64_t ldl)
 {
-    constexpr int FW = 64, RW = 256 / FW;
+    constexpr int RW = 256 / FW;
     for (int64_t f = (int64_t)blockIdx.y * FW + threadIdx.x % FW; f < F; f += (int64_t)gridDim.y * FW) {
         const float l0 = lo[f], w = __fsub_rn(hi[f], l0);
         for (int64_t i0 = (int64_t)blockIdx.x * (RW * kLqRows) + threadIdx.x / FW; i0 < n;
@@ -90,12 +93,33 @@ __global__ __launch_bounds__(256) void k_level_quantize(const float *__restrict_
     }
 }
 
+template <int FW>
+static void launch_lq(const float *X, int64_t n, int F, int64_t ldx, const float *lo, const float *hi, int L,
+                      uint16_t *lev, int64_t ldl, hipStream_t st)
+{
+    constexpr int64_t rows = 256 / FW * kLqRows;
+    const int64_t x = (n + rows - 1) / rows, y = ((int64_t)F + FW - 1) / FW;
+    const dim3 grid((unsigned)(x < (1 << 22) ? x : 1 << 22), (unsigned)(y < 65535 ? y : 65535));
+    hipLaunchKernelGGL(k_level_quantize<FW>, grid, dim3(256), 0, st, X, n, F, ldx, lo, hi, L, lev, ldl);
+}
+
 hipError_t launch_level_quantize(const float *X, int64_t n, int F, int64_t ldx, const float *lo, const float *hi,
                                  int L, uint16_t *lev, int64_t ldl, hipStream_t st)
 {
-    const int64_t x = (n + 4 * kLqRows - 1) / (4 * kLqRows), y = ((int64_t)F + 63) / 64;
-    const dim3 grid((unsigned)(x < (1 << 22) ? x : 1 << 22), (unsigned)(y < 65535 ? y : 65535));
-    hipLaunchKernelGGL(k_level_quantize, grid, dim3(256), 0, st, X, n, F, ldx, lo, hi, L, lev, ldl);
+    if (F <= 1)
+        launch_lq<1>(X, n, F, ldx, lo, hi, L, lev, ldl, st);
+    else if (F <= 2)
+        launch_lq<2>(X, n, F, ldx, lo, hi, L, lev, ldl, st);
+    else if (F <= 4)
+        launch_lq<4>(X, n, F, ldx, lo, hi, L, lev, ldl, st);
+    else if (F <= 8)
+        launch_lq<8>(X, n, F, ldx, lo, hi, L, lev, ldl, st);
+    else if (F <= 16)
+        launch_lq<16>(X, n, F, ldx, lo, hi, L, lev, ldl, st);
+    else if (F <= 32)
+        launch_lq<32>(X, n, F, ldx, lo, hi, L, lev, ldl, st);
+    else
+        launch_lq<64>(X, n, F, ldx, lo, hi, L, lev, ldl, st);
     return hipGetLastError();
 }
 
