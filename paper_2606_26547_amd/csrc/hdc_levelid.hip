@@ -404,9 +404,14 @@ static hipError_t launch_level_id_rows(const uint16_t *lev, int64_t n, int F, in
     if (attr != hipSuccess)
         return attr;
     const int W = (D + 63) / 64;
-    const dim3 grid((unsigned)((n + S::ROWS - 1) / S::ROWS), (unsigned)((W + S::W - 1) / S::W));
-    hipLaunchKernelGGL((k_level_id<LPR, R>), grid, dim3(256), S::lds(L), st, lev, n, F, ldl, ID, ldid, LV, L, ldlv, D,
-                       H, ldh);
+    // a grid's first dimension takes 2^24 workgroups
+    constexpr int64_t step = (int64_t)S::ROWS << 22;
+    for (int64_t i = 0; i < n; i += step) {
+        const int64_t m = n - i < step ? n - i : step;
+        const dim3 grid((unsigned)((m + S::ROWS - 1) / S::ROWS), (unsigned)((W + S::W - 1) / S::W));
+        hipLaunchKernelGGL((k_level_id<LPR, R>), grid, dim3(256), S::lds(L), st, lev + i * ldl, m, F, ldl, ID, ldid, LV,
+                           L, ldlv, D, H + i * ldh, ldh);
+    }
     return hipGetLastError();
 }
 
