@@ -291,13 +291,8 @@ void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl,
         *(lds_u64 *)(slv + r * S::PITCH + w * 8) = r < L && w < nw ? LV[(int64_t)r * ldlv + w0 + w] : 0;
     }
     const int wl = lane % LPR;                             // this lane's words: w0 + 2 wl, + 1
-    const int64_t row0 = (int64_t)blockIdx.x * S::ROWS + wave * (S::RPW * R) + lane / LPR;
+    int64_t row0 = (int64_t)blockIdx.x * S::ROWS + wave * (S::RPW * R) + lane / LPR;
     const uint16_t *lrow[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t row = row0 + r * S::RPW;
-        lrow[r] = lev + (row < n ? row : n - 1) * ldl;
-    }
     // eight levels of each row from feature f on (past the row: its first)
     auto lev_load = [&](uint4 (&l)[R], int f) {
 #pragma unroll
@@ -316,15 +311,22 @@ void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl,
         }
     };
     LidCounter cnt[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-        cnt[r].clear();
     const uint32_t lbase = (uint32_t)(uintptr_t)slv + wl * 16;
     const uint32_t lmax = (uint32_t)(L - 1) * 0x10001u;
     uint4 lv[2][R];
     v4i id[2][4];
-    lev_load(lv[0], 0);
-    id_load(id[0], 0);
+    // a pass over ROWS rows starts
+    auto start = [&]() {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t row = row0 + r * S::RPW;
+            lrow[r] = lev + (row < n ? row : n - 1) * ldl;
+            cnt[r].clear();
+        }
+        lev_load(lv[0], 0);
+        id_load(id[0], 0);
+    };
+    start();
     __syncthreads();
     // one block of 32 features; TAIL: features past F take the zero row, and
     // groups past it only pass the carries on (8231 rows, 65 features, 7530
@@ -367,28 +369,35 @@ void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl,
             }
         }
     };
-    int f0 = 0;
-    for (; f0 + kLidFeat <= F; f0 += kLidFeat)
-        block(f0, std::integral_constant<bool, false>{});
-    if (f0 < F)
-        block(f0, std::integral_constant<bool, true>{});
+    for (int64_t rb = blockIdx.x;;) {
+        int f0 = 0;
+        for (; f0 + kLidFeat <= F; f0 += kLidFeat)
+            block(f0, std::integral_constant<bool, false>{});
+        if (f0 < F)
+            block(f0, std::integral_constant<bool, true>{});
 
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t row = row0 + r * S::RPW;
-        if (row >= n)
-            continue;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int w = w0 + 2 * wl + i;
-            if (w >= W)
+        for (int r = 0; r < R; ++r) {
+            const int64_t row = row0 + r * S::RPW;
+            if (row >= n)
                 continue;
-            uint64_t v = (uint64_t)cnt[r].greater(2 * i, (uint32_t)F >> 1) |
-                         ((uint64_t)cnt[r].greater(2 * i + 1, (uint32_t)F >> 1) << 32);
-            if (w == W - 1 && (D & 63))
-                v &= (1ull << (D & 63)) - 1ull;
-            H[row * ldh + w] = v;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int w = w0 + 2 * wl + i;
+                if (w >= W)
+                    continue;
+                uint64_t v = (uint64_t)cnt[r].greater(2 * i, (uint32_t)F >> 1) |
+                             ((uint64_t)cnt[r].greater(2 * i + 1, (uint32_t)F >> 1) << 32);
+                if (w == W - 1 && (D & 63))
+                    v &= (1ull << (D & 63)) - 1ull;
+                H[row * ldh + w] = v;
+            }
         }
+        rb += gridDim.x;
+        if (rb * S::ROWS >= n)
+            break;
+        row0 += (int64_t)gridDim.x * S::ROWS;
+        start();
     }
 }
 
@@ -404,14 +413,15 @@ static hipError_t launch_level_id_rows(const uint16_t *lev, int64_t n, int F, in
     if (attr != hipSuccess)
         return attr;
     const int W = (D + 63) / 64;
-    // a grid's first dimension takes 2^24 workgroups
-    constexpr int64_t step = (int64_t)S::ROWS << 22;
-    for (int64_t i = 0; i < n; i += step) {
-        const int64_t m = n - i < step ? n - i : step;
-        const dim3 grid((unsigned)((m + S::ROWS - 1) / S::ROWS), (unsigned)((W + S::W - 1) / S::W));
-        hipLaunchKernelGGL((k_level_id<LPR, R>), grid, dim3(256), S::lds(L), st, lev + i * ldl, m, F, ldl, ID, ldid, LV,
-                           L, ldlv, D, H + i * ldh, ldh);
-    }
+    // Where staging the levels costs like a quarter of a pass or more, a
+    // workgroup takes several passes of rows, as many as leave two workgroups per
+    // CU (20000 rows x 20 features, 256 levels, 4096 dimensions: 42 us with one
+    // pass, 23.6 so).  Else one pass, up to 2^22 workgroups (a grid takes 2^24).
+    const int64_t blocks = (n + S::ROWS - 1) / S::ROWS, wins = (W + S::W - 1) / S::W;
+    const int64_t most = (int64_t)(L + 1) * S::W > 64ll * F * R ? (512 + wins - 1) / wins : 1 << 22;
+    const dim3 grid((unsigned)(blocks < most ? blocks : most), (unsigned)wins);
+    hipLaunchKernelGGL((k_level_id<LPR, R>), grid, dim3(256), S::lds(L), st, lev, n, F, ldl, ID, ldid, LV, L, ldlv, D,
+                       H, ldh);
     return hipGetLastError();
 }
 
