@@ -216,6 +216,12 @@ struct LidCounter {
             asm volatile("" : "+v"(fours[0]), "+v"(fours[1]), "+v"(fours[2]), "+v"(fours[3]));
         __builtin_amdgcn_sched_barrier(0);
     }
+    // plane p of dword k: the counts' bit of weight 2^p
+    __device__ __forceinline__ uint32_t &plane(int p, int k)
+    {
+        return p == 0 ? ones[k] : p == 1 ? twos[k] : p == 2 ? fours[k] : p == 3 ? eights[k] : p == 4 ? sixteens[k]
+                                                                                                     : big[p - 5][k];
+    }
     // bit set where count > T
     __device__ __forceinline__ uint32_t greater(int k, uint32_t T) const
     {
@@ -250,12 +256,22 @@ struct LidCounter {
 // quantiser: 1372 us on one word and row per lane, 792 so, the vector units
 // busy four fifths of it; 984 / 931 with one / three rows per lane, 919 with
 // the identity words through LDS.
-template <int LPR, int R> struct LidShape {
+//
+// Few rows (FS): the four waves of a workgroup take a quarter of the features
+// each of the same rows, and their counts meet in LDS.  A wave alone on its SIMD
+// takes 70 ns a feature whatever its rows, so ten rows left it at 43 us (one word
+// per lane: 32); split, 17 (617 features, 128 levels, 10240 dimensions).
+template <int LPR, int R, bool FS = false> struct LidShape {
     static constexpr int W = 2 * LPR;                      // words per window
     static constexpr int RPW = 64 / LPR;                   // rows per wave at a time
-    static constexpr int ROWS = kWaves * RPW * R;      // rows per workgroup
+    static constexpr int ROWS = (FS ? 1 : kWaves) * RPW * R;   // rows per workgroup
     static constexpr int PITCH = W * 8 + (LPR == 16 ? 0 : 16);   // bytes per level row in LDS
-    static size_t lds(int L) { return (size_t)(L + 1) * PITCH; }
+    static constexpr int SUMS = FS ? (kWaves - 1) * R * (5 + kLidBig) * 4 * 64 * 4 : 0;   // other waves' counts
+    static size_t lds(int L)
+    {
+        const size_t levels = (size_t)(L + 1) * PITCH;
+        return levels > SUMS ? levels : SUMS;
+    }
 };
 
 // base + pitch * the low (HI: high) half of the level pair
@@ -269,13 +285,13 @@ template <bool HI> __device__ __forceinline__ uint32_t lid_addr(uint32_t pair, u
     return r;
 }
 
-template <int LPR, int R>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(R == 1 ? 3 : 2)))
+template <int LPR, int R, bool FS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FS ? 1 : R == 1 ? 3 : 2)))
 void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl, const uint64_t *__restrict__ ID,
                 int64_t ldid, const uint64_t *__restrict__ LV, int L, int64_t ldlv, int D, uint64_t *__restrict__ H,
                 int64_t ldh)
 {
-    typedef LidShape<LPR, R> S;
+    typedef LidShape<LPR, R, FS> S;
     typedef unsigned short v2us __attribute__((ext_vector_type(2)));
     extern __shared__ __align__(16) uint8_t lid_lds[];
     lds_u8 *slv = (lds_u8 *)lid_lds;
@@ -291,7 +307,10 @@ void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl,
         *(lds_u64 *)(slv + r * S::PITCH + w * 8) = r < L && w < nw ? LV[(int64_t)r * ldlv + w0 + w] : 0;
     }
     const int wl = lane % LPR;                             // this lane's words: w0 + 2 wl, + 1
-    int64_t row0 = (int64_t)blockIdx.x * S::ROWS + wave * (S::RPW * R) + lane / LPR;
+    int64_t row0 = (int64_t)blockIdx.x * S::ROWS + (FS ? 0 : wave * (S::RPW * R)) + lane / LPR;
+    // this wave's features: all, or (FS) whole blocks of 32
+    const int per = FS ? (F + kLidFeat * kWaves - 1) / (kLidFeat * kWaves) * kLidFeat : F;
+    const int fb = FS ? __builtin_amdgcn_readfirstlane(wave) * per : 0, fe = fb + per < F ? fb + per : F;
     const uint16_t *lrow[R];
     // eight levels of each row from feature f on (past the row: its first)
     auto lev_load = [&](uint4 (&l)[R], int f) {
@@ -323,8 +342,8 @@ void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl,
             lrow[r] = lev + (row < n ? row : n - 1) * ldl;
             cnt[r].clear();
         }
-        lev_load(lv[0], 0);
-        id_load(id[0], 0);
+        lev_load(lv[0], fb);
+        id_load(id[0], fb);
     };
     start();
     __syncthreads();
@@ -370,11 +389,35 @@ void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl,
         }
     };
     for (int64_t rb = blockIdx.x;;) {
-        int f0 = 0;
-        for (; f0 + kLidFeat <= F; f0 += kLidFeat)
+        int f0 = fb;
+        for (; f0 + kLidFeat <= fe; f0 += kLidFeat)
             block(f0, std::integral_constant<bool, false>{});
-        if (f0 < F)
+        if (f0 < fe)
             block(f0, std::integral_constant<bool, true>{});
+        if constexpr (FS) {   // (one pass)
+            constexpr int NP = 5 + kLidBig;
+            lds_i32 *sums = (lds_i32 *)slv;
+            __syncthreads();   // the level words are done with
+            if (wave > 0) {
+#pragma unroll
+                for (int i = 0; i < R * NP * 4; ++i)
+                    sums[((wave - 1) * (R * NP * 4) + i) * 64 + lane] = (int)cnt[i / (NP * 4)].plane(i / 4 % NP, i % 4);
+            }
+            __syncthreads();
+            if (wave > 0)
+                return;
+#pragma unroll
+            for (int w = 0; w < kWaves - 1; ++w)
+#pragma unroll
+                for (int rk = 0; rk < R * 4; ++rk) {
+                    uint32_t c = 0;
+#pragma unroll
+                    for (int p = 0; p < NP; ++p) {
+                        const uint32_t x = (uint32_t)sums[(w * (R * NP * 4) + rk / 4 * (NP * 4) + p * 4 + rk % 4) * 64 + lane];
+                        c = csa(cnt[rk / 4].plane(p, rk % 4), x, c);
+                    }
+                }
+        }
 
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -401,14 +444,14 @@ void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl,
     }
 }
 
-template <int LPR, int R>
+template <int LPR, int R, bool FS>
 static hipError_t launch_level_id_rows(const uint16_t *lev, int64_t n, int F, int64_t ldl, const uint64_t *ID,
                                        int64_t ldid, const uint64_t *LV, int L, int64_t ldlv, int D, uint64_t *H,
                                        int64_t ldh, hipStream_t st)
 {
-    typedef LidShape<LPR, R> S;
+    typedef LidShape<LPR, R, FS> S;
     // once per process and shape (thread-safe static initialisation)
-    static const hipError_t attr = hipFuncSetAttribute((const void *)k_level_id<LPR, R>,
+    static const hipError_t attr = hipFuncSetAttribute((const void *)k_level_id<LPR, R, FS>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess)
         return attr;
@@ -418,9 +461,9 @@ static hipError_t launch_level_id_rows(const uint16_t *lev, int64_t n, int F, in
     // CU (20000 rows x 20 features, 256 levels, 4096 dimensions: 42 us with one
     // pass, 23.6 so).  Else one pass, up to 2^22 workgroups (a grid takes 2^24).
     const int64_t blocks = (n + S::ROWS - 1) / S::ROWS, wins = (W + S::W - 1) / S::W;
-    const int64_t most = (int64_t)(L + 1) * S::W > 64ll * F * R ? (512 + wins - 1) / wins : 1 << 22;
+    const int64_t most = !FS && (int64_t)(L + 1) * S::W > 64ll * F * R ? (512 + wins - 1) / wins : 1 << 22;
     const dim3 grid((unsigned)(blocks < most ? blocks : most), (unsigned)wins);
-    hipLaunchKernelGGL((k_level_id<LPR, R>), grid, dim3(256), S::lds(L), st, lev, n, F, ldl, ID, ldid, LV, L, ldlv, D,
+    hipLaunchKernelGGL((k_level_id<LPR, R, FS>), grid, dim3(256), S::lds(L), st, lev, n, F, ldl, ID, ldid, LV, L, ldlv, D,
                        H, ldh);
     return hipGetLastError();
 }
@@ -429,17 +472,21 @@ static hipError_t launch_level_id_rows(const uint16_t *lev, int64_t n, int F, in
 // once they make four rounds of the device's 512 workgroups; below, one row
 // and three waves per SIMD fill the last rounds better (5555 rows x 389
 // features, 5450 dimensions: 110 us with two rows, 100 with one; 32768 x 617,
-// 10240: 889 and 984).
+// 10240: 889 and 984).  While the rows, four to sixteen a workgroup, leave the
+// device half idle, the waves split the features.
 template <int LPR>
 static hipError_t launch_level_id_shape(const uint16_t *lev, int64_t n, int F, int64_t ldl, const uint64_t *ID,
                                         int64_t ldid, const uint64_t *LV, int L, int64_t ldlv, int D, uint64_t *H,
                                         int64_t ldh, hipStream_t st)
 {
     typedef LidShape<LPR, 2> S;
+    typedef LidShape<LPR, 1, true> SF;
     const int W = (D + 63) / 64;
+    if (F > kLidFeat && (n + SF::ROWS - 1) / SF::ROWS * ((W + S::W - 1) / S::W) <= 128)
+        return launch_level_id_rows<LPR, 1, true>(lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
     if ((n + S::ROWS - 1) / S::ROWS * ((W + S::W - 1) / S::W) >= 2048)
-        return launch_level_id_rows<LPR, 2>(lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
-    return launch_level_id_rows<LPR, 1>(lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
+        return launch_level_id_rows<LPR, 2, false>(lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
+    return launch_level_id_rows<LPR, 1, false>(lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
 }
 
 // Windows of 32, 16 or 8 words: the widest whose level rows leave room for
