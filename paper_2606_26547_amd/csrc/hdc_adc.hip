@@ -281,25 +281,26 @@ struct AdcCodes {
     }
 };
 
-template <int KT>
-__global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K,
-                                                  int w_lo, int w_hi, int nwin, const int8_t *__restrict__ tab,
-                                                  const int32_t *__restrict__ nc, int res, int step, int floor_,
-                                                  int ceil_, int32_t *__restrict__ label,
-                                                  int32_t *__restrict__ max_score, int32_t *__restrict__ scores)
+// The streaming search of one workgroup, its partials converted by arithmetic or
+// (not ARITH) by the table: a loop of its own each, the table's as it was before
+// the arithmetic (both in one loop: 200000 x 8192 against 100 classes, 12 bits, 257
+// us -> 362; so 247).
+template <int KT, bool ARITH>
+__device__ __forceinline__ void adc_stream(uint8_t *smem, const int *lut, const AdcConv &conv,
+                                           const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K, int w_lo,
+                                           int w_hi, int nwin, const int8_t *__restrict__ tab,
+                                           const int32_t *__restrict__ nc, int step, int floor_,
+                                           int32_t *__restrict__ label, int32_t *__restrict__ max_score,
+                                           int32_t *__restrict__ scores)
 {
     typedef HmShape<KT> S;
     constexpr int QT = S::QT, W = S::W, ROWS = S::ROWS, NST = S::NST;
-    constexpr int QG = KT == 2 ? 1 : QT;   // query tiles of a group (registers for two waves per SIMD)
-    __shared__ __align__(16) uint8_t smem[NST * S::SB];
-    __shared__ int lut[257];
+    // a group's tiles (registers for two waves per SIMD)
+    constexpr int QG = KT == 2 || !ARITH ? 1 : QT, KG = ARITH ? KT : 1;
     lds_u8 *L = (lds_u8 *)smem;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 5;
     const int64_t rbase = (int64_t)blockIdx.x * ROWS;
     const uint64_t *Qwg = Q + rbase * ldq;
-
-    const AdcConv conv(res, step, floor_, ceil_);
-    const bool arith = adc_table(lut, t, conv, res, step, floor_, ceil_);
 
     int qrow[S::NQL], qhalf[S::NQL];
 #pragma unroll
@@ -335,12 +336,14 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt)
             sc[kt][qt] = v16i{};
-    AdcCodes codes[KT][QT];
+    AdcCodes codes[KT][QT];   // (ARITH)
+    if constexpr (ARITH) {
 #pragma unroll
-    for (int kt = 0; kt < KT; ++kt)
+        for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-        for (int qt = 0; qt < QT; ++qt)
-            codes[kt][qt].clear();
+            for (int qt = 0; qt < QT; ++qt)
+                codes[kt][qt].clear();
+    }
     int pending = 0, chunks = 0;   // chunks in codes, and converted in all
     auto flush = [&]() {
 #pragma unroll
@@ -400,45 +403,48 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
             // the next ones' products are on the matrix cores
 #pragma unroll
             for (int q0 = 0; q0 < QT; q0 += QG) {
-                v16f part[QG][KT];
+                v8i bq[QG][2];
 #pragma unroll
                 for (int qt = 0; qt < QG; ++qt) {
                     const v4i u = qv[q0 + qt][cc];   // the chunk's two words: dwords 0-1 and 2-3
-                    const v8i b0 = query_bipolar((uint32_t)(g ? u[1] : u[0]));
-                    const v8i b1 = query_bipolar((uint32_t)(g ? u[3] : u[2]));
-#pragma unroll
-                    for (int kt = 0; kt < KT; ++kt) {
-                        part[qt][kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[0][kt], b0, v16f{}, 4, 4, 0,
-                                                                                       0, 0, 0);
-                        part[qt][kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[1][kt], b1, part[qt][kt], 4,
-                                                                                       4, 0, 0, 0, 0);
-                    }
+                    bq[qt][0] = query_bipolar((uint32_t)(g ? u[1] : u[0]));
+                    bq[qt][1] = query_bipolar((uint32_t)(g ? u[3] : u[2]));
                 }
-                if (arith) {
+#pragma unroll
+                for (int k0 = 0; k0 < KT; k0 += KG) {
+                    v16f part[QG][KG];
 #pragma unroll
                     for (int qt = 0; qt < QG; ++qt)
 #pragma unroll
-                        for (int kt = 0; kt < KT; ++kt)
-                            codes[kt][q0 + qt].add(conv, part[qt][kt]);
-                } else {
+                        for (int kt = 0; kt < KG; ++kt) {
+                            part[qt][kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                                af[0][k0 + kt], bq[qt][0], v16f{}, 4, 4, 0, 0, 0, 0);
+                            part[qt][kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                                af[1][k0 + kt], bq[qt][1], part[qt][kt], 4, 4, 0, 0, 0, 0);
+                        }
 #pragma unroll
                     for (int qt = 0; qt < QG; ++qt)
 #pragma unroll
-                        for (int kt = 0; kt < KT; ++kt)
+                        for (int kt = 0; kt < KG; ++kt) {
+                            if constexpr (ARITH) {
+                                codes[k0 + kt][q0 + qt].add(conv, part[qt][kt]);
+                            } else {
 #pragma unroll
-                            for (int e = 0; e < 16; ++e)
-                                sc[kt][q0 + qt][e] += lut[(int)part[qt][kt][e] + 128];
+                                for (int e = 0; e < 16; ++e)
+                                    sc[k0 + kt][q0 + qt][e] += lut[(int)part[qt][kt][e] + 128];
+                            }
+                        }
                 }
             }
         }
-        if (arith && pending > kAdcFlush - W / 2)
+        if (ARITH && pending > kAdcFlush - W / 2)
             flush();
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(G * (NST - 2)) : "memory");
         st = st == NST - 1 ? 0 : st + 1;
     }
     __builtin_amdgcn_s_waitcnt(0);
-    const int mul = arith ? step : 1, add = arith ? floor_ * chunks : 0;   // codes to values
-    if (arith)
+    const int mul = ARITH ? step : 1, add = ARITH ? floor_ * chunks : 0;   // codes to values
+    if (ARITH)
         flush();
 
     // argmax: lane holds query l%32 of each tile and classes 8(v/4)+4g+v%4
@@ -466,6 +472,33 @@ __global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q
                 max_score[q] = best;
         }
     }
+}
+
+// ARITH: by arithmetic if that gives the table's values, else by the table; the
+// registers of the arithmetic (two waves per SIMD from 33 classes on) slow the
+// table's loop, so where the table is foreseen (adc_arith) it has its own kernel
+// with three.
+template <int KT, bool ARITH>
+__global__ __launch_bounds__(256) void k_adc_mfma(const uint64_t *__restrict__ Q, int64_t n, int64_t ldq, int K,
+                                                  int w_lo, int w_hi, int nwin, const int8_t *__restrict__ tab,
+                                                  const int32_t *__restrict__ nc, int res, int step, int floor_,
+                                                  int ceil_, int32_t *__restrict__ label,
+                                                  int32_t *__restrict__ max_score, int32_t *__restrict__ scores)
+{
+    typedef HmShape<KT> S;
+    __shared__ __align__(16) uint8_t smem[S::NST * S::SB];
+    __shared__ int lut[257];
+    const AdcConv conv(res, step, floor_, ceil_);
+    const bool arith = adc_table(lut, threadIdx.x, conv, res, step, floor_, ceil_);   // uniform
+    if constexpr (ARITH) {
+        if (arith) {
+            adc_stream<KT, true>(smem, lut, conv, Q, n, ldq, K, w_lo, w_hi, nwin, tab, nc, step, floor_, label,
+                                 max_score, scores);
+            return;
+        }
+    }
+    adc_stream<KT, false>(smem, lut, conv, Q, n, ldq, K, w_lo, w_hi, nwin, tab, nc, step, floor_, label, max_score,
+                          scores);
 }
 
 // The same for few queries (see few_pairs): a pair of words is a chunk; the
@@ -563,6 +596,34 @@ __global__ __launch_bounds__(256) void k_adc_few(const uint64_t *__restrict__ Q,
     }
 }
 
+// Whether the arithmetic of AdcConv gives the table's values: the same check in
+// single precision, its results rounded to halves' 11 bits, to choose the kernel
+// (which checks for itself).  Settings whose codes pass 1023, and about one in
+// fifty others, take the table.
+static bool adc_arith(int res, int step, int floor_, int ceil_)
+{
+    auto half = [](float v) {
+        const float g = v * 8193.0f;
+        return g - (g - v);
+    };
+    const float top = (float)((1ll << res) - 1);
+    float range = (float)((int64_t)ceil_ - floor_) / (float)step;
+    range = range < top ? range : top;
+    range = range > 0.0f ? range : 1.0f;
+    const float inv = 1.0f / ((float)step * range);
+    const float k = half(inv), c = half((0.25f - (float)floor_) * inv), r = half(range);
+    for (int s = -128; s <= 128; ++s) {
+        const int64_t x = s < floor_ ? floor_ : (s > ceil_ ? ceil_ : s);
+        int64_t code = (2 * (x - floor_) + step) / (2 * (int64_t)step);
+        code = code < (1ll << res) - 1 ? code : (1ll << res) - 1;
+        float t = half((float)s * k + c);
+        t = t < 0.0f ? 0.0f : t > 1.0f ? 1.0f : t;
+        if (code >= 1024 || half(t * r + 1024.0f) != 1024.0f + (float)code)
+            return false;
+    }
+    return true;
+}
+
 hipError_t launch_adc_prepared(const uint64_t *Q, int64_t n, int64_t ldq, int K, int start, int end, int res,
                                int step, int floor_, int ceil_, const uint8_t *ws, int32_t *label,
                                int32_t *max_score, int32_t *scores, hipStream_t st)
@@ -579,9 +640,13 @@ hipError_t launch_adc_prepared(const uint64_t *Q, int64_t n, int64_t ldq, int K,
     if (L.KT == KT_) {                                                                                         \
         typedef HmShape<KT_> S;                                                                                \
         constexpr int NW = kHmWin / S::W;                                                                      \
-        hipLaunchKernelGGL(k_adc_mfma<KT_>, dim3((unsigned)((n + S::ROWS - 1) / S::ROWS)), dim3(256), 0, st, Q,  \
-                           n, ldq, K, L.w_lo, L.w_hi, L.nwin * NW, tab, nc, res, step, floor_, ceil_, label,   \
-                           max_score, scores);                                                                 \
+        const dim3 grid((unsigned)((n + S::ROWS - 1) / S::ROWS));                                              \
+        if (adc_arith(res, step, floor_, ceil_))                                                               \
+            hipLaunchKernelGGL((k_adc_mfma<KT_, true>), grid, dim3(256), 0, st, Q, n, ldq, K, L.w_lo, L.w_hi,    \
+                               L.nwin * NW, tab, nc, res, step, floor_, ceil_, label, max_score, scores);      \
+        else                                                                                                   \
+            hipLaunchKernelGGL((k_adc_mfma<KT_, false>), grid, dim3(256), 0, st, Q, n, ldq, K, L.w_lo, L.w_hi,   \
+                               L.nwin * NW, tab, nc, res, step, floor_, ceil_, label, max_score, scores);      \
         return hipGetLastError();                                                                              \
     }
     HDC_ADCP_CASE(1)
