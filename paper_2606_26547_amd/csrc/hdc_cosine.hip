@@ -101,38 +101,63 @@ __device__ __forceinline__ bool in_set(int64_t d, int start, int end, int stride
     return d >= start && d < end && (d - start) % stride == 0;
 }
 
-// The FP6 operand of (word, class tile, lane, part): index idx counts the
-// entries of both formats' tables (four per word, tile and lane); here two of
-// the four write.
+// The FP6 operand of (word, class tile, lane), both digits: index idx counts the
+// entries of the int8 table (four per word, tile and lane); here one of the four
+// works.  A lane's 32 entries are one run of its class's sums: read without
+// branches (those outside the set read one inside and count 0), all in flight
+// (entry by entry, each digit for itself and with a remainder by the stride: 100
+// classes x 16384 35 us, 8 so).
 __device__ __forceinline__ void f6_entry(const int32_t *__restrict__ acc, int K, int64_t lda, int start, int end,
                                          int stride, int w_lo, int KT, int64_t idx, int8_t *__restrict__ tab)
 {
     const int lane = (int)(idx & 63);
     const int kt = (int)((idx >> 6) % KT);
     const int64_t whp = (idx >> 6) / KT;
-    const int part = (int)(whp & 1);
-    if (whp & 2)
+    if (whp & 3)
         return;
-    const int64_t wi = whp >> 2, w = w_lo + wi;
+    const int64_t wi = whp >> 2;
     const int k = kt * 32 + (lane & 31), g = lane >> 5;
-    uint32_t o[6] = {0, 0, 0, 0, 0, 0};
-    if (k < K) {
+    const int d0 = (int)((w_lo + wi) * 64) + 32 * g;
+    uint32_t o[2][6] = {};
+    const uint32_t m = k < K ? set_mask(d0, start, end, stride) : 0u;
+    if (m) {
+        const int32_t *row = acc + k * lda + d0;
+        const int in = __builtin_ctz(m);
+        int a[32];
+        if (m == ~0u) {   // (16-byte loads at 4-byte alignment)
+            typedef int v4i4 __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+            for (int j = 0; j < 32; j += 4) {
+                const v4i4 v = *(const v4i4 *)(row + j);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    a[j + e] = v[e];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 32; ++j)
+                a[j] = row[(m >> j) & 1u ? j : in];
+        }
 #pragma unroll
         for (int i = 0; i < 32; ++i) {
-            const int64_t d = w * 64 + 32 * g + 4 * (i & 7) + (i >> 3);
-            if (in_set(d, start, end, stride)) {
-                const int a = acc[k * lda + d], m = a < 0 ? -a : a;
-                const uint32_t c = (uint32_t)(part ? m >> 4 : m & 15) | (a < 0 ? 0x20u : 0u);
-                const int bit = 6 * i;
-                o[bit >> 5] |= c << (bit & 31);
+            const int j = 4 * (i & 7) + (i >> 3), bit = 6 * i;
+            const int v = (m >> j) & 1u ? a[j] : 0;
+            const uint32_t u = (uint32_t)(v < 0 ? -v : v), sign = v < 0 ? 0x20u : 0u;
+#pragma unroll
+            for (int part = 0; part < 2; ++part) {
+                const uint32_t c = (part ? u >> 4 : u & 15u) | sign;
+                o[part][bit >> 5] |= c << (bit & 31);
                 if ((bit & 31) > 26)
-                    o[(bit >> 5) + 1] |= c >> (32 - (bit & 31));
+                    o[part][(bit >> 5) + 1] |= c >> (32 - (bit & 31));
             }
         }
     }
     int8_t *word = tab + wi * (3072 * KT);
-    *(uint4 *)(word + (part * KT + kt) * 1024 + lane * 16) = make_uint4(o[0], o[1], o[2], o[3]);
-    *(uint2 *)(word + 2048 * KT + (part * KT + kt) * 512 + lane * 8) = make_uint2(o[4], o[5]);
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+        *(uint4 *)(word + (part * KT + kt) * 1024 + lane * 16) = make_uint4(o[part][0], o[part][1], o[part][2], o[part][3]);
+        *(uint2 *)(word + 2048 * KT + (part * KT + kt) * 512 + lane * 8) = make_uint2(o[part][4], o[part][5]);
+    }
 }
 
 __global__ __launch_bounds__(256) void k_cos_table(const int32_t *__restrict__ acc, int K, int64_t lda, int start,
@@ -170,7 +195,8 @@ __global__ __launch_bounds__(256) void k_cos_table(const int32_t *__restrict__ a
 }
 
 // T_k, rinv_k and max |a_kd| over S, one workgroup per class (classes past
-// K get 0).
+// K get 0).  It is the first to read the sums: eight loads in flight a thread (one:
+// 100 classes x 16384 20 us, 7.5 so).
 __global__ __launch_bounds__(256) void k_cos_norms(const int32_t *__restrict__ acc, int K, int64_t lda, int start,
                                                    int end, int stride, int64_t *__restrict__ T,
                                                    double *__restrict__ rinv, int32_t *__restrict__ amax)
@@ -179,11 +205,20 @@ __global__ __launch_bounds__(256) void k_cos_norms(const int32_t *__restrict__ a
     const int k = blockIdx.x, t = threadIdx.x;
     long long s = 0, q = 0, m = 0;
     if (k < K)
-        for (int64_t d = start + (int64_t)t * stride; d < end; d += (int64_t)256 * stride) {
-            const long long a = acc[k * lda + d];
-            s += a;
-            q += a * a;
-            m = a > m ? a : (-a > m ? -a : m);
+        for (int64_t d = start + (int64_t)t * stride; d < end; d += (int64_t)(8 * 256) * stride) {
+            int v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int64_t du = d + (int64_t)(u * 256) * stride;
+                v[u] = acc[k * lda + (du < end ? du : d)];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const long long a = d + (int64_t)(u * 256) * stride < end ? v[u] : 0;
+                s += a;
+                q += a * a;
+                m = a > m ? a : (-a > m ? -a : m);
+            }
         }
     ps[t] = s;
     pq[t] = q;
