@@ -81,11 +81,17 @@ __global__ __launch_bounds__(256) void k_classify_f32_few(EncodeArgs a)
         for (int v = 0; v < 16; ++v)
             sums[wave][kt * 32 + 8 * (v >> 2) + 4 * g + (v & 3)][c] = dacc[kt][v];
     __syncthreads();
-    for (int k = threadIdx.x >> 5; k < a.K; k += 8) {
-        const int col = threadIdx.x & 31;
+    auto sum = [&](int k, int col) {
         if (qb + col < a.n)
-            a.part[((int64_t)z * a.K + k) * a.n + qb + col] = sums[0][k][col] + sums[1][k][col] + sums[2][k][col] +
-                                                               sums[3][k][col];
+            a.part[part_at(a, KT, z, k, qb + col)] = sums[0][k][col] + sums[1][k][col] + sums[2][k][col] + sums[3][k][col];
+    };
+    if (part_rows(KT, a.n)) {   // a query's classes in turn
+        for (int i = threadIdx.x; i < KT * 32 * 32; i += 256)
+            if (i % (KT * 32) < a.K)
+                sum(i % (KT * 32), i / (KT * 32));
+    } else {
+        for (int k = threadIdx.x >> 5; k < a.K; k += 8)
+            sum(k, threadIdx.x & 31);
     }
 }
 
@@ -109,7 +115,10 @@ hipError_t launch_encode_f32(const EncodeArgs &a, int mode, Tile tile, hipStream
 {
     if (mode == M_CLASSIFY && tile.variant == TV_AUTO && a.F <= 256 && few_blocks(a, mode)) {
         const int Z = split_count((a.n + 255) / 256, a.nd, a.max_split, 256);
-        if (Z > 1) {
+        // four class tiles: two workgroups per CU, and each writes 16 KiB of sums;
+        // past two rounds the encoder's 128 queries a workgroup are faster (1000 x
+        // 64, 10240 dimensions, 100 classes: 45 us, 42)
+        if (Z > 1 && (class_tiles(a.K) < 4 || (a.n + 31) / 32 * Z <= 1024)) {
             if (a.F <= 64)
                 return launch_f32_few<32>(a, Z, st);
             return a.F <= 128 ? launch_f32_few<64>(a, Z, st) : launch_f32_few<128>(a, Z, st);

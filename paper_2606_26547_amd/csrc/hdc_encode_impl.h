@@ -7,6 +7,23 @@
 
 namespace hdc {
 
+// Whether a split launch's partial sums are [z][n][K] (else [z][K][n]): from 65
+// classes on, and from 33 on for few queries.  With the classes apart every
+// workgroup of the argmin touches a line per class and split, however few its
+// queries (60 x 64 E4M3, 10240 dimensions, 100 classes, 40 splits: 18.4 us with
+// the encoder, 14 so; 1500 x 617 int8, 8192 dimensions, 128 classes 40 and 34); 50
+// classes gain 2% below 1024 queries and lose 3% above.
+constexpr int64_t kRowQueries = 1024;
+__host__ __device__ __forceinline__ bool part_rows(int KT, int64_t n)
+{
+    return KT == 4 || (KT == 2 && n < kRowQueries);
+}
+// Place of (split, class, query) in them.
+__device__ __forceinline__ int64_t part_at(const EncodeArgs &a, int KT, int z, int k, int64_t q)
+{
+    return part_rows(KT, a.n) ? ((int64_t)z * a.n + q) * a.K + k : ((int64_t)z * a.K + k) * a.n + q;
+}
+
 // Grid: query blocks, or (dimension split, query block) when the launch
 // splits its dimensions (a.nsplit = Z > 1).  Split z of Z takes the whole
 // 64-dimension words [z * per, (z + 1) * per) of the dimension list: its
@@ -15,8 +32,7 @@ namespace hdc {
 // with the split index fastest each XCD's L2 holds the projection rows of
 // its splits only, not all of them.  In classify mode every split adds its
 // own part of the class sums, so a split launch writes them to
-// part[z][K][n] (a wave's stores cover whole lines) and k_split_argmin
-// finishes.
+// part (part_rows) and k_split_argmin or k_split_argmin_rows finishes.
 template <int CT, int XF, int QT, int KS, int KT, int MODE, bool DMA, int RT, int SRC>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(Encoder<CT, XF, QT, KS, KT, MODE, 0, DMA, RT, SRC>::REGW)))
@@ -55,7 +71,7 @@ void k_encode(EncodeArgs a)
                     for (int v = 0; v < 16; ++v) {
                         const int k = kt * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
                         if (k < a.K)
-                            a.part[((int64_t)z * a.K + k) * a.n + q] = dacc[kt][qt][v];
+                            a.part[part_at(a, KT, z, k, q)] = dacc[kt][qt][v];
                     }
             }
             return;
@@ -126,9 +142,61 @@ static __global__ __launch_bounds__(1024) void k_split_argmin(EncodeArgs a, int 
     }
 }
 
+// The same for rows of classes (part_rows): a wave per query, lane l classes l and
+// l + 64.
+static __global__ __launch_bounds__(256) void k_split_argmin_rows(EncodeArgs a, int Z)
+{
+    const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (q >= a.n)
+        return;
+    // (classes past the last: an earlier one again)
+    const int k0 = lane < a.K ? lane : a.K - 1, k1 = lane + 64 < a.K ? lane + 64 : k0;
+    const int32_t *p = a.part + q * a.K;
+    const int64_t zs = a.n * a.K;
+    int s0 = 0, s1 = 0;
+    for (int z0 = 0; z0 < Z; z0 += 8) {
+        int v0[8], v1[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int32_t *pz = p + (z0 + u < Z ? z0 + u : z0) * zs;
+            v0[u] = pz[k0];
+            v1[u] = pz[k1];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            s0 += z0 + u < Z ? v0[u] : 0;
+            s1 += z0 + u < Z ? v1[u] : 0;
+        }
+    }
+    int bd = a.cpop[k0] - s0, bk = k0;
+    const int d1 = a.cpop[k1] - s1;
+    if (a.dists) {
+        a.dists[q * a.K + k0] = bd;
+        a.dists[q * a.K + k1] = d1;
+    }
+    if (d1 < bd) {
+        bd = d1;
+        bk = k1;
+    }
+    // first minimum across the lanes (lower class index on ties)
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const int od = __shfl_xor(bd, o), ok = __shfl_xor(bk, o);
+        if (od < bd || (od == bd && ok < bk)) {
+            bd = od;
+            bk = ok;
+        }
+    }
+    if (lane == 0)
+        a.labels[q] = bk;
+}
+
 static void launch_split_argmin(const EncodeArgs &a, int Z, hipStream_t st)
 {
-    if (a.n >= 1024)
+    if (part_rows(class_tiles(a.K), a.n))
+        hipLaunchKernelGGL(k_split_argmin_rows, dim3((unsigned)((a.n + 3) / 4)), dim3(256), 0, st, a, Z);
+    else if (a.n >= 1024)
         hipLaunchKernelGGL(k_split_argmin<32>, dim3((unsigned)((a.n + 31) / 32)), dim3(1024), 0, st, a, Z);
     else
         hipLaunchKernelGGL(k_split_argmin<8>, dim3((unsigned)((a.n + 7) / 8)), dim3(1024), 0, st, a, Z);
