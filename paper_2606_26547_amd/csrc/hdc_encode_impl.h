@@ -220,6 +220,33 @@ static bool few_blocks(const EncodeArgs &a, int mode)
     return 2 * blocks * z1 <= 256 && 4 * split_units(a.nd, z1) <= 5 * split_units(a.nd, z2);
 }
 
+// Expected time (ns) of a direct-staged classify launch with qt query tiles per
+// wave on width features: the words of a split, one after the other, and where
+// there are splits the second launch and the partial sums it writes and reads.
+// Two tiles cost less than twice one a word on narrow features (LDS bound) and
+// about twice on wide ones; more workgroups of one tile mean fewer splits, which
+// many classes and few dimensions favour: 30000 x 64 E4M3, 1024 dimensions, 50
+// classes, 15 us with one tile unsplit and 28 with two in two splits; 20000 x 617
+// int8, 8192 dimensions, 100 classes, 140 and 120.  Coefficients fitted to 1500
+// launches of both kinds (64 to 784 features, 300 to 30000 queries, 5 to 128
+// classes, 1024 to 8192 dimensions, int8, uint8, E4M3); on none of them is the
+// choice slower than the kernels of one shape before.
+static int64_t classify_ns(const EncodeArgs &a, int qt, int width)
+{
+    const int64_t blocks = (a.n + 128 * qt - 1) / (128 * qt);
+    const int z = split_count(blocks, a.nd, a.max_split, 256);
+    const int kt = class_tiles(a.K), word = qt == 1 ? 700 + width * 4 / 5 + 20 * kt : 500 + 2 * width + 100 * kt;
+    return (int64_t)split_units(a.nd, z) * word + (z > 1 ? 4000 + a.n * a.K * z * 7 / 2000 : 0);
+}
+
+// Whether a direct-staged launch takes one query tile per wave.
+static bool one_tile(const EncodeArgs &a, int mode, int width)
+{
+    if (mode == M_ENCODE)
+        return few_blocks(a, mode);
+    return (a.n + 255) / 256 <= 128 && classify_ns(a, 1, width) <= classify_ns(a, 2, width);
+}
+
 template <int CT, int XF, int QT, int KS, int KT, int MODE, bool DMA = false, int RT = 1, int SRC = W_ROWS>
 static hipError_t launch_one(const EncodeArgs &a, hipStream_t st)
 {
@@ -249,7 +276,7 @@ static hipError_t launch_one(const EncodeArgs &a, hipStream_t st)
 // two class tiles, where two take 297 registers, one wave per SIMD, and the last
 // round of workgroups costs a whole one (200000 x 300, 4096 dimensions, 40
 // classes: 298 us with two, 259 with one; 65536: 75 and 79).
-// Few query blocks take one query tile (few_blocks), except the shifted int8
+// Few query blocks take one query tile (one_tile), except the shifted int8
 // type, whose start values need the registers of one wave per SIMD (20000 x
 // 617, 8192 dimensions on the shifted E4M3 form without scratch: 190 us with
 // two, 144 with one).
@@ -260,7 +287,7 @@ static hipError_t launch_direct(const EncodeArgs &a, hipStream_t st)
     constexpr bool SHIFT1 = CT == C_FP8 && SRC == W_ROWS && W <= 320 && KT == 2;
     constexpr int QT = CT == C_FP8S || (W > 832 && KT == 4) || SHIFT1 ? 1 : 2;
     constexpr int RT = QT == 1 || W > 640 || (CT == C_I8 && SRC == W_ALT) ? 1 : 2;
-    if (QT == 2 && (CT == C_FP8 || !a.poff) && few_blocks(a, MODE))
+    if (QT == 2 && (CT == C_FP8 || !a.poff) && one_tile(a, MODE, W))
         return launch_one<CT, 0, 1, KS, KT, MODE, true, 1, SRC>(a, st);
     return launch_one<CT, 0, QT, KS, KT, MODE, true, RT, SRC>(a, st);
 }
