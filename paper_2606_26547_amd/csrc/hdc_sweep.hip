@@ -678,7 +678,7 @@ hipError_t launch_sweep(const SweepArgs &a, hipStream_t st)
             s.ct = -1;
         s.s0 = ok ? c.start : 0;
         s.stride = ok ? c.stride : 1;
-        s.nd = ok ? (c.d_trunc - c.start + c.stride - 1) / c.stride : 0;
+        s.nd = ok ? (int32_t)(((int64_t)c.d_trunc - c.start + c.stride - 1) / c.stride) : 0;
         // built-in work items: 256 queries
         s.iq = c.tile_id == SV_ITEM128 ? 1 : c.tile_id == SV_ITEM256_DMA ? 3 : c.tile_id == SV_SHARED ? SV_SHARED : 2;
         s.tiles = ok && s.iq != SV_SHARED ? (int32_t)((a.n + (s.iq == 1 ? 127 : 255)) / (s.iq == 1 ? 128 : 256)) : 0;

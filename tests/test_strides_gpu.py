@@ -71,3 +71,26 @@ def test_encode_and_classify_one_dimension(F, xt, compute, stride):
         lab, dists = hdc.classify(Xd, F, Pd, D, Cd, compute, start, D, stride, with_dists=True)
         lref, dref = O.classify(X, P, C.view(np.uint64), compute, *one, with_dists=True)
         assert np.array_equal(dists.cpu().numpy(), dref) and np.array_equal(lab.cpu().numpy(), lref)
+
+
+@pytest.mark.parametrize("stride", [700, MAX - 100, MAX])
+def test_sweep_of_one_dimension(stride):
+    from paper_2606_26547_amd import datagen as dg
+    from paper_2606_26547_amd import hdc
+    print("[case] sweep stride", stride, flush=True)
+    n, F, D, K = 150, 100, 700, 5
+    X, P = dg.random_case(n, F, D, "int8", seed=F)
+    C = np.random.default_rng(F).integers(0, 2 ** 60, size=(K, 11), dtype=np.int64)
+    C[:, -1] &= (1 << (D % 64)) - 1
+    y = torch.as_tensor(np.random.default_rng(1).integers(0, K, n, dtype=np.int32)).cuda()
+    cfgs, one = [], []
+    for start in (0, 69, 640):
+        for t in ("int8", "bf16", "fp8"):
+            for tile in (1, 2, 3, 4):
+                cfgs.append((D, stride, start, t, tile))
+                one.append((start + 1, 1, start, t, tile))
+    args = (hdc.pad_cols(X), F, y, hdc.pad_cols(P), D, torch.as_tensor(C).cuda())
+    got, ref = hdc.eval_configs(*args, cfgs), hdc.eval_configs(*args, one)
+    assert np.array_equal(got["correct"], ref["correct"]) and np.array_equal(got["n"], ref["n"])
+    sref = [int((O.classify(X, P, C.view(np.uint64), t, s, s + 1, 1) == y.cpu().numpy()).sum()) for _, _, s, t, _ in cfgs]
+    assert got["correct"].tolist() == sref
