@@ -74,7 +74,10 @@ typedef enum {
  *   HDC_INT8 / HDC_UINT8 -> HDC_INT8     exact: int8 MFMA, int32 accumulation
  *                                        (uint8 runs as x-128 plus a column-sum
  *                                        correction, also exact)
- *   HDC_INT8 / HDC_UINT8 -> HDC_BF16     bf16 MFMA, fp32 accumulation
+ *   HDC_INT8 / HDC_UINT8 -> HDC_BF16     the same bits as HDC_INT8: integers up
+ *                                        to 255 and +-1 are exact in bf16 and
+ *                                        their sums in fp32, so the int8 kernels
+ *                                        run it (whichever tile is named)
  *   HDC_INT8 / HDC_UINT8 -> HDC_FP8_E4M3 OCP E4M3 MFMA, fp32 accumulation
  *   HDC_INT8 / HDC_UINT8 -> HDC_FP8_E4M3_SPLIT
  *                                        each feature x written as
@@ -95,6 +98,9 @@ typedef enum {
  *                                        sum started from minus the sum of
  *                                        the query's rounded features
  *   HDC_FP32 -> HDC_FP32 / HDC_BF16 / HDC_FP8_E4M3   (F <= 256)
+ *                                        fp32 sums, in one order per compute type
+ *                                        and width, whatever the batch, the kernel
+ *                                        shape, the splits or the classes
  * The reduced types round each feature to the compute type (round to nearest
  * even) and multiply by the exactly representable +-1 weights (Sec. 4.2
  * "Element Type Representation").  HDC_FP8_E4M3_SPLIT is a compute type

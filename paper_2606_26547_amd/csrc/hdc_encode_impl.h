@@ -205,13 +205,12 @@ static void launch_split_argmin(const EncodeArgs &a, int Z, hipStream_t st)
 // Smallest dimension split (64-dimension words) of a launch.
 constexpr int split_units_min(int mode) { return mode == M_ENCODE ? 1 : kSplitMinUnits; }
 
-// Whether two query tiles per wave would leave much of the device idle: then
-// one query tile (128 queries per workgroup) makes twice the workgroups, each
-// with half the features to load and half the MFMAs a word.  It pays while its
-// splits, over twice the blocks, are not over a quarter longer (both are
-// bounded by the shortest split, see split_units_min): 3000 x 771, 3418
-// dimensions, 10 classes, 22.4 us with two tiles and 17.8 with one; at 4500,
-// where one tile's splits are 7 words against 5, 24 with one and 23 with two.
+// Whether two query tiles per wave would leave much of the device idle (encodings,
+// and the fp32 features' kernels): then one query tile (128 queries per workgroup)
+// makes twice the workgroups, each with half the features to load and half the
+// MFMAs a word.  It pays while its splits, over twice the blocks, are not over a
+// quarter longer: where the words run out (both are bounded by the shortest split,
+// see split_units_min).
 static bool few_blocks(const EncodeArgs &a, int mode)
 {
     const int64_t blocks = (a.n + 255) / 256;

@@ -97,16 +97,17 @@ constexpr int kMaxConfigs = 4096;
 // The prepared searches address a workgroup's query rows with 32-bit byte
 // offsets from its first row (at most 256 rows).
 constexpr int64_t kMaxPreparedLdq = 1 << 20;
-// Level-ID encoding keeps a window of every identity and level hypervector
-// in LDS.
+// Level-ID encoding keeps a window of every level hypervector in LDS, and counts
+// in 11 bits.
 constexpr int kMaxLevelIdF = 1024;
 constexpr int kMaxLevels = 1024;
 
 inline int class_tiles(int K) { return (K + 31) / 32 <= 1 ? 1 : ((K + 31) / 32 <= 2 ? 2 : 4); }
 inline int64_t chunks(int nd) { return (nd + kDimChunk - 1) / kDimChunk; }
-// The fused classifier's class operand covers a whole number of every
-// chunk width it is read in (2 and 3 tiles of 32: a multiple of kMaxRT
-// tiles); rows past the dimension count are 0.
+// The fused classifier's class operand is read in chunks of one or two tiles of
+// 32 dimensions and padded to a multiple of kMaxRT tiles, of which the kernels
+// need two: the size callers have allocated by stays what it was.  Rows past the
+// dimension count are 0.
 constexpr int kMaxRT = 6;
 inline int64_t table_chunks(int nd) { return (chunks(nd) + kMaxRT - 1) / kMaxRT * kMaxRT; }
 inline size_t class_table_bytes(int nd, int K) { return (size_t)table_chunks(nd) * class_tiles(K) * 1024; }

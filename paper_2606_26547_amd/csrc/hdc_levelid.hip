@@ -254,8 +254,7 @@ struct LidCounter {
 // lane, against 13 per 64-bit word and feature for plain xor and majority on
 // one word per lane.  32768 x 617, 10240 dimensions, 128 levels, with the
 // quantiser: 1372 us on one word and row per lane, 792 so, the vector units
-// busy four fifths of it; 984 / 931 with one / three rows per lane, 919 with
-// the identity words through LDS.
+// busy four fifths of it; without it 779 so, 876 with one row per lane.
 //
 // Few rows (FS): the four waves of a workgroup take a quarter of the features
 // each of the same rows, and their counts meet in LDS.  A wave alone on its SIMD
@@ -471,8 +470,8 @@ static hipError_t launch_level_id_rows(const uint16_t *lev, int64_t n, int F, in
 // Two rows per lane (each identity word read serves both, two waves per SIMD)
 // once they make four rounds of the device's 512 workgroups; below, one row
 // and three waves per SIMD fill the last rounds better (5555 rows x 389
-// features, 5450 dimensions: 110 us with two rows, 100 with one; 32768 x 617,
-// 10240: 889 and 984).  While the rows, four to sixteen a workgroup, leave the
+// features, 5450 dimensions: 110 us with two rows, 75 with one; 32768 x 617,
+// 10240: 779 and 876, without the quantiser).  While the rows, four to sixteen a workgroup, leave the
 // device half idle, the waves split the features.
 template <int LPR>
 static hipError_t launch_level_id_shape(const uint16_t *lev, int64_t n, int F, int64_t ldl, const uint64_t *ID,

@@ -2,7 +2,9 @@
 // type, feature width, class tiles) bucket is compiled with.  A launch names
 // its variant (0 = the built-in rule); an autotuner measures the variants of
 // a bucket and passes the fastest with each call.  Every variant of a bucket
-// computes the same result.  Nothing here is mutable.
+// computes the same result.  Of byte features' ids only DMA_1X1 is a shape of its
+// own (int8, up to 640 features and 64 classes); the others stay listed, and are
+// one kernel, because saved tile tables name them.  Nothing here is mutable.
 #include "hdc_internal.h"
 
 namespace hdc {

@@ -26,8 +26,10 @@ import torch
 
 from . import hdc
 
-# relative cost of one encoded dimension per compute type on gfx950 (MFMA
-# throughput: int8 and fp8 run at the same dense rate, bf16 at half)
+# relative cost of one encoded dimension per compute type (the per-configuration
+# sweep kernels' MFMA rates: int8 and fp8 the same, bf16 half).  Classified by
+# itself, a bf16 configuration of byte features runs as int8 with the same labels,
+# so this also ranks int8 before the bf16 configuration that equals it.
 DTYPE_COST = {"int8": 1.0, "fp8": 1.0, "bf16": 2.0}
 
 
