@@ -230,20 +230,33 @@ static bool few_blocks(const EncodeArgs &a, int mode)
 // launches of both kinds (64 to 784 features, 300 to 30000 queries, 5 to 128
 // classes, 1024 to 8192 dimensions, int8, uint8, E4M3); on none of them is the
 // choice slower than the kernels of one shape before.
+static int word_ns(int qt, int width, int kt)
+{
+    return qt == 1 ? 700 + width * 4 / 5 + 20 * kt : 500 + 2 * width + 100 * kt;
+}
 static int64_t classify_ns(const EncodeArgs &a, int qt, int width)
 {
     const int64_t blocks = (a.n + 128 * qt - 1) / (128 * qt);
     const int z = split_count(blocks, a.nd, a.max_split, 256);
-    const int kt = class_tiles(a.K), word = qt == 1 ? 700 + width * 4 / 5 + 20 * kt : 500 + 2 * width + 100 * kt;
-    return (int64_t)split_units(a.nd, z) * word + (z > 1 ? 4000 + a.n * a.K * z * 7 / 2000 : 0);
+    return (int64_t)split_units(a.nd, z) * word_ns(qt, width, class_tiles(a.K)) +
+           (z > 1 ? 4000 + a.n * a.K * z * 7 / 2000 : 0);
 }
 
-// Whether a direct-staged launch takes one query tile per wave.
+// Whether a direct-staged launch takes one query tile per wave.  An encoding has no
+// partial sums; its few longest splits may take a quarter longer, for half the
+// features to load first (1000 x 784, 10240 dimensions: 17.2 us with two tiles, 13.2
+// with one; 6000 x 1024, 1000 dimensions 16.8 and 12.1).
 static bool one_tile(const EncodeArgs &a, int mode, int width)
 {
-    if (mode == M_ENCODE)
-        return few_blocks(a, mode);
-    return (a.n + 255) / 256 <= 128 && classify_ns(a, 1, width) <= classify_ns(a, 2, width);
+    if ((a.n + 255) / 256 > 128)
+        return false;
+    if (mode == M_CLASSIFY)
+        return classify_ns(a, 1, width) <= classify_ns(a, 2, width);
+    auto split_ns = [&](int qt) {
+        const int z = split_count((a.n + 128 * qt - 1) / (128 * qt), a.nd, a.max_split, 256, 1);
+        return (int64_t)split_units(a.nd, z) * word_ns(qt, width, 0);
+    };
+    return few_blocks(a, mode) || 4 * split_ns(1) <= 5 * split_ns(2);
 }
 
 template <int CT, int XF, int QT, int KS, int KT, int MODE, bool DMA = false, int RT = 1, int SRC = W_ROWS>
