@@ -612,16 +612,18 @@ static bool adc_arith(int res, int step, int floor_, int ceil_)
     range = range > 0.0f ? range : 1.0f;
     const float inv = 1.0f / ((float)step * range);
     const float k = half(inv), c = half((0.25f - (float)floor_) * inv), r = half(range);
+    // (single precision and without exits: four values at a time)
+    const float lo = (float)floor_, hi = (float)ceil_, two = 2.0f * (float)step;
+    int bad = 0;
     for (int s = -128; s <= 128; ++s) {
-        const int64_t x = s < floor_ ? floor_ : (s > ceil_ ? ceil_ : s);
-        int64_t code = (2 * (x - floor_) + step) / (2 * (int64_t)step);
-        code = code < (1ll << res) - 1 ? code : (1ll << res) - 1;
+        const float x = (float)s < lo ? lo : (float)s > hi ? hi : (float)s;
+        const float v = (2.0f * (x - lo) + (float)step) / two;
+        const float code = (float)(int)(v < top ? v : top);
         float t = half((float)s * k + c);
         t = t < 0.0f ? 0.0f : t > 1.0f ? 1.0f : t;
-        if (code >= 1024 || half(t * r + 1024.0f) != 1024.0f + (float)code)
-            return false;
+        bad |= !(code < 1024.0f) | !(half(t * r + 1024.0f) == 1024.0f + code);
     }
-    return true;
+    return !bad;
 }
 
 hipError_t launch_adc_prepared(const uint64_t *Q, int64_t n, int64_t ldq, int K, int start, int end, int res,

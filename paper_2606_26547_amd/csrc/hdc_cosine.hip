@@ -455,7 +455,7 @@ __device__ __forceinline__ void cosine_f6(uint8_t *smem, int64_t rbase, const ui
 #pragma unroll
         for (int i = 0; i < S::NQL; ++i) {
             const int w = w_lo + vc * W + qunit[i];
-            if (S::QB % (1024 * kWaves) == 0 || (i * kWaves + wave) * 1024 < S::QB)
+            if ((i * kWaves + wave) * 1024 < S::QB)
                 lds_dma16(Qwg, qoff[i] + 8u * (uint32_t)(w < w_hi ? w : w_lo), sq + (i * kWaves + wave) * 1024);
         }
 #pragma unroll

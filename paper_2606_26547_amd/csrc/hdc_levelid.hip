@@ -60,36 +60,48 @@ hipError_t launch_gather_cols(const void *X, int elem, int64_t n, int64_t ldx, i
 // division to find it, took 41 us for 32768 x 617; the bytes take 25).  A
 // workgroup's lanes cover FW features of 256 / FW rows: 64, or for narrow rows
 // the power of two that holds them, so that no lane is without a feature (4194304
-// x 1: 197 us with 64, 17.6 so).  The grid's limits are covered by striding.
+// x 1: 197 us with 64, 17.6 so).
 constexpr int kLqRows = 8;
 template <int FW>
+__device__ __forceinline__ void quantize_rows(const float *__restrict__ X, int64_t n, int64_t ldx, float l0, float w,
+                                              int64_t i0, int64_t f, int L, uint16_t *__restrict__ lev, int64_t ldl)
+{
+    constexpr int RW = 256 / FW;
+    float x[kLqRows];
+#pragma unroll
+    for (int r = 0; r < kLqRows; ++r)
+        x[r] = X[(i0 + r * RW < n ? i0 + r * RW : n - 1) * ldx + f];
+#pragma unroll
+    for (int r = 0; r < kLqRows; ++r) {
+        const float v = __fdiv_rn(__fmul_rn(__fsub_rn(x[r], l0), (float)L), w);
+        int level;
+        if (!(w > 0.0f) || !(v > 0.0f))
+            level = 0;
+        else if (v >= (float)(L - 1))
+            level = L - 1;
+        else
+            level = (int)floorf(v);
+        if (i0 + r * RW < n)
+            lev[(i0 + r * RW) * ldl + f] = (uint16_t)level;
+    }
+}
+
+// STRIDE: more rows or features than a grid holds (the loops cost 5 to 10%).
+template <int FW, bool STRIDE>
 __global__ __launch_bounds__(256) void k_level_quantize(const float *__restrict__ X, int64_t n, int F, int64_t ldx,
                                                         const float *__restrict__ lo, const float *__restrict__ hi,
                                                         int L, uint16_t *__restrict__ lev, int64_t ldl)
 {
-    constexpr int RW = 256 / FW;
-    for (int64_t f = (int64_t)blockIdx.y * FW + threadIdx.x % FW; f < F; f += (int64_t)gridDim.y * FW) {
-        const float l0 = lo[f], w = __fsub_rn(hi[f], l0);
-        for (int64_t i0 = (int64_t)blockIdx.x * (RW * kLqRows) + threadIdx.x / FW; i0 < n;
-             i0 += (int64_t)gridDim.x * (RW * kLqRows)) {
-            float x[kLqRows];
-#pragma unroll
-            for (int r = 0; r < kLqRows; ++r)
-                x[r] = X[(i0 + r * RW < n ? i0 + r * RW : n - 1) * ldx + f];
-#pragma unroll
-            for (int r = 0; r < kLqRows; ++r) {
-                const float v = __fdiv_rn(__fmul_rn(__fsub_rn(x[r], l0), (float)L), w);
-                int level;
-                if (!(w > 0.0f) || !(v > 0.0f))
-                    level = 0;
-                else if (v >= (float)(L - 1))
-                    level = L - 1;
-                else
-                    level = (int)floorf(v);
-                if (i0 + r * RW < n)
-                    lev[(i0 + r * RW) * ldl + f] = (uint16_t)level;
-            }
-        }
+    constexpr int64_t ROWS = 256 / FW * kLqRows;
+    const int64_t i0 = (int64_t)blockIdx.x * ROWS + threadIdx.x / FW;
+    if constexpr (STRIDE) {
+        for (int64_t f = (int64_t)blockIdx.y * FW + threadIdx.x % FW; f < F; f += (int64_t)gridDim.y * FW)
+            for (int64_t i = i0; i < n; i += (int64_t)gridDim.x * ROWS)
+                quantize_rows<FW>(X, n, ldx, lo[f], __fsub_rn(hi[f], lo[f]), i, f, L, lev, ldl);
+    } else {
+        const int f = blockIdx.y * FW + threadIdx.x % FW;
+        if (f < F)
+            quantize_rows<FW>(X, n, ldx, lo[f], __fsub_rn(hi[f], lo[f]), i0, f, L, lev, ldl);
     }
 }
 
@@ -100,7 +112,10 @@ static void launch_lq(const float *X, int64_t n, int F, int64_t ldx, const float
     constexpr int64_t rows = 256 / FW * kLqRows;
     const int64_t x = (n + rows - 1) / rows, y = ((int64_t)F + FW - 1) / FW;
     const dim3 grid((unsigned)(x < (1 << 22) ? x : 1 << 22), (unsigned)(y < 65535 ? y : 65535));
-    hipLaunchKernelGGL(k_level_quantize<FW>, grid, dim3(256), 0, st, X, n, F, ldx, lo, hi, L, lev, ldl);
+    if (x > grid.x || y > grid.y)
+        hipLaunchKernelGGL((k_level_quantize<FW, true>), grid, dim3(256), 0, st, X, n, F, ldx, lo, hi, L, lev, ldl);
+    else
+        hipLaunchKernelGGL((k_level_quantize<FW, false>), grid, dim3(256), 0, st, X, n, F, ldx, lo, hi, L, lev, ldl);
 }
 
 hipError_t launch_level_quantize(const float *X, int64_t n, int F, int64_t ldx, const float *lo, const float *hi,
@@ -284,7 +299,7 @@ template <bool HI> __device__ __forceinline__ uint32_t lid_addr(uint32_t pair, u
     return r;
 }
 
-template <int LPR, int R, bool FS>
+template <int LPR, int R, bool FS, bool PASSES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FS ? 1 : R == 1 ? 3 : 2)))
 void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl, const uint64_t *__restrict__ ID,
                 int64_t ldid, const uint64_t *__restrict__ LV, int L, int64_t ldlv, int D, uint64_t *__restrict__ H,
@@ -436,11 +451,26 @@ void k_level_id(const uint16_t *__restrict__ lev, int64_t n, int F, int64_t ldl,
             }
         }
         rb += gridDim.x;
-        if (rb * S::ROWS >= n)
+        if (!PASSES || rb * S::ROWS >= n)
             break;
         row0 += (int64_t)gridDim.x * S::ROWS;
         start();
     }
+}
+
+template <int LPR, int R, bool FS, bool PASSES>
+static hipError_t launch_level_id_grid(const dim3 &grid, const uint16_t *lev, int64_t n, int F, int64_t ldl,
+                                       const uint64_t *ID, int64_t ldid, const uint64_t *LV, int L, int64_t ldlv, int D,
+                                       uint64_t *H, int64_t ldh, hipStream_t st)
+{
+    // once per process and shape (thread-safe static initialisation)
+    static const hipError_t attr = hipFuncSetAttribute((const void *)k_level_id<LPR, R, FS, PASSES>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (attr != hipSuccess)
+        return attr;
+    hipLaunchKernelGGL((k_level_id<LPR, R, FS, PASSES>), grid, dim3(256), (LidShape<LPR, R, FS>::lds(L)), st, lev, n, F,
+                       ldl, ID, ldid, LV, L, ldlv, D, H, ldh);
+    return hipGetLastError();
 }
 
 template <int LPR, int R, bool FS>
@@ -449,22 +479,23 @@ static hipError_t launch_level_id_rows(const uint16_t *lev, int64_t n, int F, in
                                        int64_t ldh, hipStream_t st)
 {
     typedef LidShape<LPR, R, FS> S;
-    // once per process and shape (thread-safe static initialisation)
-    static const hipError_t attr = hipFuncSetAttribute((const void *)k_level_id<LPR, R, FS>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (attr != hipSuccess)
-        return attr;
     const int W = (D + 63) / 64;
-    // Where staging the levels costs like a quarter of a pass or more, a
-    // workgroup takes several passes of rows, as many as leave two workgroups per
-    // CU (20000 rows x 20 features, 256 levels, 4096 dimensions: 42 us with one
-    // pass, 23.6 so).  Else one pass, up to 2^22 workgroups (a grid takes 2^24).
+    // Where staging the levels costs like half a pass or more, and their LDS leaves
+    // too few workgroups per CU to hide it, a workgroup takes several passes of
+    // rows, as many as leave two per CU (20000 rows x 20 features, 256 levels, 4096
+    // dimensions: 42 us with one pass, 23 so; 60000 x 60, 2000 dimensions 87 and 51;
+    // but 8000 x 40, 100 levels, 10000 dimensions, four per CU: 28 and 31).  Else one
+    // pass (without the loop, whose registers cost 5%), up to 2^22 workgroups (a grid
+    // takes 2^24).
     const int64_t blocks = (n + S::ROWS - 1) / S::ROWS, wins = (W + S::W - 1) / S::W;
-    const int64_t most = !FS && (int64_t)(L + 1) * S::W > 64ll * F * R ? (512 + wins - 1) / wins : 1 << 22;
+    const bool stage = !FS && S::lds(L) > 40 * 1024 && (int64_t)(L + 1) * S::W > 64ll * F * R;
+    const int64_t most = stage ? (512 + wins - 1) / wins : 1 << 22;
     const dim3 grid((unsigned)(blocks < most ? blocks : most), (unsigned)wins);
-    hipLaunchKernelGGL((k_level_id<LPR, R, FS>), grid, dim3(256), S::lds(L), st, lev, n, F, ldl, ID, ldid, LV, L, ldlv, D,
-                       H, ldh);
-    return hipGetLastError();
+    if constexpr (!FS) {
+        if (blocks > most)
+            return launch_level_id_grid<LPR, R, FS, true>(grid, lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
+    }
+    return launch_level_id_grid<LPR, R, FS, false>(grid, lev, n, F, ldl, ID, ldid, LV, L, ldlv, D, H, ldh, st);
 }
 
 // Two rows per lane (each identity word read serves both, two waves per SIMD)
