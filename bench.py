@@ -760,9 +760,9 @@ def encode_side(dev, hdc, dg, torch, np, event_loop, sp, Xtr, ytr, Xte, Pd, Xqd,
             hp(Hq, out=lab)
         ms_wall, ms, _ = event_loop(step, 3, 1)
         _, ms_enc, _ = event_loop(lambda: hdc.level_id_encode(lev, ID, LV, Dl, out=Hq), 3, 1)
-        # VALU-bound: about 5 operations (bind XOR + carry-save adders) per
-        # (row, feature, 32 dimensions)
-        ops = n * F * (Dl / 32) * 5
+        # VALU-bound: about 3 operations per (row, feature, 32 dimensions): 2.8
+        # in the carry-save tree, whose first adders bind, and the level address
+        ops = n * F * (Dl / 32) * 3
         res["level_id"]["L=%d D=%d" % (L, Dl)] = {
             "test_accuracy": acc_te, "batch_accuracy": float((lab == yqd).float().mean().item()),
             "ms": ms, "queries_per_s": n / (ms / 1e3), "encode_ms": ms_enc,

@@ -546,9 +546,9 @@ __device__ __forceinline__ void cosine_f6(uint8_t *smem, int64_t rbase, const ui
 // The streaming search on the operand _prepare chose.  Two workgroups per CU:
 // one's LDS waits and barriers under the other's MFMAs.  100003 x 16384
 // against 100 classes: 518 us on the int8 operand (its four products per 64
-// dimensions and class tile the bound), 218 on FP6, the matrix cores about half
-// busy, the rest the operand's LDS reads (24 bytes per lane and two products)
-// and the barriers.  One kernel for both operands: a launch of each, the
+// dimensions and class tile the bound), 218 on FP6, the matrix cores busy 0.43 of
+// the cycles, the rest the operand's LDS reads (24 bytes per lane and two
+// products) and the barriers.  One kernel for both operands: a launch of each, the
 // unwanted one returning at once, cost 2 us.
 template <int KT, int QT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
